@@ -184,7 +184,11 @@ typedef struct qsq_trace_opts {
  *   lanes  resident-lane target of the persistent stepping launch, in units of
  *          256 lanes per compute unit, 1..15 (0: 8)
  *   wg     workgroup size code: 0 = 256, 1 = 64, 2 = 128 lanes
- *   gather 0 = automatic (3 where it applies, otherwise 1),
+ *   gather 0 = automatic: work lists short enough that the longest line sets
+ *          the time (the list's length is compared on the device) are stepped
+ *          with four lanes per half-line, in a launch shape of their own
+ *          (trilinear Cartesian fields, records below 2 GiB); other lists 3
+ *          where it applies, otherwise 1,
  *          1 = direct corner loads, 2 = per-lane LDS cache of
  *          the last cell's corners (FP32 or BF16 records and FP32 stepping,
  *          one field per call, field below 2 GiB; otherwise direct),

@@ -121,6 +121,10 @@ struct TraceJob {
     // lanes of a wave trace nearby lines; 0: seed order (maps, whose seeds
     // already follow a space-filling curve)
     int spatial_bits;
+    // work lists of up to this many half-lines are stepped with four lanes per
+    // line (0: none)
+    int64_t quad_max;
+    int simds;          // SIMDs of the device
 };
 
 // kernels the profiler can time

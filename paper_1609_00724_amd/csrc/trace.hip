@@ -1089,6 +1089,8 @@ static __global__ void k_land_compact(TraceJob job)
         if (job.rec.flag[it]) job.rec.work2[job.rec.wpos[it]] = (int32_t)half_record(job, it, n);
 }
 
+#include "quad.h"
+
 // ---------------------------------------------------------------------------
 // k_trace: persistent stepping kernel
 // ---------------------------------------------------------------------------
@@ -1112,6 +1114,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(EULER 
     double h_init = o.h_init, hmin = o.hmin;
     const int lane = (int)(threadIdx.x & 63);
     const int64_t total = *job.rec.n_work;
+    if (total <= job.quad_max) return;   // the four-lane kernel's call, or nothing to do
 
     // lane state
     double X[3] = {0, 0, 0}, s = 0.0;
@@ -2285,12 +2288,18 @@ __global__ void __launch_bounds__(256) k_land_geo(TraceJob job)
 static __global__ void k_set_u64(unsigned long long *p, unsigned long long v) { *p = v; }
 
 // counters of the stepping launch's work-list parts: part p starts past the
-// first items of its workgroups (blocks b with b mod nparts = p, wg lanes each)
-static __global__ void k_part_counters(TraceJob job, int blocks, int wg, int nparts)
+// first items of its workgroups (blocks b with b mod nparts = p, wg lanes each);
+// of the four-lane kernel's qblocks waves where the call is its own
+static __global__ void k_part_counters(TraceJob job, int blocks, int wg, int nparts, int qblocks)
 {
     const int p = (int)threadIdx.x;
     if (p >= nparts) return;
     const int64_t total = *job.rec.n_work;
+    if (total <= job.quad_max) {
+        // the four-lane kernel's only counter, past the first 16 items of each wave
+        if (p == 0) job.counter[kPartCounter] = (unsigned long long)qblocks * (kQuadWg / 64) * 16;
+        return;
+    }
     const int64_t nb = p < blocks ? (blocks - p + nparts - 1) / nparts : 0;
     job.counter[kPartCounter + p] = (unsigned long long)(total * p / nparts + nb * wg);
 }
@@ -2396,6 +2405,9 @@ static int resident_blocks(const void *kern, int wg, size_t lds)
     return n;
 }
 
+// record bytes that 32-bit offsets reach, with room for the neighbours' offsets
+constexpr uint64_t kCacheLimit = ((uint64_t)1 << 31) - ((uint64_t)1 << 26);
+
 // the stepping kernel of a gather variant for the job's stepper
 template <typename T, typename S, int MODE, int GATHER, bool BATCH>
 static const void *trace_kernel(bool euler)
@@ -2444,7 +2456,7 @@ static hipError_t launch_typed(const TraceJob &job, hipStream_t st)
         const uint64_t field_bytes = (uint64_t)node_bytes<S>() * job.g.n[0] * job.g.n[1] * job.g.n[2];
         const uint64_t brick_bytes = (uint64_t)node_bytes<S>() * 8 * ((job.g.n[0] + 1) / 2) *
                                      ((job.g.n[1] + 1) / 2) * ((job.g.n[2] + 1) / 2);
-        const uint64_t limit = ((uint64_t)1 << 31) - ((uint64_t)1 << 26);
+        const uint64_t limit = kCacheLimit;
         const bool fits = field_bytes < limit;
         // the direction records' variant keys cells by a 32-bit cell index
         const uint64_t ncells =
@@ -2480,12 +2492,30 @@ static hipError_t launch_typed(const TraceJob &job, hipStream_t st)
     const int64_t want = (2 * n_max + wg - 1) / wg;
     const int blocks = (int)(want < cap_blocks ? want : cap_blocks);
     const int nparts = (job.o.launch >> 9) & 1 ? kParts : 1;
-    hipLaunchKernelGGL(k_part_counters, dim3(1), dim3(64), 0, st, job, blocks, wg, nparts);
+    // few half-lines: four lanes each.  The count is known on the device
+    // only, so where it may fall on either side both kernels are launched and
+    // the one whose call it is not returns at once.
+    const void *quad = nullptr;
+    int qblocks = 0;
+    if constexpr (interp_order<MODE>() == 1) {
+        if (job.quad_max > 0) {
+            quad = euler ? reinterpret_cast<const void *>(&k_trace_quad<T, S, MODE, BATCH, true>)
+                         : reinterpret_cast<const void *>(&k_trace_quad<T, S, MODE, BATCH, false>);
+            // at least the workgroups of one wave per SIMD, so that a short list can spread
+            const int64_t full = (int64_t)cus * resident_blocks(quad, kQuadWg, 0);
+            const int64_t need = (2 * n_max * 4 + kQuadWg - 1) / kQuadWg;
+            qblocks = (int)(need < cus ? cus : need < full ? need : full);
+        }
+    }
+    hipLaunchKernelGGL(k_part_counters, dim3(1), dim3(64), 0, st, job, blocks, wg, nparts, qblocks);
     const bool prof = profiling();
     void *tok = nullptr;
     if (prof) prof_begin(kProfStep, st, &tok);
     void *args[] = {const_cast<TraceJob *>(&job)};
-    const hipError_t le = hipLaunchKernel(kern, dim3(blocks), dim3(wg), args, lds, st);
+    hipError_t le = hipSuccess;
+    if (quad) le = hipLaunchKernel(quad, dim3(qblocks), dim3(kQuadWg), args, 0, st);
+    if (le == hipSuccess && (!quad || 2 * n_max > job.quad_max))
+        le = hipLaunchKernel(kern, dim3(blocks), dim3(wg), args, lds, st);
     if (prof) prof_end(tok, st);
     if (le != hipSuccess) return le;
     int64_t lb = (2 * n_max + 255) / 256;
@@ -2606,9 +2636,46 @@ static hipError_t dispatch(const TraceJob &job, int step_dtype, hipStream_t st)
     return paper ? launch_typed<double, double, P, BATCH>(job, st) : launch_typed<double, double, N, BATCH>(job, st);
 }
 
+// Largest work list that the four-lane kernel takes under an automatic gather
+// (0: none; a named gather always gets the one-lane kernel).  A list that fits
+// the grid lasts as long as its longest line, and four lanes a line shorten
+// that chain: 64 000 half-lines of 224 x 224 x 112 cells at a 1-cell cap take
+// 1.09 ms against 2.10 (8 cells: 0.43 against 0.53).  A longer list is bound
+// by VALU issue, where four lanes a line cost 1.7 times the instructions and
+// the refills weigh more the shorter the lines: 128 000 half-lines 1.71
+// against 2.25 ms (64^2 x 32 cells at 8 cells a step 0.42 against 0.40),
+// 512 000 4.07 against 4.41 (1.02 against 0.87).  So lines of 32 steps or more
+// across the box's longest edge go four lanes each up to 2^19, shorter ones up
+// to 2^16.  FP64 stepping keeps half as many waves resident and a batch
+// reloads its grid with every line: up to 2^17 (FP64, 128^2 x 64 cells at 1
+// cell: 128 000 half-lines 1.53 against 1.74 ms, 256 000 2.45 against 2.34).
+static int64_t quad_limit(const Geom &g, double h_max, int storage, bool f32, bool batch)
+{
+    // records are addressed with 32-bit byte offsets, keys formed by 24-bit products
+    const uint64_t rec = storage == QSQ_F64 ? 32 : storage == QSQ_F32 ? 16 : 8;
+    const uint64_t xy = (uint64_t)g.n[0] * (uint64_t)g.n[1];
+    if (xy >= ((uint64_t)1 << 23) || (uint64_t)g.n[2] >= ((uint64_t)1 << 23) ||
+        xy * (uint64_t)g.n[2] * rec >= kCacheLimit)
+        return 0;
+    const double edge = fmax(fmax(g.hi[0] - g.lo[0], g.hi[1] - g.lo[1]), g.hi[2] - g.lo[2]);
+    if (!(edge >= 32.0 * h_max)) return (int64_t)1 << 16;
+    return (int64_t)1 << (f32 && !batch ? 19 : 17);
+}
+
+// longest step of a line
+static double step_cap(const StepOpts &o, double h_init, double h_max)
+{
+    return o.stepper == QSQ_STEPPER_EULER ? h_init : h_max;
+}
+
 hipError_t launch_trace(const TraceJob &job, int step_dtype, hipStream_t st)
 {
-    return dispatch<false>(job, step_dtype, st);
+    TraceJob j = job;
+    j.simds = 4 * device_cu_count();
+    j.quad_max = 0;
+    if (((job.o.launch >> 6) & 7) == 0 && job.mode <= 1)
+        j.quad_max = quad_limit(job.g, step_cap(job.o, job.o.h_init, job.o.h_max), job.storage, step_dtype == QSQ_F32, false);
+    return dispatch<false>(j, step_dtype, st);
 }
 
 // The set table travels in kernel arguments, a few entries per launch, so
@@ -2637,7 +2704,18 @@ hipError_t launch_trace_batch(const TraceJob &job, const SetDesc *host_sets, int
         for (int k = 0; k < c.count; ++k) c.d[k] = host_sets[first + k];
         hipLaunchKernelGGL(k_put_sets, dim3(1), dim3(64), 0, st, table, c);
     }
-    return dispatch<true>(job, step_dtype, st);
+    TraceJob j = job;
+    j.simds = 4 * device_cu_count();
+    j.quad_max = 0;
+    if (((job.o.launch >> 6) & 7) == 0) {
+        j.quad_max = (int64_t)1 << 30;
+        for (int k = 0; k < nsets; ++k) {
+            const SetDesc &d = host_sets[k];
+            const int64_t q = quad_limit(d.g, step_cap(job.o, d.h_init, d.h_max), job.storage, step_dtype == QSQ_F32, true);
+            if (q < j.quad_max) j.quad_max = q;
+        }
+    }
+    return dispatch<true>(j, step_dtype, st);
 }
 
 #endif  // QSQ_TRACE_HIGH_TU
