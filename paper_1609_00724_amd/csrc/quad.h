@@ -3,9 +3,11 @@
 // evaluates component c of the field (lane 3 repeats lane 2), and the values
 // that every component needs (cell fractions, deviations) cross the quad by
 // DPP moves.  An attempt is a serial chain of six evaluations; a lane that does
-// a third of the components issues about a third of the instructions, so the
-// chain is shorter, and the lane's state (18 stage slopes and 8 corner values
-// instead of 54 and 24) lets more waves stay resident.  Included by trace.hip
+// a third of the components issues about a third of the instructions (640
+// vector instructions against 1490), so the chain is shorter: 2.4 us an
+// attempt against 5.4 where one line is all a SIMD has.  The lane's state (18
+// stage slopes and 8 corner values instead of 54 and 24) lets four waves stay
+// resident on a SIMD instead of two.  Included by trace.hip
 // after the evaluation helpers it shares with the one-lane kernel; every
 // operation on a component is the one-lane kernel's, in its order, so the
 // results are the same bit for bit.
@@ -328,26 +330,82 @@ __device__ __forceinline__ QuadGeom<T> quad_geom(const Geom &g, int c, bool dup)
     return q;
 }
 
-// Persistent stepping kernel of calls with few half-lines (quad_limit), up to 16
-// half-lines per wave.  A list of fewer than 16 lines per SIMD is spread over
-// one wave per SIMD (a wave with fewer lines waits for fewer cell moves); a
-// longer one goes 16 lines per wave, and what does not fit the grid at first
-// goes, with one atomic per chunk of 16, to the quads that fall idle.
-constexpr int kQuadWg = 256;
+// Work distribution of the four-lane kernels, up to 16 half-lines per wave.  A
+// list of fewer than 16 lines per SIMD is spread over one wave per SIMD (a
+// wave with fewer lines waits for fewer cell moves); a longer one goes 16
+// lines per wave, and what does not fit the grid at first goes, with one
+// atomic per chunk of 16, to the quads that fall idle.  start(record) sets up
+// the quad's line, attempt() takes one step and clears `active` at its end.
+constexpr int kQuadWg = 256, kQuadLines = 16;
+
+template <typename Start, typename Attempt>
+__device__ __forceinline__ void quad_drive(const TraceJob &job, int64_t total, bool &active, Start start, Attempt attempt)
+{
+    const int lane = (int)(threadIdx.x & 63), qi = lane >> 2;
+    const int64_t wave = (int64_t)blockIdx.x * (kQuadWg / 64) + (threadIdx.x >> 6);
+    const int per = total >= (int64_t)job.simds * kQuadLines ? kQuadLines : (int)((total + job.simds - 1) / job.simds);
+    unsigned long long *count = job.counter + kPartCounter;
+    int64_t item = wave * per + qi;
+    if (qi >= per || item >= total) item = -1;
+    // the counter may hold items past the first of every wave
+    bool more = total > (int64_t)gridDim.x * (kQuadWg / 64) * per;
+    int64_t cnext = 0, cend = 0;   // the wave's unassigned items [cnext, cend)
+    for (;;) {
+        if (!active && item >= 0) {
+            start((int64_t)job.rec.work[item]);
+            active = true;
+        }
+        if (__ballot(active) == 0 && !more) break;
+        if (active) attempt();
+        item = -1;
+        const uint64_t need = __ballot(!active);
+        if (more && need) {
+            // items for the idle quads: what is left of the wave's chunk, then a fresh one
+            const int j = __popcll(need & ((1ull << (lane & ~3)) - 1ull)) >> 2, k = __popcll(need) >> 2;
+            const int64_t avail = cend - cnext;
+            if (j < avail) item = cnext + j;
+            if (avail < k) {
+                unsigned long long b = 0;
+                if (lane == 0) b = atomicAdd(count, (unsigned long long)kQuadLines);
+                const int64_t fresh = (int64_t)__shfl(b, 0);
+                more = fresh < total;
+                cend = more ? min(fresh + kQuadLines, total) : fresh;
+                if (j >= avail && fresh + (j - avail) < cend) item = fresh + (j - avail);
+                cnext = min(fresh + (k - avail), cend);
+            } else {
+                cnext += k;
+            }
+            if (active) item = -1;
+        }
+    }
+}
+
+// work counters: one lane of each quad counts its lines
+__device__ __forceinline__ void quad_count(unsigned long long *work, const QuadCount &cnt)
+{
+    const int lane = (int)(threadIdx.x & 63);
+    unsigned long long v[4] = {cnt.att, cnt.ev, cnt.act, cnt.land};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        if (lane & 3) v[k] = 0;
+#pragma unroll
+        for (int s = 32; s >= 4; s >>= 1) v[k] += __shfl_xor(v[k], s);
+    }
+    if (lane == 0 && (v[0] | v[1] | v[2] | v[3]))
+#pragma unroll
+        for (int k = 0; k < 4; ++k) atomicAdd(&work[k], v[k]);
+}
+
+// Stepping kernel of calls with few half-lines (quad_limit)
 template <typename T, typename S, int MODE, bool BATCH, bool EULER>
 __global__ void __launch_bounds__(kQuadWg) k_trace_quad(TraceJob job)
 {
-    constexpr int kLines = 16;
     constexpr bool FIRST = !BATCH && std::is_same<T, float>::value && std::is_same<S, float>::value;
     const StepOpts &o = job.o;
-    const int lane = (int)(threadIdx.x & 63), qi = lane >> 2, c3 = lane & 3, c = c3 == 3 ? 2 : c3;
+    const int c3 = (int)(threadIdx.x & 3), c = c3 == 3 ? 2 : c3;
     const int64_t total = *job.rec.n_work;
     if (total > job.quad_max) return;   // the one-lane kernel's call
-    const int64_t wave = (int64_t)blockIdx.x * (kQuadWg / 64) + (threadIdx.x >> 6), P = 2 * job.rec.cap;
-    // lines of a wave at the start: 16, or fewer while there is a SIMD for every wave
-    const int per = total >= (int64_t)job.simds * kLines ? kLines : (int)((total + job.simds - 1) / job.simds);
-    const bool fits = total <= (int64_t)gridDim.x * (kQuadWg / 64) * per;
-    unsigned long long *count = job.counter + kPartCounter;
+    const int64_t P = 2 * job.rec.cap;
     const T rtol = (T)o.rtol, atol = (T)o.atol;
     T hmax = (T)o.h_max;
     double h_init = o.h_init, hmin = o.hmin;
@@ -357,16 +415,13 @@ __global__ void __launch_bounds__(kQuadWg) k_trace_quad(TraceJob job)
     QuadCell<T> cell{};
     cell.key = -1;
     QuadCount cnt{};
-    int64_t item = wave * per + qi;
-    if (qi >= per || item >= total) item = -1;
-    bool more = !fits;             // the counter may hold items yet
-    int64_t cnext = 0, cend = 0;   // the wave's unassigned items [cnext, cend)
-    for (;;) {
-        if (!st.active && item >= 0) {
-            st.rec = job.rec.work[item];
-            const int dir = st.rec >= job.rec.cap ? 1 : 0;
+    quad_drive(
+        job, total, st.active,
+        [&](int64_t rec) {
+            st.rec = rec;
+            const int dir = rec >= job.rec.cap ? 1 : 0;
             if constexpr (BATCH) {
-                const SetDesc &sd = job.sets[job.set_of[dir ? st.rec - job.rec.cap : st.rec]];
+                const SetDesc &sd = job.sets[job.set_of[dir ? rec - job.rec.cap : rec]];
                 g = quad_geom<T, S>(sd.g, c, c3 == 3);
                 recs = static_cast<const char *>(sd.nodes);
                 h_init = sd.h_init;
@@ -376,51 +431,15 @@ __global__ void __launch_bounds__(kQuadWg) k_trace_quad(TraceJob job)
             }
             // the seed pass left x0 and the frame (eq. 9) in the record
             st.sigma = dir ? (T)-1 : (T)1;
-            st.X = job.rec.y[c * P + st.rec];
-            st.D1 = (T)job.rec.y[(3 + c) * P + st.rec];
-            st.D2 = (T)job.rec.y[(6 + c) * P + st.rec];
+            st.X = job.rec.y[c * P + rec];
+            st.D1 = (T)job.rec.y[(3 + c) * P + rec];
+            st.D2 = (T)job.rec.y[(6 + c) * P + rec];
             st.s = 0.0;
             st.h = (T)h_init;
             st.attempts = 0;
             st.have_k1 = false;
-            st.active = true;
             ++cnt.act;
-        }
-        if (__ballot(st.active) == 0 && !more) break;
-        if (st.active)
-            quad_attempt<T, S, MODE, FIRST, EULER>(recs, g, o, rtol, atol, hmax, hmin, c3, job.rec, st, cell, cnt);
-        item = -1;
-        const uint64_t need = __ballot(!st.active);
-        if (more && need) {
-            // items for the idle quads: what is left of the wave's chunk, then a fresh one
-            const int j = __popcll(need & ((1ull << (lane & ~3)) - 1ull)) >> 2, k = __popcll(need) >> 2;
-            const int64_t avail = cend - cnext;
-            if (j < avail) item = cnext + j;
-            if (avail < k) {
-                unsigned long long b = 0;
-                if (lane == 0) b = atomicAdd(count, (unsigned long long)kLines);
-                const int64_t fresh = (int64_t)__shfl(b, 0);
-                more = fresh < total;
-                cend = more ? min(fresh + kLines, total) : fresh;
-                if (j >= avail && fresh + (j - avail) < cend) item = fresh + (j - avail);
-                cnext = min(fresh + (k - avail), cend);
-            } else {
-                cnext += k;
-            }
-            if (st.active) item = -1;
-        }
-    }
-    if (job.work) {
-        // one lane of each quad counts its lines
-        unsigned long long v[4] = {cnt.att, cnt.ev, cnt.act, cnt.land};
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            if (c3) v[k] = 0;
-#pragma unroll
-            for (int s2 = 32; s2 >= 4; s2 >>= 1) v[k] += __shfl_xor(v[k], s2);
-        }
-        if (lane == 0 && (v[0] | v[1] | v[2] | v[3]))
-#pragma unroll
-            for (int k = 0; k < 4; ++k) atomicAdd(&job.work[k], v[k]);
-    }
+        },
+        [&] { quad_attempt<T, S, MODE, FIRST, EULER>(recs, g, o, rtol, atol, hmax, hmin, c3, job.rec, st, cell, cnt); });
+    if (job.work) quad_count(job.work, cnt);
 }

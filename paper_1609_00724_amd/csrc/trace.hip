@@ -1972,320 +1972,7 @@ __global__ void __launch_bounds__(256) k_assemble(TraceJob job)
 // ---------------------------------------------------------------------------
 // General geometry: stepping and landing in physical coordinates
 // ---------------------------------------------------------------------------
-// f(y) of eq. (1)+(5) (Cartesian) or eq. (2)+(6) (spherical: the metric factors
-// divide each component) at the physical point x; returns |u|^2
-template <typename T, typename S, int MODE>
-__device__ __forceinline__ T rhs_geo(const S *__restrict__ nodes, const Geom &g, const double x[3], T sigma,
-                                     const T d1[3], const T d2[3], T kx[3], T k1[3], T k2[3])
-{
-    T u[3], G[3][3], mag;
-    field_at_geo<T, S, MODE, false>(nodes, g, x, u, G, mag);
-    const T un2 = rhs_from(sigma, u, G, d1, d2, kx, k1, k2);
-    if (g.geometry == QSQ_GEOMETRY_SPHERICAL) {
-        double sc[3];
-        geo_scale(g, x, sc);
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            const T m = (T)(1.0 / sc[i]);
-            kx[i] *= m;
-            k1[i] *= m;
-            k2[i] *= m;
-        }
-    }
-    return un2;
-}
-
-// one FP64 Cash-Karp step of the whole state in physical coordinates (5th-order end)
-template <typename S, int MODE>
-__device__ void ck54_geo(const S *__restrict__ nodes, const Geom &g, double sigma, const double y[9], double hs,
-                         double yo[9])
-{
-    double K[6][9];
-    const double A[6][5] = {{0, 0, 0, 0, 0},
-                            {ck::a21, 0, 0, 0, 0},
-                            {ck::a31, ck::a32, 0, 0, 0},
-                            {ck::a41, ck::a42, ck::a43, 0, 0},
-                            {ck::a51, ck::a52, ck::a53, ck::a54, 0},
-                            {ck::a61, ck::a62, ck::a63, ck::a64, ck::a65}};
-#pragma unroll 1
-    for (int st = 0; st < 6; ++st) {
-        double yt[9];
-#pragma unroll
-        for (int i = 0; i < 9; ++i) {
-            double a = 0;
-            for (int j = 0; j < st; ++j) a = fma(A[st][j], K[j][i], a);
-            yt[i] = fma(hs, a, y[i]);
-        }
-        double kx[3], k1[3], k2[3];
-        rhs_geo<double, S, MODE>(nodes, g, yt, sigma, yt + 3, yt + 6, kx, k1, k2);
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            K[st][i] = kx[i];
-            K[st][3 + i] = k1[i];
-            K[st][6 + i] = k2[i];
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < 9; ++i)
-        yo[i] = y[i] + hs * (ck::b1 * K[0][i] + ck::b3 * K[2][i] + ck::b4 * K[3][i] + ck::b6 * K[5][i]);
-}
-
-// Adaptive Cash-Karp 5(4) stepping of general-geometry half-lines: one lane
-// per half-line, items taken one at a time from the work counter; the same
-// error norm, controller, limits and statuses as the uniform-grid kernel,
-// positions held in FP64, stage arithmetic in T.
-template <typename T, typename S, int MODE>
-__global__ void __launch_bounds__(256) k_trace_geo(TraceJob job)
-{
-    const S *__restrict__ nodes = static_cast<const S *>(job.nodes);
-    const Geom g = job.g;
-    const StepOpts &o = job.o;
-    const int64_t total = *job.rec.n_work;
-    const int64_t P = 2 * job.rec.cap;
-    const T rtol = (T)o.rtol, atol = (T)o.atol;
-    unsigned long long c_att = 0, c_ev = 0, c_act = 0, c_land = 0;
-    for (;;) {
-        const int64_t it = (int64_t)atomicAdd(job.counter, 1ull);
-        if (it >= total) break;
-        const int64_t rec = job.rec.work[it];
-        const T sigma = rec >= job.rec.cap ? (T)-1 : (T)1;
-        double X[3];
-        T D1[3], D2[3];
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            X[k] = job.rec.y[k * P + rec];
-            D1[k] = (T)job.rec.y[(3 + k) * P + rec];
-            D2[k] = (T)job.rec.y[(6 + k) * P + rec];
-        }
-        double s = 0.0;
-        T h = (T)o.h_init;
-        int attempts = 0, stop = -1;
-        ++c_act;
-        for (;;) {
-            if (attempts >= o.max_steps) {
-                stop = QSQ_END_MAX_STEPS;
-                break;
-            }
-            T K[6][9];
-            // first stage (also the null test at the current point)
-            {
-                T kx[3], k1[3], k2[3];
-                const T un2 = rhs_geo<T, S, MODE>(nodes, g, X, sigma, D1, D2, kx, k1, k2);
-                ++c_ev;
-                if (un2 < (T)1e-12) {
-                    stop = QSQ_END_NULL;
-                    break;
-                }
-                for (int i = 0; i < 3; ++i) {
-                    K[0][i] = kx[i];
-                    K[0][3 + i] = k1[i];
-                    K[0][6 + i] = k2[i];
-                }
-            }
-            T hs = h < (T)o.h_max ? h : (T)o.h_max;
-            bool last = false;
-            if (o.max_length > 0.0 && (double)hs >= o.max_length - s) {
-                hs = (T)(o.max_length - s);
-                last = true;
-            }
-            const double A[6][5] = {{0, 0, 0, 0, 0},
-                                    {ck::a21, 0, 0, 0, 0},
-                                    {ck::a31, ck::a32, 0, 0, 0},
-                                    {ck::a41, ck::a42, ck::a43, 0, 0},
-                                    {ck::a51, ck::a52, ck::a53, ck::a54, 0},
-                                    {ck::a61, ck::a62, ck::a63, ck::a64, ck::a65}};
-#pragma unroll 1
-            for (int st = 1; st < 6; ++st) {
-                double xs[3];
-                T d1[3], d2[3];
-                for (int i = 0; i < 3; ++i) {
-                    T ax = 0, a1 = 0, a2 = 0;
-                    for (int j = 0; j < st; ++j) {
-                        ax = fma((T)A[st][j], K[j][i], ax);
-                        a1 = fma((T)A[st][j], K[j][3 + i], a1);
-                        a2 = fma((T)A[st][j], K[j][6 + i], a2);
-                    }
-                    xs[i] = X[i] + (double)(hs * ax);
-                    d1[i] = fma(hs, a1, D1[i]);
-                    d2[i] = fma(hs, a2, D2[i]);
-                }
-                T kx[3], k1[3], k2[3];
-                rhs_geo<T, S, MODE>(nodes, g, xs, sigma, d1, d2, kx, k1, k2);
-                ++c_ev;
-                for (int i = 0; i < 3; ++i) {
-                    K[st][i] = kx[i];
-                    K[st][3 + i] = k1[i];
-                    K[st][6 + i] = k2[i];
-                }
-            }
-            double Xn[3];
-            T D1n[3], D2n[3], err = 0, fsum = 0;
-            for (int i = 0; i < 9; ++i) {
-                const T b5 = ck_b5(K[0][i], K[2][i], K[3][i], K[5][i]);
-                const T e = ck_e(K[0][i], K[2][i], K[3][i], K[4][i], K[5][i]);
-                T yo, yn;
-                if (i < 3) {
-                    Xn[i] = X[i] + (double)(hs * b5);
-                    yo = (T)X[i];
-                    yn = (T)Xn[i];
-                } else if (i < 6) {
-                    D1n[i - 3] = fma(hs, b5, D1[i - 3]);
-                    yo = D1[i - 3];
-                    yn = D1n[i - 3];
-                } else {
-                    D2n[i - 6] = fma(hs, b5, D2[i - 6]);
-                    yo = D2[i - 6];
-                    yn = D2n[i - 6];
-                }
-                err = fmax(err, fabs(hs * e) / err_scale(atol, rtol, yo, yn));
-                fsum += yn + e;
-            }
-            ++attempts;
-            ++c_att;
-            if (!isfinite(fsum)) {
-                stop = QSQ_END_NONFINITE;
-                break;
-            }
-            if (err > (T)1) {
-                const T f = (T)0.9 * (T)pow((double)err, -0.25);
-                h = hs * (f > (T)0.2 ? f : (T)0.2);
-                if ((double)h < o.hmin) {
-                    stop = QSQ_END_UNDERFLOW;
-                    break;
-                }
-                continue;
-            }
-            if (outside_box(g, Xn[0], Xn[1], Xn[2])) {
-                const double y[9] = {X[0], X[1], X[2], (double)D1[0], (double)D1[1], (double)D1[2],
-                                     (double)D2[0], (double)D2[1], (double)D2[2]};
-                put_rec(job.rec, rec, y, s, (double)hs, kPendingLand, attempts);
-                ++c_land;
-                break;
-            }
-            for (int i = 0; i < 3; ++i) {
-                X[i] = Xn[i];
-                D1[i] = D1n[i];
-                D2[i] = D2n[i];
-            }
-            if (last) {
-                s = o.max_length;
-                stop = QSQ_END_MAX_LENGTH;
-                break;
-            }
-            s += (double)hs;
-            const T f = err > (T)0 ? (T)0.9 * (T)pow((double)err, -0.2) : (T)5;
-            h = hs * (f < (T)5 ? f : (T)5);
-        }
-        if (stop >= 0) {
-            const double y[9] = {X[0], X[1], X[2], (double)D1[0], (double)D1[1], (double)D1[2],
-                                 (double)D2[0], (double)D2[1], (double)D2[2]};
-            put_rec(job.rec, rec, y, s, 0.0, stop, attempts);
-        }
-    }
-    if (job.work) {
-        atomicAdd(&job.work[0], c_att);
-        atomicAdd(&job.work[1], c_ev);
-        atomicAdd(&job.work[2], c_act);
-        atomicAdd(&job.work[3], c_land);
-    }
-}
-
-// signed distance past face f of the FP64 step's end from y over length h
-template <typename S, int MODE>
-__device__ double face_gap_geo(const S *nodes, const Geom &g, double sigma, const double y[9], double h, int f,
-                               double yo[9])
-{
-    if (h > 0.0) {
-        ck54_geo<S, MODE>(nodes, g, sigma, y, h, yo);
-    } else {
-        for (int k = 0; k < 9; ++k) yo[k] = y[k];
-    }
-    return beyond_face(g, yo, f);
-}
-
-// FP64 landing of general-geometry half-lines: for every face the trial step
-// crosses, Illinois regula falsi from the secant point on the face gap of the
-// FP64 step's end over its length (|gap| <= gtol); the face reached first (the
-// shortest length; exact ties keep the lower face) takes the line, the state
-// is stepped there and snapped onto the face
-template <typename S, int MODE>
-__global__ void __launch_bounds__(256) k_land_geo(TraceJob job)
-{
-    const int64_t total = *job.rec.n_land;
-    for (int64_t it = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; it < total;
-         it += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t r = job.rec.work2[it];
-        const S *__restrict__ nodes = static_cast<const S *>(job.nodes);
-        const Geom &g = job.g;
-        const double gtol = job.o.gtol;
-        const double sigma = r >= job.rec.cap ? -1.0 : 1.0;
-        double y[9], s, hs, yo[9];
-        get_rec(job.rec, r, y, s, hs);
-        ck54_geo<S, MODE>(nodes, g, sigma, y, hs, yo);
-        double best = INFINITY;
-        int face = -1;
-        for (int f = 0; f < 6; ++f) {
-            if (!(beyond_face(g, yo, f) > 0.0)) continue;
-            double a = 0.0, b = hs, ga = face_gap_geo<S, MODE>(nodes, g, sigma, y, a, f, yo), gb, root;
-            if (ga >= 0.0) {
-                root = 0.0;
-            } else {
-                gb = face_gap_geo<S, MODE>(nodes, g, sigma, y, b, f, yo);
-                int side = 0;
-                root = -1.0;
-                for (int k = 0; k < 200 && root < 0.0; ++k) {
-                    const double c = (a * gb - b * ga) / (gb - ga);
-                    const double gc = face_gap_geo<S, MODE>(nodes, g, sigma, y, c, f, yo);
-                    if (fabs(gc) <= gtol) {
-                        root = c;
-                    } else if (gc > 0.0) {
-                        b = c;
-                        gb = gc;
-                        if (side == +1) ga *= 0.5;
-                        side = +1;
-                    } else {
-                        a = c;
-                        ga = gc;
-                        if (side == -1) gb *= 0.5;
-                        side = -1;
-                    }
-                    if (root < 0.0 && b - a <= 1e-15 * hs) root = ga > -gb ? a : b;
-                }
-                if (root < 0.0) root = ga > -gb ? a : b;
-            }
-            if (root < best) {
-                best = root;
-                face = f;
-            }
-        }
-        if (face < 0) {
-            // the trial step left the box in FP32 but the FP64 step does not:
-            // end on the face nearest the FP64 end
-            best = hs;
-            double gmax = -INFINITY;
-            for (int f = 0; f < 6; ++f) {
-                const double gp = beyond_face(g, yo, f);
-                if (gp > gmax) {
-                    gmax = gp;
-                    face = f;
-                }
-            }
-        }
-        double yl[9];
-        if (best > 0.0) {
-            ck54_geo<S, MODE>(nodes, g, sigma, y, best, yl);
-        } else {
-            for (int k = 0; k < 9; ++k) yl[k] = y[k];
-        }
-        const int d = face >> 1;
-        const double snap = (face & 1) ? pick3(g.hi, d) : pick3(g.lo, d);
-        for (int k = 0; k < 3; ++k)
-            if (k == d) yl[k] = snap;
-        put_rec(job.rec, r, yl, s + best, 0.0, face, job.rec.attempts[r]);
-    }
-}
-
-static __global__ void k_set_u64(unsigned long long *p, unsigned long long v) { *p = v; }
+#include "quad_geo.h"
 
 // counters of the stepping launch's work-list parts: part p starts past the
 // first items of its workgroups (blocks b with b mod nparts = p, wg lanes each);
@@ -2559,17 +2246,24 @@ static hipError_t launch_geo(const TraceJob &job, hipStream_t st)
     hipLaunchKernelGGL((k_seed_pass<S, MODE, false>), dim3(blocks_of(n_max)), dim3(256), 0, st, job);
     launch_scan_i32(job.rec.flag, job.rec.n_items, 2 * n_max, job.rec.scan_tmp, job.rec.wpos, job.rec.n_work, st);
     hipLaunchKernelGGL(k_compact, dim3(blocks_of(2 * n_max)), dim3(256), 0, st, job);
-    hipLaunchKernelGGL(k_set_u64, dim3(1), dim3(1), 0, st, job.counter, 0ull);
+    TraceJob jq = job;
+    jq.quad_max = INT64_MAX;
+    jq.simds = 4 * cus;
+    const void *kern = reinterpret_cast<const void *>(&k_trace_geo<T, S, MODE>);
+    const int64_t full = (int64_t)cus * resident_blocks(kern, kQuadWg, 0);
+    const int64_t need = (2 * n_max * 4 + kQuadWg - 1) / kQuadWg;
+    const int qblocks = (int)(need < cus ? cus : need < full ? need : full);
+    hipLaunchKernelGGL(k_part_counters, dim3(1), dim3(64), 0, st, jq, 0, 0, 1, qblocks);
     const bool prof = profiling();
     void *tok = nullptr;
     if (prof) prof_begin(kProfStep, st, &tok);
-    hipLaunchKernelGGL((k_trace_geo<T, S, MODE>), dim3(cus * 8), dim3(256), 0, st, job);
+    hipLaunchKernelGGL((k_trace_geo<T, S, MODE>), dim3(qblocks), dim3(kQuadWg), 0, st, jq);
     if (prof) prof_end(tok, st);
     if (prof) prof_begin(kProfLand, st, &tok);
     hipLaunchKernelGGL(k_land_flags, dim3(blocks_of(2 * n_max)), dim3(256), 0, st, job);
     launch_scan_i32(job.rec.flag, job.rec.n_items, 2 * n_max, job.rec.scan_tmp, job.rec.wpos, job.rec.n_land, st);
     hipLaunchKernelGGL(k_land_compact, dim3(blocks_of(2 * n_max)), dim3(256), 0, st, job);
-    hipLaunchKernelGGL((k_land_geo<S, MODE>), dim3(blocks_of(2 * n_max)), dim3(256), 0, st, job);
+    hipLaunchKernelGGL((k_land_geo<S, MODE>), dim3(blocks_of(4 * 2 * n_max)), dim3(kQuadWg), 0, st, job);
     if (prof) prof_end(tok, st);
     if (prof) prof_begin(kProfAssemble, st, &tok);
     hipLaunchKernelGGL((k_assemble<S, MODE, false>), dim3(blocks_of(n_max)), dim3(256), 0, st, job);

@@ -103,3 +103,23 @@ def test_batch(step):
     torch.cuda.synchronize()
     assert torch.equal(res[0][1], res[1][1])
     assert all(_equal(a, b) for a, b in zip(res[0][0], res[1][0]))
+
+
+@pytest.mark.parametrize("n", [1, 130, 20000, 45000])
+def test_general_geometry_list_lengths(n):
+    """A spherical trace of n seeds (spread, full waves, refills) gives every
+    seed what it gets in a call of its own few."""
+    import torch
+
+    import paper_1609_00724_amd as q
+    lo, hi, g = (-0.3, -0.3, 1.0), (0.3, 0.3, 1.5), (25, 21, 17)
+    ch = np.array([[0.93, 0.05, 0.1, 1.0], [0.95, -0.1, -0.05, -1.0]])
+    b, origin, spacing = synth.sample_charges_spherical(ch, g, lo, hi, dtype=np.float32)
+    f = q.field_init(*(torch.from_numpy(np.ascontiguousarray(c)).cuda() for c in b), origin, spacing, geometry="spherical")
+    s = torch.from_numpy(synth.random_seeds(n + 1, n, lo=lo, hi=hi)).cuda()
+    kw = dict(rtol=1e-4, atol=1e-4, h_init=0.002, h_max=0.02, want_steps=True)
+    full = q.trace(f, s, **kw)
+    idx = torch.arange(0, n, max(1, n // 50), device=s.device)
+    part = q.trace(f, s[idx], **kw)
+    torch.cuda.synchronize()
+    assert _equal({k: v[..., idx] for k, v in full.items()}, part)
