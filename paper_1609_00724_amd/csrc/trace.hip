@@ -1619,6 +1619,7 @@ __global__ void __launch_bounds__(256) k_land(TraceJob job)
     for (int64_t it = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; it < total;
          it += (int64_t)gridDim.x * blockDim.x) {
         const int64_t r = job.rec.work2[it];
+        if (job.rec.status[r] != kPendingLand) continue;
         const int dir = r >= job.rec.cap ? 1 : 0;
         const int64_t i = dir ? r - job.rec.cap : r;
         const S *__restrict__ nodes = static_cast<const S *>(job.nodes);
@@ -1717,6 +1718,8 @@ __global__ void __launch_bounds__(256) k_land_final(TraceJob job)
     for (int64_t it = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; it < total;
          it += (int64_t)gridDim.x * blockDim.x) {
         const int64_t r = job.rec.work2[it];
+        const int face = job.rec.status[r] - kLandFace;
+        if (face < 0 || face > 5) continue;   // not landed by k_land
         const int dir = r >= job.rec.cap ? 1 : 0;
         const int64_t i = dir ? r - job.rec.cap : r;
         const S *__restrict__ nodes = static_cast<const S *>(job.nodes);
@@ -1730,7 +1733,6 @@ __global__ void __launch_bounds__(256) k_land_final(TraceJob job)
         const double sigma = dir ? -1.0 : 1.0;
         double y[9], s, best, yl[9];
         get_rec(job.rec, r, y, s, best);
-        const int face = job.rec.status[r] - kLandFace;
         if (best > 0.0) {
             ck54_fp64<S, MODE>(nodes, g, sigma, y, best, yl);
         } else {
@@ -1762,6 +1764,7 @@ __global__ void __launch_bounds__(256) k_land_euler(TraceJob job)
     for (int64_t it = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; it < total;
          it += (int64_t)gridDim.x * blockDim.x) {
         const int64_t r = job.rec.work2[it];
+        if (job.rec.status[r] != kPendingLand) continue;
         const int dir = r >= job.rec.cap ? 1 : 0;
         const int64_t i = dir ? r - job.rec.cap : r;
         const S *__restrict__ nodes = static_cast<const S *>(job.nodes);
@@ -1969,6 +1972,8 @@ __global__ void __launch_bounds__(256) k_assemble(TraceJob job)
     }
 }
 
+#include "finish.h"
+
 // ---------------------------------------------------------------------------
 // General geometry: stepping and landing in physical coordinates
 // ---------------------------------------------------------------------------
@@ -2092,6 +2097,15 @@ static int resident_blocks(const void *kern, int wg, size_t lds)
     return n;
 }
 
+// Largest call whose ends k_finish takes, one field and batched; a larger one
+// is landed by one lane per half-line over a compacted list and assembled in a
+// kernel of its own.  k_finish replaces eight launches, and its chain is a third
+// as long: 2000 seeds at 8 cells a step 260 -> 203 us, 200 000 592 -> 530 us;
+// over the 1.3 M seeds of a 1024^2 map, where FP64 issue is the bound and four
+// lanes cost more of it, it takes 0.84 ms against 0.53.  A batch reloads a
+// grid per seed in every kernel: 570 000 seeds 0.67 against 0.73 ms.
+constexpr int64_t kFinishMax = (int64_t)1 << 18, kFinishMaxBatch = (int64_t)1 << 20;
+
 // record bytes that 32-bit offsets reach, with room for the neighbours' offsets
 constexpr uint64_t kCacheLimit = ((uint64_t)1 << 31) - ((uint64_t)1 << 26);
 
@@ -2205,18 +2219,39 @@ static hipError_t launch_typed(const TraceJob &job, hipStream_t st)
         le = hipLaunchKernel(kern, dim3(blocks), dim3(wg), args, lds, st);
     if (prof) prof_end(tok, st);
     if (le != hipSuccess) return le;
+    if constexpr (interp_order<MODE>() == 1) {
+        if (n_max <= (BATCH ? kFinishMaxBatch : kFinishMax)) {
+            const int64_t fb = (4 * n_max + 255) / 256;
+            const int fblocks = (int)(fb < (int64_t)cus * 32 ? fb : (int64_t)cus * 32);
+            if (prof) prof_begin(kProfLand, st, &tok);
+            if (euler)
+                hipLaunchKernelGGL((k_finish<S, MODE, BATCH, true>), dim3(fblocks), dim3(256), 0, st, job);
+            else
+                hipLaunchKernelGGL((k_finish<S, MODE, BATCH, false>), dim3(fblocks), dim3(256), 0, st, job);
+            if (prof) prof_end(tok, st);
+            return hipGetLastError();
+        }
+    }
     int64_t lb = (2 * n_max + 255) / 256;
     int lblocks = (int)(lb < (int64_t)cus * 16 ? lb : (int64_t)cus * 16);
     if (prof) prof_begin(kProfLand, st, &tok);
-    // list of the half-lines to land, in record order
-    hipLaunchKernelGGL(k_land_flags, dim3(cblocks), dim3(256), 0, st, job);
-    launch_scan_i32(job.rec.flag, job.rec.n_items, 2 * n_max, job.rec.scan_tmp, job.rec.wpos, job.rec.n_land, st);
-    hipLaunchKernelGGL(k_land_compact, dim3(cblocks), dim3(256), 0, st, job);
-    if (euler) {
-        hipLaunchKernelGGL((k_land_euler<S, MODE, BATCH>), dim3(lblocks), dim3(256), 0, st, job);
+    TraceJob jl = job;
+    if (job.spatial_bits > 0) {
+        // list of the half-lines to land, in record order
+        hipLaunchKernelGGL(k_land_flags, dim3(cblocks), dim3(256), 0, st, job);
+        launch_scan_i32(job.rec.flag, job.rec.n_items, 2 * n_max, job.rec.scan_tmp, job.rec.wpos, job.rec.n_land, st);
+        hipLaunchKernelGGL(k_land_compact, dim3(cblocks), dim3(256), 0, st, job);
     } else {
-        hipLaunchKernelGGL((k_land<S, MODE, BATCH>), dim3(lblocks), dim3(256), 0, st, job);
-        hipLaunchKernelGGL((k_land_final<S, MODE, BATCH>), dim3(lblocks), dim3(256), 0, st, job);
+        // the unsorted work list is in record order already, and nearly all
+        // of its lines leave the box
+        jl.rec.work2 = job.rec.work;
+        jl.rec.n_land = job.rec.n_work;
+    }
+    if (euler) {
+        hipLaunchKernelGGL((k_land_euler<S, MODE, BATCH>), dim3(lblocks), dim3(256), 0, st, jl);
+    } else {
+        hipLaunchKernelGGL((k_land<S, MODE, BATCH>), dim3(lblocks), dim3(256), 0, st, jl);
+        hipLaunchKernelGGL((k_land_final<S, MODE, BATCH>), dim3(lblocks), dim3(256), 0, st, jl);
     }
     if (prof) prof_end(tok, st);
     int64_t ab = (n_max + 255) / 256;

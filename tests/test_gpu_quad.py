@@ -123,3 +123,32 @@ def test_general_geometry_list_lengths(n):
     part = q.trace(f, s[idx], **kw)
     torch.cuda.synchronize()
     assert _equal({k: v[..., idx] for k, v in full.items()}, part)
+
+
+@pytest.mark.parametrize("n,where", [(1, "box"), (15, "box"), (33, "bottom"), (5000, "mixed")])
+@pytest.mark.parametrize("stepper,mode", [("ck54", "paper"), ("ck54", "interp_normalize"), ("euler", "paper")])
+def test_small_calls_end_as_large_ones(charges, n, where, stepper, mode):
+    """Landing and Q of a small call (one kernel) against the same seeds inside
+    a call past 2^18 seeds (landing list, separate assembly): FP64 results of
+    different summation orders, so 1e-9 relative; whole numbers the same."""
+    import torch
+
+    import paper_1609_00724_amd as q
+    h = min(charges[2])
+    f = _field(charges, "f32", mode)
+    s = synth.random_seeds(n, n)
+    if where != "box":
+        s[:: 1 if where == "bottom" else 2, 2] = 0.0
+    s = torch.from_numpy(s).cuda()
+    pad = torch.tensor([[2.0, 0.0, 0.0]], dtype=torch.float64, device="cuda").expand((1 << 18) + 1, 3)   # outside: no work
+    kw = dict(rtol=1e-4, atol=1e-4, h_init=0.2 * h, h_max=2 * h, stepper=stepper, want_steps=True)
+    a = q.trace(f, s, **kw)
+    b = q.trace(f, torch.cat([s, pad]), **kw)
+    torch.cuda.synchronize()
+    for k, v in a.items():
+        w = b[k][..., :n]
+        if not v.is_floating_point():
+            assert torch.equal(v, w), k
+            continue
+        assert torch.equal(v.isnan(), w.isnan()), k
+        assert torch.allclose(v.nan_to_num(0.0), w.nan_to_num(0.0), rtol=1e-9, atol=1e-12), k
