@@ -138,20 +138,41 @@ __global__ void __launch_bounds__(256) k_brick_records(const R *__restrict__ nod
 // Direction records: for each cell (x fastest) the direction part (3 FP32
 // values) of its 8 corner records in the order a + 2b + 4c of corner
 // (i+a, j+b, k+c), 96 contiguous bytes, so that a cell's corners come in six
-// 16-byte loads from at most two 128-byte lines.  One thread per (cell, corner).
-__global__ void __launch_bounds__(256) k_cell_dirs(const float4 *__restrict__ nodes, int64_t nx, int64_t ny,
-                                                   int64_t ncells, float *__restrict__ dirs)
+// 16-byte loads from at most two 128-byte lines.  One workgroup per 256 cells
+// of a row: the four node rows go through LDS, and each thread writes 16
+// consecutive bytes at a time, past the caches (nothing here reads the records
+// back).  Bound by the writes: 256 x 256 x 128 nodes take 150 us (792 MB at
+// 5.3 TB/s, what a fill reaches); 12-byte cached stores took 240 us, and 282
+// with every thread finding its cell by 64-bit divisions.
+constexpr int kDirCells = 256;
+
+__global__ void __launch_bounds__(256) k_cell_dirs(const float4 *__restrict__ nodes, int nx, int ny, int chunks,
+                                                   int64_t units, float *__restrict__ dirs)
 {
-    const int64_t cx = nx - 1, cy = ny - 1;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < 8 * ncells;
-         e += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t c = e >> 3;
-        const int v = (int)(e & 7);
-        const int64_t i = c % cx, j = (c / cx) % cy, k = c / (cx * cy);
-        const float4 r = nodes[((k + (v >> 2)) * ny + j + ((v >> 1) & 1)) * nx + i + (v & 1)];
-        dirs[3 * e] = r.x;
-        dirs[3 * e + 1] = r.y;
-        dirs[3 * e + 2] = r.z;
+    __shared__ float4 stage[4][kDirCells + 1];
+    const int cx = nx - 1, cy = ny - 1;
+    for (int64_t u = blockIdx.x; u < units; u += gridDim.x) {
+        const int64_t row = u / chunks;
+        const int x0 = (int)(u % chunks) * kDirCells, nc = cx - x0 < kDirCells ? cx - x0 : kDirCells;
+        const int64_t j = row % cy, k = row / cy;
+        const float4 *base = nodes + (k * ny + j) * nx + x0;
+        for (int x = (int)threadIdx.x; x <= nc; x += 256)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) stage[r][x] = base[(int64_t)((r >> 1) * ny + (r & 1)) * nx + x];
+        __syncthreads();
+        typedef float f32x4 __attribute__((ext_vector_type(4)));
+        f32x4 *out = reinterpret_cast<f32x4 *>(dirs + (row * cx + x0) * 24);
+        for (int q = (int)threadIdx.x; q < 6 * nc; q += 256) {
+            const int c = q / 6, w = 4 * (q - 6 * c);   // floats w .. w + 3 of cell c
+            f32x4 o;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const int v = (w + t) / 3;
+                o[t] = reinterpret_cast<const float *>(&stage[v >> 1][c + (v & 1)])[w + t - 3 * v];
+            }
+            __builtin_nontemporal_store(o, out + q);
+        }
+        __syncthreads();
     }
 }
 
@@ -163,12 +184,11 @@ uint64_t cell_dir_bytes(const qsq_grid *g)
 hipError_t launch_cell_dirs(const qsq_field *f, void *ws, hipStream_t st)
 {
     const int64_t nx = f->grid.n[0], ny = f->grid.n[1];
-    const int64_t ncells = (nx - 1) * (ny - 1) * (f->grid.n[2] - 1);
-    const int cus = device_cu_count();
-    const int64_t want = (8 * ncells + 255) / 256;
-    const int blocks = (int)(want < (int64_t)cus * 32 ? want : (int64_t)cus * 32);
-    hipLaunchKernelGGL(k_cell_dirs, dim3(blocks), dim3(256), 0, st, static_cast<const float4 *>(f->nodes), nx, ny,
-                       ncells, static_cast<float *>(ws));
+    const int64_t chunks = (nx - 1 + kDirCells - 1) / kDirCells, units = chunks * (ny - 1) * (f->grid.n[2] - 1);
+    const int64_t cap = (int64_t)device_cu_count() * 64;
+    hipLaunchKernelGGL(k_cell_dirs, dim3((unsigned)(units < cap ? units : cap)), dim3(256), 0, st,
+                       static_cast<const float4 *>(f->nodes), (int)nx, (int)ny, (int)chunks, units,
+                       static_cast<float *>(ws));
     return hipGetLastError();
 }
 
