@@ -70,6 +70,49 @@ __device__ __forceinline__ double fin_lerp(const FinCell &c, const double t[3])
     return lerp_val<double>(c.v[0], c.v[1], c.v[2], c.v[3], c.v[4], c.v[5], c.v[6], c.v[7], t[0], t[1], t[2]);
 }
 
+// value and gradient of record component comp by a higher order's stencil (a
+// call: inlined at its twenty-odd places the cubic's 64 nodes outgrow the
+// instruction cache)
+struct FinStencil {
+    double val, dx, dy, dz;
+};
+template <typename S, int MODE>
+__device__ __attribute__((noinline)) double fin_stencil_value(const char *recs, int n, int nx, int ny, int c3, int comp,
+                                                              int ib, double q)
+{
+    constexpr uint32_t RB = 4 * value_bytes<S>();
+    int ci;
+    double t, val, dx, dy, dz;
+    cell_of(ib, q, n, ci, t);
+    const uint32_t sy = RB * (uint32_t)nx;
+    quad_stencil<double, S, interp_order<MODE>() + 1>(recs, n, sy, sy * (uint32_t)ny, c3, comp, ci, t, val, dx, dy, dz);
+    return val;
+}
+template <typename S, int MODE>
+__device__ __attribute__((noinline)) FinStencil fin_stencil_of(const char *recs, int n, int nx, int ny, int c3, int comp,
+                                                               int ib, double q)
+{
+    constexpr uint32_t RB = 4 * value_bytes<S>();
+    int ci;
+    double t;
+    cell_of(ib, q, n, ci, t);
+    const uint32_t sy = RB * (uint32_t)nx;
+    FinStencil r;
+    quad_stencil<double, S, interp_order<MODE>() + 1>(recs, n, sy, sy * (uint32_t)ny, c3, comp, ci, t, r.val, r.dx, r.dy,
+                                                      r.dz);
+    return r;
+}
+template <typename S, int MODE>
+__device__ __forceinline__ void fin_stencil(const char *recs, const FinAxis &a, int c3, int comp, int ib, double q,
+                                            double &val, double &dx, double &dy, double &dz)
+{
+    const FinStencil r = fin_stencil_of<S, MODE>(recs, a.n, a.nx, a.ny, c3, comp, ib, q);
+    val = r.val;
+    dx = r.dx;
+    dy = r.dy;
+    dz = r.dz;
+}
+
 // 1 / |v| over the quad's three components (0 for |v| <= 1e-300); bn = |v|
 __device__ __forceinline__ double fin_inverse(double val, double &bn)
 {
@@ -80,23 +123,33 @@ __device__ __forceinline__ double fin_inverse(double val, double &bn)
 
 // the lane's component of the direction u
 template <typename S, int MODE>
-__device__ __forceinline__ double fin_u(const char *comp, const FinAxis &a, int ib, double q, FinCell &cell)
+__device__ __forceinline__ double fin_u(const char *recs, const FinAxis &a, int c3, int ib, double q, FinCell &cell)
 {
-    double t[3], bn;
-    fin_corners<S>(comp, a, ib, q, t, cell);
-    const double val = fin_lerp(cell, t);
+    double bn, val;
+    if constexpr (interp_order<MODE>() > 1) {
+        val = fin_stencil_value<S, MODE>(recs, a.n, a.nx, a.ny, c3, c3 == 3 ? 2 : c3, ib, q);
+    } else {
+        double t[3];
+        fin_corners<S>(recs + (c3 == 3 ? 2 : c3) * value_bytes<S>(), a, ib, q, t, cell);
+        val = fin_lerp(cell, t);
+    }
     return normalize_first<MODE>() ? val : val * fin_inverse(val, bn);
 }
 
 // right-hand side for the lane's components: sigma (u, J d1, J d2)
 template <typename S, int MODE>
-__device__ __forceinline__ void fin_rhs(const char *comp, const FinAxis &a, int ib, double q, double sigma, double d1,
-                                        double d2, double k[3], FinCell &cell)
+__device__ __forceinline__ void fin_rhs(const char *recs, const FinAxis &a, int c3, int ib, double q, double sigma,
+                                        double d1, double d2, double k[3], FinCell &cell)
 {
-    double t[3], val, dx, dy, dz, G[3], u;
-    fin_corners<S>(comp, a, ib, q, t, cell);
-    lerp_tree<double>(cell.v[0], cell.v[1], cell.v[2], cell.v[3], cell.v[4], cell.v[5], cell.v[6], cell.v[7], t[0], t[1],
-                      t[2], val, dx, dy, dz);
+    double val, dx, dy, dz, G[3], u;
+    if constexpr (interp_order<MODE>() > 1) {
+        fin_stencil<S, MODE>(recs, a, c3, c3 == 3 ? 2 : c3, ib, q, val, dx, dy, dz);
+    } else {
+        double t[3];
+        fin_corners<S>(recs + (c3 == 3 ? 2 : c3) * value_bytes<S>(), a, ib, q, t, cell);
+        lerp_tree<double>(cell.v[0], cell.v[1], cell.v[2], cell.v[3], cell.v[4], cell.v[5], cell.v[6], cell.v[7], t[0],
+                          t[1], t[2], val, dx, dy, dz);
+    }
     const double Gb[3] = {dx * a.ihx, dy * a.ihy, dz * a.ihz};
     if (normalize_first<MODE>()) {
         u = val;
@@ -126,6 +179,14 @@ __device__ __forceinline__ void fin_ref(const FinAxis &a, double x, int &ib, dou
     fb = xg - fl;
 }
 
+// the same as field_at_x forms it (the product rounded before the subtraction)
+__device__ __forceinline__ void fin_point(const FinAxis &a, double x, int &ib, double &q)
+{
+    const double s = fmin(fmax((x - a.o) * a.ih, -1e9), 1e9), fl = floor(s);
+    ib = (int)fl;
+    q = s - fl;
+}
+
 #define QSQ_FIN_STAGES(STAGE)                                \
     STAGE(1, ck::a21)                                        \
     STAGE(2, ck::a31, ck::a32)                               \
@@ -136,7 +197,7 @@ __device__ __forceinline__ void fin_ref(const FinAxis &a, double x, int &ib, dou
 // the lane's position component at the end of a Cash-Karp step of length h
 // from x, whose first-stage slope is k0
 template <typename S, int MODE>
-__device__ __forceinline__ double fin_step_x(const char *comp, const FinAxis &a, int ib, double fb, double sigma, double x,
+__device__ __forceinline__ double fin_step_x(const char *recs, const FinAxis &a, int c3, int ib, double fb, double sigma, double x,
                                              double h, double k0, FinCell &cell)
 {
     double K[6];
@@ -146,11 +207,11 @@ __device__ __forceinline__ double fin_step_x(const char *comp, const FinAxis &a,
         const double c_[] = {__VA_ARGS__};                                                          \
         double ax = 0;                                                                              \
         _Pragma("unroll") for (int j = 0; j < ST; ++j) ax = fma(c_[j], K[j], ax);                   \
-        K[ST] = sigma * fin_u<S, MODE>(comp, a, ib, fma(h * ax, a.ih, fb), cell);                   \
+        K[ST] = sigma * fin_u<S, MODE>(recs, a, c3, ib, fma(h * ax, a.ih, fb), cell);               \
     }
     QSQ_FIN_STAGES(QSQ_FSTAGE)
 #undef QSQ_FSTAGE
-    return x + h * (ck::b1 * K[0] + ck::b3 * K[2] + ck::b4 * K[3] + ck::b6 * K[5]);
+    return fma(h, ck_b5(K[0], K[2], K[3], K[5]), x);
 }
 
 // signed distance beyond face f of the quad's point, from every lane's
@@ -168,14 +229,18 @@ __device__ __forceinline__ double fin_gap(double glo, double ghi, int f)
 // Regula falsi with the Anderson-Bjorck factor from a quadratic model's root.
 // Returns the length and the face; x, d1, d2 become the landed state.
 template <typename S, int MODE, bool EULER>
-__device__ __forceinline__ double fin_land(const char *comp, const FinAxis &a, int c, double gtol, double sigma, double hs,
+__device__ __forceinline__ double fin_land(const char *recs, const FinAxis &a, int c3, double gtol, double sigma, double hs,
                                            double &x, double &d1, double &d2, int &face, FinCell &cell)
 {
+    const int c = c3 == 3 ? 2 : c3;
     int ib;
     double fb;
-    fin_ref(a, x, ib, fb);
+    if (EULER)
+        fin_point(a, x, ib, fb);
+    else
+        fin_ref(a, x, ib, fb);
     double Kx[6], K1[6], K2[6], k[3];
-    fin_rhs<S, MODE>(comp, a, ib, fb, sigma, d1, d2, k, cell);
+    fin_rhs<S, MODE>(recs, a, c3, ib, fb, sigma, d1, d2, k, cell);
     Kx[0] = k[0];
     K1[0] = k[1];
     K2[0] = k[2];
@@ -183,7 +248,7 @@ __device__ __forceinline__ double fin_land(const char *comp, const FinAxis &a, i
     int fnear = 0;
     unsigned crossed = 0;
     face = -1;
-    const double xe = EULER ? x + hs * Kx[0] : fin_step_x<S, MODE>(comp, a, ib, fb, sigma, x, hs, Kx[0], cell);
+    const double xe = EULER ? fma(hs, Kx[0], x) : fin_step_x<S, MODE>(recs, a, c3, ib, fb, sigma, x, hs, Kx[0], cell);
     const double elo = a.lo - xe, ehi = xe - a.hi;
 #pragma unroll
     for (int f = 0; f < 6; ++f) {
@@ -216,9 +281,9 @@ __device__ __forceinline__ double fin_land(const char *comp, const FinAxis &a, i
                 int side = 0;
                 hf = -1.0;
                 for (int it = 0; it < 200; ++it) {
-                    const double h = it == 0 ? c0 : (lo * gb - hi * ga) / (gb - ga);
+                    const double h = it == 0 ? c0 : landing_secant(lo, ga, hi, gb);
                     double xh = x;
-                    if (h != 0.0) xh = fin_step_x<S, MODE>(comp, a, ib, fb, sigma, x, h, Kx[0], cell);
+                    if (h != 0.0) xh = fin_step_x<S, MODE>(recs, a, c3, ib, fb, sigma, x, h, Kx[0], cell);
                     const double gc = fin_gap(a.lo - xh, xh - a.hi, f);
                     if (fabs(gc) <= gtol) {
                         hf = h;
@@ -261,9 +326,9 @@ __device__ __forceinline__ double fin_land(const char *comp, const FinAxis &a, i
         best = hs;
     }
     if constexpr (EULER) {
-        x += best * Kx[0];
-        d1 += best * K1[0];
-        d2 += best * K2[0];
+        x = fma(best, Kx[0], x);
+        d1 = fma(best, K1[0], d1);
+        d2 = fma(best, K2[0], d2);
     } else if (best > 0.0) {
 #define QSQ_FSTAGE(ST, ...)                                                                                        \
     {                                                                                                              \
@@ -275,34 +340,40 @@ __device__ __forceinline__ double fin_land(const char *comp, const FinAxis &a, i
             a1 = fma(c_[j], K1[j], a1);                                                                            \
             a2 = fma(c_[j], K2[j], a2);                                                                            \
         }                                                                                                          \
-        fin_rhs<S, MODE>(comp, a, ib, fma(best * ax, a.ih, fb), sigma, fma(best, a1, d1), fma(best, a2, d2), k, cell); \
+        fin_rhs<S, MODE>(recs, a, c3, ib, fma(best * ax, a.ih, fb), sigma, fma(best, a1, d1), fma(best, a2, d2), k, \
+                         cell);                                                                                    \
         Kx[ST] = k[0];                                                                                             \
         K1[ST] = k[1];                                                                                             \
         K2[ST] = k[2];                                                                                             \
     }
         QSQ_FIN_STAGES(QSQ_FSTAGE)
 #undef QSQ_FSTAGE
-        x = x + best * (ck::b1 * Kx[0] + ck::b3 * Kx[2] + ck::b4 * Kx[3] + ck::b6 * Kx[5]);
-        d1 = d1 + best * (ck::b1 * K1[0] + ck::b3 * K1[2] + ck::b4 * K1[3] + ck::b6 * K1[5]);
-        d2 = d2 + best * (ck::b1 * K2[0] + ck::b3 * K2[2] + ck::b4 * K2[3] + ck::b6 * K2[5]);
+        x = fma(best, ck_b5(Kx[0], Kx[2], Kx[3], Kx[5]), x);
+        d1 = fma(best, ck_b5(K1[0], K1[2], K1[3], K1[5]), d1);
+        d2 = fma(best, ck_b5(K2[0], K2[2], K2[3], K2[5]), d2);
     }
     if (c == (face >> 1)) x = (face & 1) ? a.hi : a.lo;
     return best;
 }
 #undef QSQ_FIN_STAGES
 
-// u (not renormalised; the lane's component) and |B| at coordinate x; `rec`
-// points at the lane's component of the records, the fourth for lane 3
+// u (not renormalised; the lane's component) and |B| at coordinate x: the
+// fourth record component, which lane 3 takes (PAPER), or |interpolated B|
 template <typename S, int MODE>
-__device__ __forceinline__ double fin_value(const char *rec, const FinAxis &a, double x, double &mag)
+__device__ __forceinline__ double fin_value(const char *recs, const FinAxis &a, int c3, double x, double &mag)
 {
     int ib;
-    double fb, t[3];
-    fin_ref(a, x, ib, fb);
-    FinCell cell;
-    cell.key = -1;
-    fin_corners<S>(rec, a, ib, fb, t, cell);
-    const double val = fin_lerp(cell, t);
+    double fb, val;
+    fin_point(a, x, ib, fb);
+    if constexpr (interp_order<MODE>() > 1) {
+        val = fin_stencil_value<S, MODE>(recs, a.n, a.nx, a.ny, c3, c3, ib, fb);
+    } else {
+        FinCell cell;
+        double t[3];
+        cell.key = -1;
+        fin_corners<S>(recs + c3 * value_bytes<S>(), a, ib, fb, t, cell);
+        val = fin_lerp(cell, t);
+    }
     if (normalize_first<MODE>()) {
         mag = quad_get<3>(val);
         return val;
@@ -314,6 +385,7 @@ __device__ __forceinline__ double fin_value(const char *rec, const FinAxis &a, d
 // a0 b0 + a1 b1 + a2 b2 over the quad's components
 __device__ __forceinline__ double quad_dot(double a, double b)
 {
+#pragma clang fp contract(off)
     const double p = a * b;
     return quad_get<0>(p) + quad_get<1>(p) + quad_get<2>(p);
 }
@@ -330,6 +402,7 @@ __device__ __forceinline__ double quad_turn(double v, bool next)
 
 __device__ __forceinline__ double quad_cross_len(double a, double b)
 {
+#pragma clang fp contract(off)
     const double x = quad_turn(a, true) * quad_turn(b, false) - quad_turn(a, false) * quad_turn(b, true);
     return sqrt(quad_dot(x, x));
 }
@@ -345,6 +418,7 @@ __device__ __forceinline__ EndDots end_dots(double a, double b)
 }
 __device__ __forceinline__ double end_bracket(const EndDots &e, double &areas)
 {
+#pragma clang fp contract(off)
     const double aa = __shfl_xor(e.aa, 4), bb = __shfl_xor(e.bb, 4), ab = __shfl_xor(e.ab, 4);
     areas = e.area * __shfl_xor(e.area, 4);
     return e.aa * bb + aa * e.bb - 2.0 * ab * e.ab;
@@ -357,9 +431,8 @@ __device__ __forceinline__ double end_bracket(const EndDots &e, double &areas)
 // issue and by the latency of its gathers (about 24 evaluations of 8 corners
 // per landed half-line; a quad's lanes read one record together).
 template <typename S, int MODE, bool BATCH, bool EULER>
-__global__ void __launch_bounds__(256) k_finish(TraceJob job)
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(interp_order<MODE>() > 1 ? 2 : 1))) k_finish(TraceJob job)
 {
-    constexpr int VB = value_bytes<S>();
     const int64_t n = seed_count(job), P = 2 * job.rec.cap;
     const int lane = (int)(threadIdx.x & 63), c3 = lane & 3, c = c3 == 3 ? 2 : c3;
     FinAxis a = fin_axis(job.g, c);
@@ -388,7 +461,7 @@ __global__ void __launch_bounds__(256) k_finish(TraceJob job)
                 int face;
                 FinCell cell;
                 cell.key = -1;
-                const double cut = fin_land<S, MODE, EULER>(recs + c * VB, a, c, gtol, h >> 4 ? -1.0 : 1.0, job.rec.h[r], x,
+                const double cut = fin_land<S, MODE, EULER>(recs, a, c3, gtol, h >> 4 ? -1.0 : 1.0, job.rec.h[r], x,
                                                             d1, d2, face, cell);
                 if (c3 < 3) {
                     job.rec.y[c * P + r] = x;
@@ -456,12 +529,11 @@ __global__ void __launch_bounds__(256) k_finish(TraceJob job)
             const bool skip = (job.o.flags & QSQ_FLAG_SKIP_OPEN) && open;
             if (defF && defB && !skip) {
                 double mag, mag0;
-                const char *rec = recs + c3 * VB;
-                const double v = fin_value<S, MODE>(rec, a, x, mag);
-                fin_value<S, MODE>(rec, a, seeds[c * ss + li], mag0);
+                const double v = fin_value<S, MODE>(recs, a, c3, x, mag);
+                fin_value<S, MODE>(recs, a, c3, seeds[c * ss + li], mag0);
                 const double u = v / sqrt(quad_dot(v, v));
                 // perpendicular parts of the deviations (Sect. 3.5)
-                const EndDots ep = end_dots(d1 - u * quad_dot(u, d1), d2 - u * quad_dot(u, d2));
+                const EndDots ep = end_dots(less_along(d1, u, quad_dot(u, d1)), less_along(d2, u, quad_dot(u, d2)));
                 double areas;
                 const double br = end_bracket(ep, areas);
                 qp = mag * __shfl_xor(mag, 4) / (mag0 * mag0) * br;   // eq. (11)
@@ -474,7 +546,7 @@ __global__ void __launch_bounds__(256) k_finish(TraceJob job)
                         return d == 0 ? w0 : d == 1 ? w1 : w2;
                     };
                     const double vd = pick(v), r1 = pick(d1) / vd, r2 = pick(d2) / vd;
-                    const EndDots ef = end_dots(d1 - v * r1, d2 - v * r2);
+                    const EndDots ef = end_dots(less_along(d1, v, r1), less_along(d2, v, r2));
                     const double bf = end_bracket(ef, areas);
                     qf = bf / areas;
                 }

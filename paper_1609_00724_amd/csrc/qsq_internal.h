@@ -125,6 +125,7 @@ struct TraceJob {
     // line (0: none)
     int64_t quad_max;
     int simds;          // SIMDs of the device
+    bool quad_ok;       // the field's records are addressable by the four-lane kernels
 };
 
 // kernels the profiler can time

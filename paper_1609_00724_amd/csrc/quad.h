@@ -1,6 +1,7 @@
 // Stepping with four lanes per half-line (a quad of adjacent lanes): lane c of
 // the quad holds component c of the position and of both deviation vectors and
-// evaluates component c of the field (lane 3 repeats lane 2), and the values
+// evaluates component c of the field (lane 3 repeats lane 2, or idles along on
+// values that nothing reads), and the values
 // that every component needs (cell fractions, deviations) cross the quad by
 // DPP moves.  An attempt is a serial chain of six evaluations; a lane that does
 // a third of the components issues about a third of the instructions (640
@@ -86,40 +87,139 @@ __device__ __forceinline__ QuadRef<T> quad_ref(const QuadGeom<T> &g, int ib)
     return {ib, __mul24(ib, g.ka), (T)-ib, (T)(g.n - 2 - ib)};
 }
 
+// Values (the lane's component) of the K records of one stencil row, K = 3 or
+// 4.  FP32 records: lane l of the quad loads record l whole (16 bytes; the
+// quad's loads fall in one or two cache lines, one access instead of K), and a
+// 4 x 4 transpose across the quad hands every lane its component of all four.
+// Other types: the lane's component of each record.  off: byte offset of the
+// row; ox: of the quad lane's record in it; oc: of the lane's component of
+// records 0 .. K - 1.
+template <typename T, typename S, int K>
+__device__ __forceinline__ void quad_row(const char *recs, uint32_t off, uint32_t ox, const uint32_t oc[K], int c3, T v[K])
+{
+    if constexpr (std::is_same<S, float>::value) {
+        const float4 r = *reinterpret_cast<const float4 *>(recs + (off + ox));
+        float a0 = r.x, a1 = r.y, a2 = r.z, a3 = r.w;
+        const bool odd = c3 & 1, high = c3 & 2;
+        // swap across lanes 1 apart, then 2 apart
+        const auto x1 = [](float w) { return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(w), 0xb1, 0xf, 0xf, true)); };
+        const auto x2 = [](float w) { return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(w), 0x4e, 0xf, 0xf, true)); };
+        const float s0 = x1(a0), s1 = x1(a1), s2 = x1(a2), s3 = x1(a3);
+        a0 = odd ? s1 : a0;
+        a1 = odd ? a1 : s0;
+        a2 = odd ? s3 : a2;
+        a3 = odd ? a3 : s2;
+        const float t0 = x2(a0), t1 = x2(a1), t2 = x2(a2), t3 = x2(a3);
+        const float o[4] = {high ? t2 : a0, high ? t3 : a1, high ? a2 : t0, high ? a3 : t1};
+#pragma unroll
+        for (int k = 0; k < K; ++k) v[k] = (T)o[k];
+    } else {
+#pragma unroll
+        for (int k = 0; k < K; ++k) v[k] = quad_load<T, S>(recs + (off + oc[k]));
+    }
+}
+
+// Value and grid-unit gradient of record component comp (lane 3 of the FP32
+// transpose: the fourth) by the separable stencil sum of order K - 1 at cell ci, fraction t of the lane's axis: along x per
+// row, then y, then z, in stencil_sum's order.  Each lane forms its own axis'
+// weights and the quad shares them.
+template <typename T, typename S, int K>
+__device__ __forceinline__ void quad_stencil(const char *recs, int n, uint32_t sy, uint32_t sz, int c3, int comp, int ci,
+                                             T t, T &val, T &dx, T &dy, T &dz)
+{
+    constexpr uint32_t VB = value_bytes<S>(), RB = 4 * VB;
+    const int c = c3 == 3 ? 2 : c3;
+    int s0;
+    T w[K], dw[K];
+    axis_stencil<K, T>(ci, t, n, s0, w, dw);
+    // byte offsets of the lane's axis' stencil nodes (the last may lie past
+    // the grid, with weight zero)
+    const uint32_t st = c == 0 ? RB : c == 1 ? sy : sz;
+    uint32_t off[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) off[k] = (uint32_t)(s0 + k < n - 1 ? s0 + k : n - 1) * st;
+    uint32_t oc[K], oy[K], oz[K], ox = 0;
+    T wx[K], wy[K], wz[K], dwx[K], dwy[K], dwz[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const uint32_t o = (uint32_t)quad_get<0>((int)off[k]);
+        oc[k] = o + VB * (uint32_t)comp;
+        if (k == c3 || (k == K - 1 && c3 > k)) ox = o;
+        oy[k] = (uint32_t)quad_get<1>((int)off[k]);
+        oz[k] = (uint32_t)quad_get<2>((int)off[k]);
+        wx[k] = quad_get<0>(w[k]);
+        wy[k] = quad_get<1>(w[k]);
+        wz[k] = quad_get<2>(w[k]);
+        dwx[k] = quad_get<0>(dw[k]);
+        dwy[k] = quad_get<1>(dw[k]);
+        dwz[k] = quad_get<2>(dw[k]);
+    }
+    val = dx = dy = dz = (T)0;
+#pragma unroll
+    for (int kz = 0; kz < K; ++kz) {
+        T v[K][K], ay = 0, axy = 0, ayy = 0;
+#pragma unroll
+        for (int ky = 0; ky < K; ++ky) quad_row<T, S, K>(recs, oz[kz] + oy[ky], ox, oc, c3, v[ky]);
+#pragma unroll
+        for (int ky = 0; ky < K; ++ky) {
+            T rx = 0, drx = 0;
+#pragma unroll
+            for (int kx = 0; kx < K; ++kx) {
+                rx = fma(wx[kx], v[ky][kx], rx);
+                drx = fma(dwx[kx], v[ky][kx], drx);
+            }
+            ay = fma(wy[ky], rx, ay);
+            axy = fma(wy[ky], drx, axy);
+            ayy = fma(dwy[ky], rx, ayy);
+        }
+        val = fma(wz[kz], ay, val);
+        dx = fma(wz[kz], axy, dx);
+        dy = fma(wz[kz], ayy, dy);
+        dz = fma(dwz[kz], ay, dz);
+        // one z plane's rows in flight, not all of the stencil's
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
 // One evaluation at grid-unit reference r plus offset q (the lane's axis) for
 // deviations d1, d2 (the lane's components); returns |u|^2 if NORM2.  `recs`
-// points at the records, `c` is the lane's component.  Record keys and byte
+// points at the records, `c3` is the lane's place in its quad.  Record keys and byte
 // offsets fit 32 bits and the axis products 24 bits (the launcher checks).
 template <typename T, typename S, int MODE, bool FIRST, bool NORM2>
-__device__ __forceinline__ T quad_rhs(const char *recs, const QuadGeom<T> &g, int c, const QuadRef<T> &r, T q, T d1,
+__device__ __forceinline__ T quad_rhs(const char *recs, const QuadGeom<T> &g, int c3, const QuadRef<T> &r, T q, T d1,
                                       T d2, T &kx, T &k1, T &k2, QuadCell<T> &cell)
 {
+    const int c = c3 == 3 ? 2 : c3;
     constexpr uint32_t VB = value_bytes<S>(), RB = 4 * VB;
     // cell and fraction as cell_of gives them
     const T fl = clamp_floor(q, r.flo, r.fhi), t = q - fl;
-    // the record key of the cell, summed over the axes (lane 3 adds nothing)
     const int ifl = (int)fl;
-    int key = __mul24(ifl, g.ka) + r.key0;
-    key += __builtin_amdgcn_mov_dpp(key, 0xb1, 0xf, 0xf, true);   // lanes 1 0 3 2
-    key += __builtin_amdgcn_mov_dpp(key, 0x4e, 0xf, 0xf, true);   // lanes 2 3 0 1
-    if (key != cell.key) {
-        cell.key = key;
-        const uint32_t o0 = (uint32_t)key * RB + VB * (uint32_t)c, o1 = o0 + g.sy, o2 = o0 + g.sz, o3 = o1 + g.sz;
-        cell.v[0] = quad_load<T, S>(recs + o0);
-        cell.v[1] = quad_load<T, S>(recs + o0 + RB);
-        cell.v[2] = quad_load<T, S>(recs + o1);
-        cell.v[3] = quad_load<T, S>(recs + o1 + RB);
-        cell.v[4] = quad_load<T, S>(recs + o2);
-        cell.v[5] = quad_load<T, S>(recs + o2 + RB);
-        cell.v[6] = quad_load<T, S>(recs + o3);
-        cell.v[7] = quad_load<T, S>(recs + o3 + RB);
+    T val, dx, dy, dz;
+    if constexpr (interp_order<MODE>() > 1) {
+        quad_stencil<T, S, interp_order<MODE>() + 1>(recs, g.n, g.sy, g.sz, c3, c, r.ib + ifl, t, val, dx,
+                                                        dy, dz);
+    } else {
+        // the record key of the cell, summed over the axes (lane 3 adds nothing)
+        int key = __mul24(ifl, g.ka) + r.key0;
+        key += __builtin_amdgcn_mov_dpp(key, 0xb1, 0xf, 0xf, true);   // lanes 1 0 3 2
+        key += __builtin_amdgcn_mov_dpp(key, 0x4e, 0xf, 0xf, true);   // lanes 2 3 0 1
+        if (key != cell.key) {
+            cell.key = key;
+            const uint32_t o0 = (uint32_t)key * RB + VB * (uint32_t)c, o1 = o0 + g.sy, o2 = o0 + g.sz, o3 = o1 + g.sz;
+            cell.v[0] = quad_load<T, S>(recs + o0);
+            cell.v[1] = quad_load<T, S>(recs + o0 + RB);
+            cell.v[2] = quad_load<T, S>(recs + o1);
+            cell.v[3] = quad_load<T, S>(recs + o1 + RB);
+            cell.v[4] = quad_load<T, S>(recs + o2);
+            cell.v[5] = quad_load<T, S>(recs + o2 + RB);
+            cell.v[6] = quad_load<T, S>(recs + o3);
+            cell.v[7] = quad_load<T, S>(recs + o3 + RB);
+        }
+        lerp_tree<T>(cell.v[0], cell.v[1], cell.v[2], cell.v[3], cell.v[4], cell.v[5], cell.v[6], cell.v[7],
+                     quad_get<0>(t), quad_get<1>(t), quad_get<2>(t), val, dx, dy, dz);
     }
-    const T t0 = quad_get<0>(t), t1 = quad_get<1>(t), t2 = quad_get<2>(t);
     const T a0 = quad_get<0>(d1), a1 = quad_get<1>(d1), a2 = quad_get<2>(d1);
     const T b0 = quad_get<0>(d2), b1 = quad_get<1>(d2), b2 = quad_get<2>(d2);
-    T val, dx, dy, dz;
-    lerp_tree<T>(cell.v[0], cell.v[1], cell.v[2], cell.v[3], cell.v[4], cell.v[5], cell.v[6], cell.v[7], t0, t1, t2,
-                 val, dx, dy, dz);
     T u, G[3], n2 = 0;
     if (normalize_first<MODE>()) {
         u = val;
@@ -195,7 +295,6 @@ __device__ __forceinline__ void quad_attempt(const char *recs, const QuadGeom<T>
 {
     int stop = -1;
     if (st.attempts >= o.max_steps) stop = QSQ_END_MAX_STEPS;
-    const int c = c3 == 3 ? 2 : c3;
     QuadRef<T> ref{};
     T fb = 0;
     if (stop < 0) {
@@ -204,7 +303,7 @@ __device__ __forceinline__ void quad_attempt(const char *recs, const QuadGeom<T>
         ref = quad_ref<T>(g, (int)fl);
         fb = (T)(xg - fl);
         if (EULER || !st.have_k1) {
-            const T un2 = quad_rhs<T, S, MODE, FIRST, true>(recs, g, c, ref, fb, st.D1, st.D2, st.Kx0, st.K10,
+            const T un2 = quad_rhs<T, S, MODE, FIRST, true>(recs, g, c3, ref, fb, st.D1, st.D2, st.Kx0, st.K10,
                                                              st.K20, cell);
             ++cnt.ev;
             if (un2 < (T)1e-12) stop = QSQ_END_NULL;   // NaN: not a null (the step reports it)
@@ -242,7 +341,7 @@ __device__ __forceinline__ void quad_attempt(const char *recs, const QuadGeom<T>
             a1 = fma(c_[j], K1[j], a1);                                                                            \
             a2 = fma(c_[j], K2[j], a2);                                                                            \
         }                                                                                                          \
-        quad_rhs<T, S, MODE, FIRST, false>(recs, g, c, ref, fma(hsig * ax, g.iha, fb), fma(hsig, a1, st.D1),        \
+        quad_rhs<T, S, MODE, FIRST, false>(recs, g, c3, ref, fma(hsig * ax, g.iha, fb), fma(hsig, a1, st.D1),        \
                                             fma(hsig, a2, st.D2), Kx[ST], K1[ST], K2[ST], cell);                   \
     }
             QSQ_QSTAGE(1, (T)ck::a21)
@@ -274,7 +373,7 @@ __device__ __forceinline__ void quad_attempt(const char *recs, const QuadGeom<T>
         fsum += quad_get<1>(fpart);
         fsum += quad_get<2>(fpart);
         ++st.attempts;
-        const bool out = quad_any(!(Xn >= g.lo && Xn <= g.hi));
+        const bool out = quad_any(c3 < 3 && !(Xn >= g.lo && Xn <= g.hi));
         if (!isfinite(fsum)) {
             stop = QSQ_END_NONFINITE;
         } else if (!EULER && err > (T)1) {
@@ -400,7 +499,8 @@ __device__ __forceinline__ void quad_count(unsigned long long *work, const QuadC
 template <typename T, typename S, int MODE, bool BATCH, bool EULER>
 __global__ void __launch_bounds__(kQuadWg) k_trace_quad(TraceJob job)
 {
-    constexpr bool FIRST = !BATCH && std::is_same<T, float>::value && std::is_same<S, float>::value;
+    constexpr bool FIRST =
+        !BATCH && std::is_same<T, float>::value && std::is_same<S, float>::value && interp_order<MODE>() == 1;
     const StepOpts &o = job.o;
     const int c3 = (int)(threadIdx.x & 3), c = c3 == 3 ? 2 : c3;
     const int64_t total = *job.rec.n_work;

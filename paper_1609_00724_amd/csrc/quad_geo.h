@@ -296,7 +296,7 @@ template <typename S, int MODE>
 __device__ __forceinline__ double geo_step_x(const S *nodes, const GeoAxis &a, int c, double sigma, double x, double h,
                                              double k0, GeoCell<S> &cell)
 {
-    typedef double T;
+    typedef double T;   // of the stage table
     double K[6];
     K[0] = k0;
     auto slope = [&](double xs) {
@@ -324,7 +324,7 @@ __device__ __forceinline__ double geo_step_x(const S *nodes, const GeoAxis &a, i
     }
     QSQ_GEO_STAGES(QSQ_GLSTAGE)
 #undef QSQ_GLSTAGE
-    return x + h * (ck::b1 * K[0] + ck::b3 * K[2] + ck::b4 * K[3] + ck::b6 * K[5]);
+    return fma(h, ck_b5(K[0], K[2], K[3], K[5]), x);
 }
 
 // For every face the trial step crosses, Illinois regula falsi from the secant
@@ -334,7 +334,7 @@ __device__ __forceinline__ double geo_step_x(const S *nodes, const GeoAxis &a, i
 template <typename S, int MODE>
 __global__ void __launch_bounds__(kQuadWg) k_land_geo(TraceJob job)
 {
-    typedef double T;
+    typedef double T;   // of the stage table
     const int c3 = (int)(threadIdx.x & 3), c = c3 == 3 ? 2 : c3;
     const int64_t total = *job.rec.n_land, P = 2 * job.rec.cap;
     const S *nodes = static_cast<const S *>(job.nodes) + c;
@@ -386,7 +386,7 @@ __global__ void __launch_bounds__(kQuadWg) k_land_geo(TraceJob job)
                 int side = 0;
                 root = -1.0;
                 for (int k = 0; k < 200 && root < 0.0; ++k) {
-                    const double h = (lo * gb - hi * ga) / (gb - ga);
+                    const double h = landing_secant(lo, ga, hi, gb);
                     const double gc = gap_at(h, f);
                     if (fabs(gc) <= gtol) {
                         root = h;
@@ -433,9 +433,9 @@ __global__ void __launch_bounds__(kQuadWg) k_land_geo(TraceJob job)
     }
             QSQ_GEO_STAGES(QSQ_GFSTAGE)
 #undef QSQ_GFSTAGE
-            xl = x + best * (ck::b1 * Kx[0] + ck::b3 * Kx[2] + ck::b4 * Kx[3] + ck::b6 * Kx[5]);
-            l1 = d1 + best * (ck::b1 * K1[0] + ck::b3 * K1[2] + ck::b4 * K1[3] + ck::b6 * K1[5]);
-            l2 = d2 + best * (ck::b1 * K2[0] + ck::b3 * K2[2] + ck::b4 * K2[3] + ck::b6 * K2[5]);
+            xl = fma(best, ck_b5(Kx[0], Kx[2], Kx[3], Kx[5]), x);
+            l1 = fma(best, ck_b5(K1[0], K1[2], K1[3], K1[5]), d1);
+            l2 = fma(best, ck_b5(K2[0], K2[2], K2[3], K2[5]), d2);
         }
         if (c == (face >> 1)) xl = (face & 1) ? a.hi : a.lo;
         if (c3 < 3) {

@@ -272,7 +272,7 @@ __device__ __forceinline__ void field_finish(const double ih[3], const T val[4],
         if (MAG) mag = val[3];
     } else {
         // u = B/|B|, grad u = (I - u u^T) grad B / |B|
-        const T bb = val[0] * val[0] + val[1] * val[1] + val[2] * val[2];
+        const T bb = fma(val[2], val[2], fma(val[0], val[0], val[1] * val[1]));
         const T bn = sqrt(bb);
         const T inv = bn > (T)1e-300 ? (T)1 / bn : (T)0;
         T Gb[3][3];
@@ -385,7 +385,7 @@ __device__ __forceinline__ void field_u(const S *__restrict__ nodes, const Geom 
 #pragma unroll
         for (int i = 0; i < 3; ++i) u[i] = val[i];
     } else {
-        const T bb = val[0] * val[0] + val[1] * val[1] + val[2] * val[2];
+        const T bb = fma(val[2], val[2], fma(val[0], val[0], val[1] * val[1]));
         const T bn = sqrt(bb);
         const T inv = bn > (T)1e-300 ? (T)1 / bn : (T)0;
 #pragma unroll
@@ -1504,7 +1504,7 @@ __device__ void ck54_fp64(const S *__restrict__ nodes, const Geom &g, double sig
     }
 #pragma unroll
     for (int i = 0; i < 9; ++i)
-        yo[i] = y[i] + hs * (ck::b1 * K[0][i] + ck::b3 * K[2][i] + ck::b4 * K[3][i] + ck::b6 * K[5][i]);
+        yo[i] = fma(hs, ck_b5(K[0][i], K[2][i], K[3][i], K[5][i]), y[i]);
 }
 
 // The position part of one FP64 Cash-Karp step (eq. (1) alone: the position
@@ -1554,7 +1554,7 @@ __device__ void ck54_pos(const S *__restrict__ nodes, const Geom &g, double sigm
     }
 #pragma unroll
     for (int i = 0; i < 3; ++i)
-        yo[i] = y[i] + hs * (ck::b1 * K[0][i] + ck::b3 * K[2][i] + ck::b4 * K[3][i] + ck::b6 * K[5][i]);
+        yo[i] = fma(hs, ck_b5(K[0][i], K[2][i], K[3][i], K[5][i]), y[i]);
     if (slope0) {
         // dx/dlambda at the start of the step (the first stage)
 #pragma unroll
@@ -1567,12 +1567,23 @@ __device__ void ck54_pos(const S *__restrict__ nodes, const Geom &g, double sigm
 // secant point if that root is not strictly inside.
 __device__ __forceinline__ double landing_guess(double g0, double s0, double g1, double hs)
 {
+#pragma clang fp contract(off)
     const double sec = -g0 * hs / (g1 - g0);
     const double cq = (g1 - g0 - s0 * hs) / (hs * hs);
     const double disc = s0 * s0 - 4.0 * cq * g0;
     const double den = s0 + sqrt(fmax(disc, 0.0));
     const double h = den > 0.0 ? -2.0 * g0 / den : -1.0;
     return (h > 0.0 && h < hs) ? h : sec;
+}
+
+// next trial length of the regula falsi between (a, ga < 0) and (b, gb > 0).
+// (Here and in the Q assembly products and sums round one by one: the
+// one-lane and the four-lane kernels of the same step then give the same bits,
+// however the compiler would have fused each of them.)
+__device__ __forceinline__ double landing_secant(double a, double ga, double b, double gb)
+{
+#pragma clang fp contract(off)
+    return (a * gb - b * ga) / (gb - ga);
 }
 
 // v[d] for a run-time d in 0..2 as selects (a dynamic index would put the
@@ -1665,7 +1676,7 @@ __global__ void __launch_bounds__(256) k_land(TraceJob job)
                 const double s0 = (f & 1) ? pick3(v0, dd) : -pick3(v0, dd);
                 const double c0 = landing_guess(ga, s0, gb, hs);
                 for (int k = 0; k < 200; ++k) {
-                    const double c = k == 0 ? c0 : (a * gb - b * ga) / (gb - ga);
+                    const double c = k == 0 ? c0 : landing_secant(a, ga, b, gb);
                     const double gc = face_gap<S, MODE>(nodes, g, sigma, y, c, f, yo, v0);
                     if (fabs(gc) <= gtol) {
                         hf = c;
@@ -1784,8 +1795,8 @@ __global__ void __launch_bounds__(256) k_land_euler(TraceJob job)
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
             dy[k] = sigma * u[k];
-            dy[3 + k] = sigma * (G[0][k] * y[3] + G[1][k] * y[4] + G[2][k] * y[5]);
-            dy[6 + k] = sigma * (G[0][k] * y[6] + G[1][k] * y[7] + G[2][k] * y[8]);
+            dy[3 + k] = sigma * jdot(G[0][k], G[1][k], G[2][k], y[3], y[4], y[5]);
+            dy[6 + k] = sigma * jdot(G[0][k], G[1][k], G[2][k], y[6], y[7], y[8]);
         }
         double best = INFINITY;
         int face = -1;
@@ -1793,7 +1804,7 @@ __global__ void __launch_bounds__(256) k_land_euler(TraceJob job)
             const int d = f >> 1;
             const double wall = (f & 1) ? pick3(g.hi, d) : pick3(g.lo, d);
             const double yd = pick3(y, d), vd = pick3(dy, d);
-            const double end = yd + hs * vd;
+            const double end = fma(hs, vd, yd);
             const double gap = (f & 1) ? end - wall : wall - end;
             if (!(gap > 0.0)) continue;
             double hf = (wall - yd) / vd;
@@ -1811,7 +1822,7 @@ __global__ void __launch_bounds__(256) k_land_euler(TraceJob job)
             double gmax = -INFINITY;
             for (int f = 0; f < 6; ++f) {
                 const int d = f >> 1;
-                const double end = pick3(y, d) + hs * pick3(dy, d);
+                const double end = fma(hs, pick3(dy, d), pick3(y, d));
                 const double gap = (f & 1) ? end - pick3(g.hi, d) : pick3(g.lo, d) - end;
                 if (gap > gmax) {
                     gmax = gap;
@@ -1820,7 +1831,7 @@ __global__ void __launch_bounds__(256) k_land_euler(TraceJob job)
             }
         }
 #pragma unroll
-        for (int k = 0; k < 9; ++k) yl[k] = y[k] + best * dy[k];
+        for (int k = 0; k < 9; ++k) yl[k] = fma(best, dy[k], y[k]);
         const int d = face >> 1;
         const double snap = (face & 1) ? pick3(g.hi, d) : pick3(g.lo, d);
 #pragma unroll
@@ -1835,21 +1846,31 @@ __global__ void __launch_bounds__(256) k_land_euler(TraceJob job)
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ double dot3(const double *a, const double *b)
 {
+#pragma clang fp contract(off)
     return a[0] * b[0] + a[1] * b[1] + a[2] * b[2];
 }
 
 __device__ __forceinline__ double cross_len(const double *a, const double *b)
 {
+#pragma clang fp contract(off)
     const double c0 = a[1] * b[2] - a[2] * b[1];
     const double c1 = a[2] * b[0] - a[0] * b[2];
     const double c2 = a[0] * b[1] - a[1] * b[0];
     return sqrt(c0 * c0 + c1 * c1 + c2 * c2);
 }
 
+// a - u s
+__device__ __forceinline__ double less_along(double a, double u, double s)
+{
+#pragma clang fp contract(off)
+    return a - u * s;
+}
+
 // a_F^2 b_B^2 + a_B^2 b_F^2 - 2 (a_B . b_B)(a_F . b_F)
 __device__ __forceinline__ double q_bracket(const double *aF, const double *bF, const double *aB,
                                             const double *bB)
 {
+#pragma clang fp contract(off)
     return dot3(aF, aF) * dot3(bB, bB) + dot3(aB, aB) * dot3(bF, bF) - 2.0 * dot3(aB, bB) * dot3(aF, bF);
 }
 
@@ -1943,10 +1964,10 @@ __global__ void __launch_bounds__(256) k_assemble(TraceJob job)
             const double pa = dot3(uF, yF + 3), pb = dot3(uF, yF + 6);
             const double qa = dot3(uB, yB + 3), qb = dot3(uB, yB + 6);
             for (int k = 0; k < 3; ++k) {
-                aF[k] = yF[3 + k] - uF[k] * pa;
-                bF[k] = yF[6 + k] - uF[k] * pb;
-                aB[k] = yB[3 + k] - uB[k] * qa;
-                bB[k] = yB[6 + k] - uB[k] * qb;
+                aF[k] = less_along(yF[3 + k], uF[k], pa);
+                bF[k] = less_along(yF[6 + k], uF[k], pb);
+                aB[k] = less_along(yB[3 + k], uB[k], qa);
+                bB[k] = less_along(yB[6 + k], uB[k], qb);
             }
             const double br = q_bracket(aF, bF, aB, bB);
             qp = BF * BB / (B0 * B0) * br;                                  // eq. (11)
@@ -1958,10 +1979,10 @@ __global__ void __launch_bounds__(256) k_assemble(TraceJob job)
                 const double rB1 = yB[3 + dB] / vB[dB], rB2 = yB[6 + dB] / vB[dB];
                 double pF1[3], pF2[3], pB1[3], pB2[3];
                 for (int k = 0; k < 3; ++k) {
-                    pF1[k] = yF[3 + k] - vF[k] * rF1;
-                    pF2[k] = yF[6 + k] - vF[k] * rF2;
-                    pB1[k] = yB[3 + k] - vB[k] * rB1;
-                    pB2[k] = yB[6 + k] - vB[k] * rB2;
+                    pF1[k] = less_along(yF[3 + k], vF[k], rF1);
+                    pF2[k] = less_along(yF[6 + k], vF[k], rF2);
+                    pB1[k] = less_along(yB[3 + k], vB[k], rB1);
+                    pB2[k] = less_along(yB[6 + k], vB[k], rB2);
                 }
                 qf = q_bracket(pF1, pF2, pB1, pB2) / (cross_len(pF1, pF2) * cross_len(pB1, pB2));
             }
@@ -2198,7 +2219,7 @@ static hipError_t launch_typed(const TraceJob &job, hipStream_t st)
     // the one whose call it is not returns at once.
     const void *quad = nullptr;
     int qblocks = 0;
-    if constexpr (interp_order<MODE>() == 1) {
+    {
         if (job.quad_max > 0) {
             quad = euler ? reinterpret_cast<const void *>(&k_trace_quad<T, S, MODE, BATCH, true>)
                          : reinterpret_cast<const void *>(&k_trace_quad<T, S, MODE, BATCH, false>);
@@ -2219,8 +2240,10 @@ static hipError_t launch_typed(const TraceJob &job, hipStream_t st)
         le = hipLaunchKernel(kern, dim3(blocks), dim3(wg), args, lds, st);
     if (prof) prof_end(tok, st);
     if (le != hipSuccess) return le;
-    if constexpr (interp_order<MODE>() == 1) {
-        if (n_max <= (BATCH ? kFinishMaxBatch : kFinishMax)) {
+    {
+        // (the higher orders' stencils take 32-bit byte offsets; the launch
+        // word has no say, so that it never changes a result)
+        if ((interp_order<MODE>() == 1 || job.quad_ok) && n_max <= (BATCH ? kFinishMaxBatch : kFinishMax)) {
             const int64_t fb = (4 * n_max + 255) / 256;
             const int fblocks = (int)(fb < (int64_t)cus * 32 ? fb : (int64_t)cus * 32);
             if (prof) prof_begin(kProfLand, st, &tok);
@@ -2365,6 +2388,15 @@ static hipError_t dispatch(const TraceJob &job, int step_dtype, hipStream_t st)
     return paper ? launch_typed<double, double, P, BATCH>(job, st) : launch_typed<double, double, N, BATCH>(job, st);
 }
 
+// four-lane kernels: records addressed with 32-bit byte offsets, their keys
+// formed by 24-bit products
+static bool quad_addressable(const Geom &g, int storage)
+{
+    const uint64_t rec = storage == QSQ_F64 ? 32 : storage == QSQ_F32 ? 16 : 8;
+    const uint64_t xy = (uint64_t)g.n[0] * (uint64_t)g.n[1];
+    return xy < ((uint64_t)1 << 23) && (uint64_t)g.n[2] < ((uint64_t)1 << 23) && xy * (uint64_t)g.n[2] * rec < kCacheLimit;
+}
+
 // Largest work list that the four-lane kernel takes under an automatic gather
 // (0: none; a named gather always gets the one-lane kernel).  A list that fits
 // the grid lasts as long as its longest line, and four lanes a line shorten
@@ -2378,14 +2410,13 @@ static hipError_t dispatch(const TraceJob &job, int step_dtype, hipStream_t st)
 // to 2^16.  FP64 stepping keeps half as many waves resident and a batch
 // reloads its grid with every line: up to 2^17 (FP64, 128^2 x 64 cells at 1
 // cell: 128 000 half-lines 1.53 against 1.74 ms, 256 000 2.45 against 2.34).
-static int64_t quad_limit(const Geom &g, double h_max, int storage, bool f32, bool batch)
+static int64_t quad_limit(const Geom &g, double h_max, int storage, bool f32, bool batch, int order)
 {
-    // records are addressed with 32-bit byte offsets, keys formed by 24-bit products
-    const uint64_t rec = storage == QSQ_F64 ? 32 : storage == QSQ_F32 ? 16 : 8;
-    const uint64_t xy = (uint64_t)g.n[0] * (uint64_t)g.n[1];
-    if (xy >= ((uint64_t)1 << 23) || (uint64_t)g.n[2] >= ((uint64_t)1 << 23) ||
-        xy * (uint64_t)g.n[2] * rec >= kCacheLimit)
-        return 0;
+    if (!quad_addressable(g, storage)) return 0;
+    // 27 and 64 records a stencil: loading a row of them across the quad beats
+    // one lane's loads at any length (cubic, 4 cells a step: 4000 half-lines
+    // 1.5 against 2.5 ms, 10^6 13.8 against 15.3; FP64 stepping 1.7 to 2.7 times)
+    if (order > 1) return (int64_t)1 << 30;
     const double edge = fmax(fmax(g.hi[0] - g.lo[0], g.hi[1] - g.lo[1]), g.hi[2] - g.lo[2]);
     if (!(edge >= 32.0 * h_max)) return (int64_t)1 << 16;
     return (int64_t)1 << (f32 && !batch ? 19 : 17);
@@ -2401,9 +2432,11 @@ hipError_t launch_trace(const TraceJob &job, int step_dtype, hipStream_t st)
 {
     TraceJob j = job;
     j.simds = 4 * device_cu_count();
+    j.quad_ok = quad_addressable(job.g, job.storage);
     j.quad_max = 0;
-    if (((job.o.launch >> 6) & 7) == 0 && job.mode <= 1)
-        j.quad_max = quad_limit(job.g, step_cap(job.o, job.o.h_init, job.o.h_max), job.storage, step_dtype == QSQ_F32, false);
+    if (((job.o.launch >> 6) & 7) == 0 && job.mode < 8)
+        j.quad_max = quad_limit(job.g, step_cap(job.o, job.o.h_init, job.o.h_max), job.storage, step_dtype == QSQ_F32, false,
+                                ((job.mode >> 1) & 3) + 1);
     return dispatch<false>(j, step_dtype, st);
 }
 
@@ -2440,7 +2473,7 @@ hipError_t launch_trace_batch(const TraceJob &job, const SetDesc *host_sets, int
         j.quad_max = (int64_t)1 << 30;
         for (int k = 0; k < nsets; ++k) {
             const SetDesc &d = host_sets[k];
-            const int64_t q = quad_limit(d.g, step_cap(job.o, d.h_init, d.h_max), job.storage, step_dtype == QSQ_F32, true);
+            const int64_t q = quad_limit(d.g, step_cap(job.o, d.h_init, d.h_max), job.storage, step_dtype == QSQ_F32, true, 1);
             if (q < j.quad_max) j.quad_max = q;
         }
     }

@@ -129,8 +129,7 @@ def test_general_geometry_list_lengths(n):
 @pytest.mark.parametrize("stepper,mode", [("ck54", "paper"), ("ck54", "interp_normalize"), ("euler", "paper")])
 def test_small_calls_end_as_large_ones(charges, n, where, stepper, mode):
     """Landing and Q of a small call (one kernel) against the same seeds inside
-    a call past 2^18 seeds (landing list, separate assembly): FP64 results of
-    different summation orders, so 1e-9 relative; whole numbers the same."""
+    a call past 2^18 seeds (landing list, separate assembly), bit for bit."""
     import torch
 
     import paper_1609_00724_amd as q
@@ -145,12 +144,26 @@ def test_small_calls_end_as_large_ones(charges, n, where, stepper, mode):
     a = q.trace(f, s, **kw)
     b = q.trace(f, torch.cat([s, pad]), **kw)
     torch.cuda.synchronize()
-    for k, v in a.items():
-        if k == "q_fp":
-            continue
-        w = b[k][..., :n]
-        if not v.is_floating_point():
-            assert torch.equal(v, w), k
-            continue
-        assert torch.equal(v.isnan(), w.isnan()), k
-        assert torch.allclose(v.nan_to_num(0.0), w.nan_to_num(0.0), rtol=1e-9, atol=1e-12), k
+    assert _equal({k: v[..., :n] for k, v in b.items()}, a)
+
+
+@pytest.mark.parametrize("order", ["quadratic", "cubic"])
+@pytest.mark.parametrize("storage,step,mode,stepper", [
+    ("f32", "f32", "paper", "ck54"), ("f64", "f64", "paper", "ck54"), ("f32", "f64", "interp_normalize", "ck54"),
+    ("f64", "f32", "interp_normalize", "euler")])
+def test_higher_orders(charges, order, storage, step, mode, stepper):
+    """Quad stencils (folded ones at every face: 4 nodes along z) against one lane's."""
+    import torch
+
+    import paper_1609_00724_amd as q
+    from paper_1609_00724_amd import _abi as A
+    b, origin, spacing = charges
+    dt = np.float64 if storage == "f64" else np.float32
+    b = [torch.from_numpy(np.ascontiguousarray(c[:4].astype(dt))).cuda() for c in b]
+    f = q.field_init(*b, origin, spacing, storage=storage, mode=mode, order=order)
+    h = min(spacing)
+    hi = 0.2 * h if stepper == "euler" else 0.1 * h
+    r = _runs(f, 1100, (0, A.launch_word(2, 64, A.GATHER_DIRECT)), rtol=1e-4, atol=1e-4, h_init=hi, h_max=2 * h,
+              step_dtype=step, stepper=stepper)
+    assert ((r[0]["status"] & 0xFF) <= 5).sum() > 50
+    assert _equal(*r)
