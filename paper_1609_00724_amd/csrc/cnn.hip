@@ -161,11 +161,8 @@ __global__ void k_prepare(const float *params, uint16_t *prep)
 // window of three rows sliding down the strip.  Inputs with CI < 32 channels
 // (FP32 with 3, BF16 with 2) are staged the same way, as BF16 with cpad(CI)
 // channels per pixel, and the 9 taps' channels packed along K (cpad(CI) per
-// tap) are read from there.  Outputs (each
-// nullable): BF16 activations (ReLU applied), FP32 values, a BF16 copy masked
-// by mask_cm > 0 (input gradients; mask_cm is the channel-major copy of the
-// layer's input activations), and the channel-major copy of the BF16 output
-// (masked too when mask_cm is given).  A BF16 NHWC output of 32 channels goes
+// tap) are read from there.  Outputs (each nullable): BF16 activations (ReLU
+// applied) and FP32 values.  A BF16 NHWC output of 32 channels goes
 // through LDS so that each lane stores one pixel's 8 channels (16 bytes) and
 // the wave a row's 1 KB with one store.  One tile's tensors are addressed
 // with 32-bit byte offsets (h w <= 2^24).
@@ -196,13 +193,6 @@ __device__ __forceinline__ uint32_t pack_bf2(float a, float b)
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
 }
 
-// BF16 pair with each half kept where the matching half of m (BF16) is > 0
-__device__ __forceinline__ uint32_t mask_bf2(uint32_t v, uint32_t m)
-{
-    const bool lo = __uint_as_float(m << 16) > 0.0f, hi = __uint_as_float(m & 0xffff0000u) > 0.0f;
-    return (lo ? v & 0xffffu : 0u) | (hi ? v & 0xffff0000u : 0u);
-}
-
 struct Row3 {
     bf16x8 m, z, p;   // the lane's pixel shifted by -1, 0, +1
 };
@@ -210,9 +200,7 @@ struct Row3 {
 template <int CI, int CO, bool SRC_F32>
 __global__ void __launch_bounds__(256) k_conv(const void *__restrict__ in, ConvDims d,
                                               const uint16_t *__restrict__ wm, const float *__restrict__ bias,
-                                              bool relu, uint16_t *__restrict__ out_bf, float *__restrict__ out_f32,
-                                              uint16_t *__restrict__ out_masked,
-                                              const uint16_t *__restrict__ mask_cm, uint16_t *__restrict__ out_cm)
+                                              bool relu, uint16_t *__restrict__ out_bf, float *__restrict__ out_f32)
 {
     constexpr int NT = ntile(CO), COP = 16 * NT, NK = nchunk(CI), R = kConvRows;
     static_assert(CI >= 32 ? !SRC_F32 : (CI == 3) == SRC_F32, "FP32 input has 3 channels, BF16 input 2 or 32");
@@ -299,12 +287,6 @@ __global__ void __launch_bounds__(256) k_conv(const void *__restrict__ in, ConvD
     float bv[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) bv[t] = bias && t * 16 + i < CO ? bias[t * 16 + i] : 0.0f;
-    // the tile's channel-major tensors (mask, output copy): CO channels per row
-    const int cm_bytes = (int)(npix * CO * 2);
-    const __amdgpu_buffer_rsrc_t mask_rs = buf_rsrc(mask_cm ? mask_cm + img * npix * CO : nullptr, cm_bytes);
-    const __amdgpu_buffer_rsrc_t cm_rs = buf_rsrc(out_cm ? out_cm + img * npix * CO : nullptr, cm_bytes);
-    // byte offset of (row y, channel 16 t + i, pixel x0 + 4 kg) in them
-    auto cm_off = [&](int y, int t) { return ((y * CO + t * 16 + i) * d.w + x0 + 4 * kg) * 2; };
     // BF16 NHWC output of 32 channels through the wave's LDS stage
     __shared__ uint16_t stage_all[4][16 * 32];
     uint16_t *stage = stage_all[threadIdx.x >> 6];
@@ -352,13 +334,6 @@ __global__ void __launch_bounds__(256) k_conv(const void *__restrict__ in, ConvD
 #pragma unroll
     for (int rr = 0; rr < R; ++rr) {
         const int y = y0 + rr;
-        // mask of this row's pixels 4 kg .. 4 kg + 3, fetched before the
-        // products so that its latency overlaps them
-        u32x2 mk[NT];
-        if (mask_cm) {
-#pragma unroll
-            for (int t = 0; t < NT; ++t) mk[t] = __builtin_amdgcn_raw_buffer_load_b64(mask_rs, cm_off(y, t), 0, 0);
-        }
         f32x4 acc[NT];
 #pragma unroll
         for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -420,19 +395,6 @@ __global__ void __launch_bounds__(256) k_conv(const void *__restrict__ in, ConvD
             }
         }
         if (out_bf) store_nhwc(out_bf, y, hp);
-        if (mask_cm) {
-#pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                hp[t][0] = mask_bf2(hp[t][0], mk[t].x);
-                hp[t][1] = mask_bf2(hp[t][1], mk[t].y);
-            }
-            if (out_masked) store_nhwc(out_masked, y, hp);
-        }
-        if (out_cm) {
-#pragma unroll
-            for (int t = 0; t < NT; ++t)
-                if (t * 16 + i < CO) __builtin_amdgcn_raw_buffer_store_b64(u32x2{hp[t][0], hp[t][1]}, cm_rs, cm_off(y, t), 0, 0);
-        }
     }
 }
 
@@ -440,9 +402,9 @@ __global__ void __launch_bounds__(256) k_conv(const void *__restrict__ in, ConvD
 // Channel-major row copies.  The weight gradient contracts over pixels, and a
 // matrix-core operand takes 8 consecutive K values per lane, so its operands
 // are read from copies of the activations and gradients laid out per image
-// row as [channel][x] (BF16): cm[((img h + y) C + c) w + x].  The producing
-// kernels (convolutions, loss) write them beside their NHWC outputs; k_to_cm
-// makes them from NHWC data (the network input, the per-layer check calls).
+// row as [channel][x] (BF16): cm[((img h + y) C + c) w + x], made by k_to_cm from
+// NHWC data.  (The per-layer check calls take this way; a training step's
+// backward pass is k_bwd below.)
 // ---------------------------------------------------------------------------
 template <int C, bool SRC_F32>
 __global__ void k_to_cm(const void *in, int64_t rows, int w, uint16_t *out)
@@ -620,6 +582,395 @@ __global__ void __launch_bounds__(256) k_wgrad(const uint16_t *__restrict__ xcm,
     }
 }
 
+// ---------------------------------------------------------------------------
+// Backward pass of a layer with 32 input channels, in one kernel: the input
+// gradient dx = conv(dy, transposed flipped weights), masked where the layer's
+// input activation is 0 (ReLU), and the weight and bias gradients
+//   dW[tap][ci][co] = sum over pixels of x[p + tap - (1,1)][ci] dy[p][co],
+// both from the same rows of dy and x in LDS (BF16 NHWC, as the convolutions
+// write them).  A workgroup of 4 waves takes R rows of a 64-pixel column chunk
+// of one image, two rows at a time through a ring of four staged rows per
+// tensor (pixels xc - 1 .. xc + 64, zeros outside the image); the next two
+// rows are loaded into registers while the present ones are used.  (Four at a
+// time leaves more in flight but not the registers for it: 16 .. 160 bytes of
+// scratch a lane, 55 / 62 / 126 us where two take 32 / 52 / 70.)
+//   dx: wave s takes the 16-pixel strip xc + 16 s and all 32 channels, as k_conv.
+//   dW: M = 16 input channels, N = 16 output channels, K = 32 pixels; wave
+//     (a, b) takes that pair of channel tiles over the whole chunk (CO = 2: a
+//     and the half of the chunk).  K runs along pixels, which NHWC rows hold 64
+//     bytes apart: the operands come by transposing LDS reads (each 16-lane
+//     group reads 4 pixels of 16 channels and gets 4 pixels of its lane's
+//     channel); three reads give 12 pixels, and so the operands of the three
+//     taps of a row.
+// The mask comes from the staged activations by the same reads.  FIRST (layer
+// 1): dx, wanted by layer 0's weight gradient alone, stays in LDS, where
+// dW0[tap][ci][co] = sum of x0[p + tap - (1,1)][ci] dx[p][co] is formed too
+// (M = 27 (tap, ci) pairs in two tiles).  Sums go to the workgroup's slots.
+// Bound by HBM: dy and x read once, dx written once.  256 tiles of 64 x 64, as
+// an input gradient and a weight gradient apart (which also needed channel-major
+// copies of x and dy from the kernels before them) and here: CO = 2 (138 MB)
+// 42 + 25 and 32 us (4.3 TB/s), 32 channels (201 MB) 52 + 47 and 52 us (3.9
+// TB/s), FIRST (147 MB) 52 + 47 + layer 0's 24 and 70 us (2.1 TB/s: the chain
+// through LDS with two waves per SIMD, 218 registers).
+// ---------------------------------------------------------------------------
+#ifndef QSQ_BWD_STEP
+#define QSQ_BWD_STEP 2
+#endif
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+
+// 4 pixels of the lane's channel from LDS (see above): p points at the 8 bytes
+// of pixel lane % 16 / 4, channels 4 (lane % 4) .. + 3 of the lane's group
+__device__ __forceinline__ s16x4 lds_tr(const uint16_t *p)
+{
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)p);
+}
+
+__device__ __forceinline__ bf16x8 join8(s16x4 a, s16x4 b)
+{
+    typedef short s16x8 __attribute__((ext_vector_type(8)));
+    const s16x8 v = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+    return __builtin_bit_cast(bf16x8, v);
+}
+
+constexpr int kBwdStep = 2, kRing = kBwdStep + 2, kBwdPx = 66, kBwdRow = 68;   // staged pixels; a row's room
+
+template <int CO, bool FIRST>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k_bwd(const uint16_t *__restrict__ dy, const uint16_t *__restrict__ x,
+                                             const float *__restrict__ x0, ConvDims d, int R,
+                                             const uint16_t *__restrict__ wm, uint16_t *__restrict__ dx,
+                                             float *__restrict__ part, float *__restrict__ part0)
+{
+    static_assert(CO == 32 || !FIRST, "layer 0's weight gradient goes with a 32-channel layer");
+    constexpr int NK = nchunk(CO);
+    constexpr int SLOT = 9 * 32 * CO + CO, SLOT0 = 9 * 3 * 32 + 32;
+    constexpr int XCH = kBwdPx * 4, XRO = kBwdRow * 4;   // 16-byte chunks of a staged 32-channel row; of its room
+    constexpr int SPX = 72;                         // dwords of a staged 2-channel row (pixel xc + p at p + 4)
+    constexpr int YB = CO == 32 ? kRing * XRO * 16 : kRing * SPX * 4;
+    constexpr int GB = FIRST ? kBwdStep * 64 * 64 : 4 * 16 * 64;   // dx rows, or the waves' store stages
+    constexpr int X0W = 36;                         // dwords of a staged channel of x0 (pixel p at element p + 2)
+    constexpr int X0B = FIRST ? 2 * kRing * 3 * X0W * 4 : 0;
+    __shared__ __align__(16) unsigned char lds[kRing * XRO * 16 + YB + GB + X0B];
+    uint4 *lx = reinterpret_cast<uint4 *>(lds);
+    unsigned char *lyb = lds + kRing * XRO * 16;
+    uint16_t *lg = reinterpret_cast<uint16_t *>(lds + kRing * XRO * 16 + YB);
+    uint32_t *l0 = reinterpret_cast<uint32_t *>(lds + kRing * XRO * 16 + YB + GB);   // [copy][row][ci][X0W]
+    const int tid = (int)threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int i = lane & 15, kg = lane >> 4;
+    const int cpr = (d.w + 63) / 64, rb = d.h / R;
+    const int64_t unit = blockIdx.x;
+    const int xc = (int)(unit % cpr) * 64, y0 = (int)((unit / cpr) % rb) * R;
+    const int64_t img = unit / ((int64_t)cpr * rb), npix = (int64_t)d.h * d.w;
+    const __amdgpu_buffer_rsrc_t xrs = buf_rsrc(x + img * npix * 32, (int)(npix * 64));
+    const __amdgpu_buffer_rsrc_t yrs = buf_rsrc(dy + img * npix * CO, (int)(npix * CO * 2));
+    const __amdgpu_buffer_rsrc_t grs = buf_rsrc(dx ? dx + img * npix * 32 : nullptr, (int)(npix * 64));
+    const __amdgpu_buffer_rsrc_t zrs = buf_rsrc(FIRST ? x0 + img * npix * 3 : nullptr, (int)(npix * 12));
+
+    // --- staging: rows r .. r + n - 1 (0 = image row y0 - 1) of both tensors
+    // (rows above and below the image lie outside the buffers and read zeros,
+    // and so do the pixels left and right of it)
+    auto xoff = [&](int r, int c) {
+        const int px = xc - 1 + (c >> 2), yy = y0 - 1 + r;
+        return px >= 0 && px < d.w && yy >= 0 && yy < d.h ? ((yy * d.w + px) * 32 + 8 * (c & 3)) * 2 : (int)(npix * 64);
+    };
+    auto soff = [&](int r, int p) {
+        const int px = xc - 1 + p, yy = y0 - 1 + r;
+        return px >= 0 && px < d.w && yy >= 0 && yy < d.h ? (yy * d.w + px) * 4 : (int)(npix * 4);
+    };
+    auto slot_of = [](int r) { return r % kRing; };
+    constexpr int PER = (kBwdStep * XCH + 255) / 256, PERS = (kBwdStep * kBwdPx + 255) / 256;
+    u32x4 tx[PER], ty[CO == 32 ? PER : 1];
+    uint32_t ts[PERS], tz[FIRST ? PERS : 1][2];
+    auto fetch = [&](int r0, int rows) {
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const int e = tid + 256 * k, r = e / XCH, c = e % XCH;
+            const int off = r < rows ? xoff(r0 + r, c) : (int)(npix * 64);
+            tx[k] = __builtin_amdgcn_raw_buffer_load_b128(xrs, off, 0, 0);
+            if constexpr (CO == 32) ty[k] = __builtin_amdgcn_raw_buffer_load_b128(yrs, off, 0, 0);
+        }
+        if constexpr (CO == 2) {
+#pragma unroll
+            for (int k = 0; k < PERS; ++k) {
+                const int e = tid + 256 * k, r = e / kBwdPx;
+                ts[k] = __builtin_amdgcn_raw_buffer_load_b32(yrs, r < rows ? soff(r0 + r, e % kBwdPx) : (int)(npix * 4), 0, 0);
+            }
+        }
+        if constexpr (FIRST) {
+#pragma unroll
+            for (int k = 0; k < PERS; ++k) {
+                const int e = tid + 256 * k, r = e / kBwdPx;
+                const int off = r < rows ? 3 * soff(r0 + r, e % kBwdPx) : (int)(npix * 12);
+                const float a = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(zrs, off, 0, 0));
+                const float b = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(zrs, off, 4, 0));
+                const float c = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(zrs, off, 8, 0));
+                tz[k][0] = (uint32_t)f2bf(a) | ((uint32_t)f2bf(b) << 16);
+                tz[k][1] = f2bf(c);
+            }
+        }
+    };
+    auto put = [&](int r0, int rows) {
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const int e = tid + 256 * k, r = e / XCH, c = e % XCH;
+            if (r < rows) {
+                const int q = slot_of(r0 + r) * XRO + c;
+                lx[q] = __builtin_bit_cast(uint4, tx[k]);
+                if constexpr (CO == 32) reinterpret_cast<uint4 *>(lyb)[q] = __builtin_bit_cast(uint4, ty[k]);
+            }
+        }
+        if constexpr (CO == 2 || FIRST) {
+#pragma unroll
+            for (int k = 0; k < PERS; ++k) {
+                const int e = tid + 256 * k, r = e / kBwdPx, p = e % kBwdPx;   // pixel xc - 1 + p
+                if (r >= rows) continue;
+                if constexpr (CO == 2) reinterpret_cast<uint32_t *>(lyb)[slot_of(r0 + r) * SPX + p + 3] = ts[k];
+                if constexpr (FIRST) {
+                    // two copies of each channel, one element apart, so that a
+                    // pair of pixels at any shift is an aligned dword
+                    uint16_t *z = reinterpret_cast<uint16_t *>(l0) + slot_of(r0 + r) * 3 * 2 * X0W;
+                    uint16_t *z1 = z + kRing * 3 * 2 * X0W;
+                    const uint16_t v[3] = {(uint16_t)tz[k][0], (uint16_t)(tz[k][0] >> 16), (uint16_t)tz[k][1]};
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) {
+                        z[c * 2 * X0W + p + 1] = v[c];    // pixel xc + p' at element p' + 2
+                        z1[c * 2 * X0W + p] = v[c];       // and at p' + 1
+                    }
+                }
+            }
+        }
+    };
+
+    // the input gradient's weights (as k_conv's: N = 16 t + i, K = 32 kc + 8 kg)
+    bf16x8 bw[NK][2];
+#pragma unroll
+    for (int kc = 0; kc < NK; ++kc)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) bw[kc][t] = ld_bf16x8(wm + ((int64_t)(kc * 32 + t * 16 + i) * 32 + 8 * kg));
+    const int a = CO == 32 ? wv >> 1 : wv & 1, b = CO == 32 ? wv & 1 : 0;
+    const int hfirst = CO == 32 ? 0 : wv >> 1, hlast = CO == 32 ? 2 : hfirst + 1;   // the wave's halves of the chunk
+    f32x4 acc[9], acc0 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < 9; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float dbs = 0.0f, dbs0 = 0.0f;
+    const int x0s = xc + 16 * wv;   // the wave's strip
+    // element offset of a transposing read: pixel 8 kg + i / 4, channel 4 (i % 4) of a row
+    const int tro = (8 * kg + (i >> 2)) * 32 + 4 * (i & 3);
+
+    fetch(0, 2);
+    put(0, 2);
+    fetch(2, kBwdStep);
+    for (int g = 0; g < R; g += kBwdStep) {
+        put(g + 2, kBwdStep);
+        __syncthreads();
+        if (g + kBwdStep < R) fetch(g + 2 + kBwdStep, kBwdStep);
+        int ro[kRing];   // ring slots of rows g .. g + 3
+#pragma unroll
+        for (int k = 0; k < kRing; ++k) ro[k] = slot_of(g + k);
+        // --- input gradient
+        if (x0s < d.w) {
+            Row3 win[3];
+            auto lds3 = [&](int k) {
+                const uint4 *p = reinterpret_cast<const uint4 *>(lyb) + (ro[k] * kBwdRow + 16 * wv + i) * 4 + kg;
+                Row3 o;
+                o.m = __builtin_bit_cast(bf16x8, p[0]);
+                o.z = __builtin_bit_cast(bf16x8, p[4]);
+                o.p = __builtin_bit_cast(bf16x8, p[8]);
+                return o;
+            };
+            if constexpr (CO == 32) {
+                win[0] = lds3(0);
+                win[1] = lds3(1);
+            }
+#pragma unroll
+            for (int rr = 0; rr < kBwdStep; ++rr) {
+                f32x4 o[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+                if constexpr (CO == 32) {
+                    win[2] = lds3(rr + 2);
+#pragma unroll
+                    for (int tyy = 0; tyy < 3; ++tyy)
+#pragma unroll
+                        for (int t = 0; t < 2; ++t) {
+                            o[t] = mfma(win[tyy].m, bw[3 * tyy + 0][t], o[t]);
+                            o[t] = mfma(win[tyy].z, bw[3 * tyy + 1][t], o[t]);
+                            o[t] = mfma(win[tyy].p, bw[3 * tyy + 2][t], o[t]);
+                        }
+                    win[0] = win[1];
+                    win[1] = win[2];
+                } else {
+                    constexpr int TPL = 4;   // taps a lane group packs (2 channels each)
+#pragma unroll
+                    for (int kc = 0; kc < NK; ++kc) {
+                        uint32_t wd[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+                        for (int tt = 0; tt < TPL; ++tt) {
+                            const int tap = (32 * kc + 8 * kg) / 2 + tt;
+                            if (tap < 9)
+                                wd[tt] = reinterpret_cast<const uint32_t *>(lyb)[slot_of(g + rr + tap / 3) * SPX + 16 * wv + i +
+                                                                                 tap % 3 + 3];
+                        }
+                        const bf16x8 op = __builtin_bit_cast(bf16x8, make_uint4(wd[0], wd[1], wd[2], wd[3]));
+#pragma unroll
+                        for (int t = 0; t < 2; ++t) o[t] = mfma(op, bw[kc][t], o[t]);
+                    }
+                }
+                // lane: pixels 4 kg + r of the strip, channel 16 t + i; its
+                // mask by a transposing read of the staged activations
+                const uint16_t *xm = reinterpret_cast<const uint16_t *>(lx) +
+                                     (ro[rr + 1] * kBwdRow + 16 * wv + 1 + 4 * kg + (i >> 2)) * 32 + 4 * (i & 3);
+                uint16_t *stage = FIRST ? lg + (rr * 64 + 16 * wv) * 32 : lg + wv * 16 * 32;
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    const s16x4 mk = lds_tr(xm + 16 * t);
+                    const uint32_t p0 = pack_bf2(o[t][0], o[t][1]), p1 = pack_bf2(o[t][2], o[t][3]);
+                    const uint32_t h[4] = {p0 & 0xffffu, p0 >> 16, p1 & 0xffffu, p1 >> 16};
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        stage[(4 * kg + r) * 32 + 16 * t + i] = bf2f((uint16_t)mk[r]) > 0.0f ? (uint16_t)h[r] : (uint16_t)0;
+                }
+                if constexpr (!FIRST) {
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                    const u32x4 q = reinterpret_cast<const u32x4 *>(stage)[lane];
+                    __builtin_amdgcn_raw_buffer_store_b128(q, grs, (((y0 + g + rr) * d.w + x0s) * 32 + 8 * lane) * 2, 0, 0);
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                }
+            }
+        } else if constexpr (FIRST) {
+            // pixels past the image add nothing to layer 0's sums
+#pragma unroll
+            for (int rr = 0; rr < kBwdStep; ++rr)
+                reinterpret_cast<uint4 *>(lg + (rr * 64 + 16 * wv) * 32)[lane] = make_uint4(0u, 0u, 0u, 0u);
+        }
+        // --- weight gradient: x rows g .. g + 3 against dy rows g + 1, g + 2
+        bf16x8 gb[kBwdStep][2];
+#pragma unroll
+        for (int k = 0; k < kBwdStep; ++k)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                if (h < hfirst || h >= hlast) continue;
+                if constexpr (CO == 32) {
+                    const uint16_t *p = reinterpret_cast<const uint16_t *>(lyb) + (ro[k + 1] * kBwdRow + 1 + 32 * h) * 32 + 16 * b + tro;
+                    gb[k][h] = join8(lds_tr(p), lds_tr(p + 4 * 32));
+                } else {
+                    // 8 pixels of channel i < 2 from the dword rows
+                    const uint32_t *p = reinterpret_cast<const uint32_t *>(lyb) + ro[k + 1] * SPX + 4 + 32 * h + 8 * kg;
+                    const uint4 u = reinterpret_cast<const uint4 *>(p)[0], v = reinterpret_cast<const uint4 *>(p)[1];
+                    const uint32_t w[8] = {u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w};
+                    uint32_t o[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        o[e] = i == 0 ? (w[2 * e] & 0xffffu) | (w[2 * e + 1] << 16)
+                                      : i == 1 ? (w[2 * e] >> 16) | (w[2 * e + 1] & 0xffff0000u) : 0u;
+                    gb[k][h] = __builtin_bit_cast(bf16x8, make_uint4(o[0], o[1], o[2], o[3]));
+                }
+                if (a == 0) {
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) dbs += (float)gb[k][h][j];
+                }
+            }
+#pragma unroll
+        for (int k = 0; k < kRing; ++k)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                if (h < hfirst || h >= hlast) continue;
+                const uint16_t *p = reinterpret_cast<const uint16_t *>(lx) + (ro[k] * kBwdRow + 32 * h) * 32 + 16 * a + tro;
+                // staged pixels 0 .. 11 from the lane's first; the operands
+                // shifted by 0, 1, 2 are dwords 0 .. 3, their odd pairs, 1 .. 4
+                const u32x2 q0 = __builtin_bit_cast(u32x2, lds_tr(p)), q1 = __builtin_bit_cast(u32x2, lds_tr(p + 4 * 32)),
+                            q2 = __builtin_bit_cast(u32x2, lds_tr(p + 8 * 32));
+                const uint32_t w[5] = {q0.x, q0.y, q1.x, q1.y, q2.x};
+                const bf16x8 xs[3] = {
+                    __builtin_bit_cast(bf16x8, make_uint4(w[0], w[1], w[2], w[3])),
+                    __builtin_bit_cast(bf16x8, make_uint4(__builtin_amdgcn_alignbyte(w[1], w[0], 2),
+                                                          __builtin_amdgcn_alignbyte(w[2], w[1], 2),
+                                                          __builtin_amdgcn_alignbyte(w[3], w[2], 2),
+                                                          __builtin_amdgcn_alignbyte(w[4], w[3], 2))),
+                    __builtin_bit_cast(bf16x8, make_uint4(w[1], w[2], w[3], w[4]))};
+#pragma unroll
+                for (int tyy = 0; tyy < 3; ++tyy) {
+                    const int q = k - tyy;   // dy row g + 1 + q
+                    if (q < 0 || q >= kBwdStep) continue;
+#pragma unroll
+                    for (int t = 0; t < 3; ++t) acc[3 * tyy + t] = mfma(xs[t], gb[q][h], acc[3 * tyy + t]);
+                }
+            }
+        if constexpr (FIRST) {
+            // --- layer 0: (tap, ci) pairs 16 a .. + 15 against dx channels 16 b .. + 15
+            __syncthreads();
+            const int m = 16 * a + i, tap = m / 3, ci = m % 3;
+#pragma unroll
+            for (int rr = 0; rr < kBwdStep; ++rr)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const uint16_t *p = lg + (rr * 64 + 32 * h) * 32 + 16 * b + tro;
+                    const bf16x8 gd = join8(lds_tr(p), lds_tr(p + 4 * 32));
+                    // pixels 32 h + 8 kg + tap % 3 - 1 .. + 7: element + 2 of the first copy, + 1 of the second
+                    uint32_t w[4] = {0u, 0u, 0u, 0u};
+                    if (m < 27) {
+                        const int e = 32 * h + 8 * kg + tap % 3 - 1;
+                        const uint32_t *z = l0 + ((tap % 3 == 1 ? 0 : kRing) + slot_of(g + rr + tap / 3)) * 3 * X0W + ci * X0W;
+                        const int q = (tap % 3 == 1 ? e + 2 : e + 1) >> 1;
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) w[j] = z[q + j];
+                    }
+                    acc0 = mfma(__builtin_bit_cast(bf16x8, make_uint4(w[0], w[1], w[2], w[3])), gd, acc0);
+                    if (a == 0) {
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) dbs0 += (float)gd[j];
+                    }
+                }
+        }
+        __syncthreads();
+    }
+    // lane holds D[ci = a 16 + 4 kg + r][co = b 16 + i]; the slot keeps the
+    // real channels only
+    float *slot = part + unit * SLOT;
+    if constexpr (CO == 2) {
+        // the two halves of the chunk, added in a fixed order
+        float *red = reinterpret_cast<float *>(lds);
+        if (wv >= 2) {
+#pragma unroll
+            for (int t = 0; t < 9; ++t) reinterpret_cast<f32x4 *>(red)[((wv & 1) * 9 + t) * 64 + lane] = acc[t];
+            red[2 * 9 * 64 * 4 + (wv & 1) * 64 + lane] = dbs;
+        }
+        __syncthreads();
+        if (wv >= 2) return;
+#pragma unroll
+        for (int t = 0; t < 9; ++t) acc[t] += reinterpret_cast<f32x4 *>(red)[(wv * 9 + t) * 64 + lane];
+        dbs += red[2 * 9 * 64 * 4 + wv * 64 + lane];
+    }
+    const int co = b * 16 + i;
+    if (co < CO) {
+#pragma unroll
+        for (int t = 0; t < 9; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) slot[(t * 32 + a * 16 + 4 * kg + r) * CO + co] = acc[t][r];
+    }
+    if (a == 0) {
+        dbs += __shfl_xor(dbs, 16);
+        dbs += __shfl_xor(dbs, 32);
+        if (kg == 0 && co < CO) slot[9 * 32 * CO + co] = dbs;
+    }
+    if constexpr (FIRST) {
+        float *s0 = part0 + unit * SLOT0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int m = 16 * a + 4 * kg + r;   // (tap, ci)
+            if (m < 27) s0[m * 32 + co] = acc0[r];
+        }
+        if (a == 0) {
+            dbs0 += __shfl_xor(dbs0, 16);
+            dbs0 += __shfl_xor(dbs0, 32);
+            if (kg == 0) s0[27 * 32 + co] = dbs0;
+        }
+    }
+}
+
 // Slot sums in two fixed-order stages (deterministic for a given slot count):
 // groups of kRedGroup consecutive slots, then the groups in order.  One pair
 // of launches reduces the slots of up to four layers (a training step's
@@ -683,7 +1034,7 @@ __global__ void k_wgrad_reduce2(RedJob J, const float *__restrict__ tmp, int64_t
 // operand precision of the backward contractions) and per-block sums
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) k_loss(const float *out, const float *mask, const float *logq, int64_t P,
-                                              float lam, uint16_t *g, double *part, int w, uint16_t *g_cm)
+                                              float lam, uint16_t *g, double *part)
 {
     __shared__ double red[256];
     double s = 0.0;
@@ -699,9 +1050,6 @@ __global__ void __launch_bounds__(256) k_loss(const float *out, const float *mas
         const float sig = 1.0f / (1.0f + expf(-z));
         const uint16_t g0 = f2bf((float)((sig - t) * invP)), g1 = f2bf((float)(2.0 * lam * dq * invP));
         reinterpret_cast<uint32_t *>(g)[p] = (uint32_t)g0 | ((uint32_t)g1 << 16);
-        const int row = p / w, x = p - row * w;
-        g_cm[(int64_t)(row * 2 + 0) * w + x] = g0;
-        g_cm[(int64_t)(row * 2 + 1) * w + x] = g1;
     }
     red[threadIdx.x] = s;
     __syncthreads();
@@ -801,31 +1149,27 @@ hipError_t cnn_prepare(const float *params, void *prep, hipStream_t st)
 }
 
 static void conv_launch(int l, bool transposed, const void *in, ConvDims d, const void *prep, bool relu, uint16_t *out_bf,
-                        float *out_f32, uint16_t *out_masked, const uint16_t *mask_cm, uint16_t *out_cm,
-                        hipStream_t st)
+                        float *out_f32, hipStream_t st)
 {
     const dim3 grid((unsigned)(d.n * (d.h / kConvRows) * ((d.w + 63) / 64))), block(256);
     if (!transposed) {
         const uint16_t *wm = fwd_mat(prep, l);
         const float *b = bias_of(prep, l);
         if (l == 0)
-            hipLaunchKernelGGL((k_conv<3, 32, true>), grid, block, 0, st, in, d, wm, b, relu, out_bf, out_f32,
-                               out_masked, mask_cm, out_cm);
+            hipLaunchKernelGGL((k_conv<3, 32, true>), grid, block, 0, st, in, d, wm, b, relu, out_bf, out_f32);
         else if (l == 3)
-            hipLaunchKernelGGL((k_conv<32, 2, false>), grid, block, 0, st, in, d, wm, b, relu, out_bf, out_f32,
-                               out_masked, mask_cm, out_cm);
+            hipLaunchKernelGGL((k_conv<32, 2, false>), grid, block, 0, st, in, d, wm, b, relu, out_bf, out_f32);
         else
-            hipLaunchKernelGGL((k_conv<32, 32, false>), grid, block, 0, st, in, d, wm, b, relu, out_bf, out_f32,
-                               out_masked, mask_cm, out_cm);
+            hipLaunchKernelGGL((k_conv<32, 32, false>), grid, block, 0, st, in, d, wm, b, relu, out_bf, out_f32);
     } else {
         // input gradient of layer l: a convolution from Co(l) to Ci(l) = 32 channels
         const uint16_t *wm = bwd_mat(prep, l);
         if (l == 3)
             hipLaunchKernelGGL((k_conv<2, 32, false>), grid, block, 0, st, in, d, wm, (const float *)nullptr, false,
-                               out_bf, out_f32, out_masked, mask_cm, out_cm);
+                               out_bf, out_f32);
         else
             hipLaunchKernelGGL((k_conv<32, 32, false>), grid, block, 0, st, in, d, wm, (const float *)nullptr, false,
-                               out_bf, out_f32, out_masked, mask_cm, out_cm);
+                               out_bf, out_f32);
     }
 }
 
@@ -880,7 +1224,20 @@ uint64_t cnn_wgrad_scratch_bytes(int64_t n, int h, int w)
     return 2 * cm + wgrad_part_bytes(ConvDims{n, h, w});
 }
 
-// the slots of layer l (written to `part`) as a segment of a reduction job
+// the slots of layer l at `part` as a segment of a reduction job
+static void add_seg(int l, int64_t slots, float *part, float *dw, float *db, RedJob &J)
+{
+    RedSeg &g = J.s[J.nseg++];
+    g.part = part;
+    g.dw = dw;
+    g.db = db;
+    g.nw = 9LL * kCi[l] * kCo[l];
+    g.nslots = slots;
+    g.nout = slot_floats(l);
+    g.e0 = J.total;
+    J.total += g.nout;
+}
+
 static void wgrad_slots_launch(int l, const uint16_t *xcm, const uint16_t *gcm, ConvDims d, float *part, float *dw,
                                float *db, RedJob &J, hipStream_t st)
 {
@@ -893,15 +1250,7 @@ static void wgrad_slots_launch(int l, const uint16_t *xcm, const uint16_t *gcm, 
         hipLaunchKernelGGL((k_wgrad<32, 2>), grid, block, 0, st, xcm, gcm, d, R, part);
     else
         hipLaunchKernelGGL((k_wgrad<32, 32>), grid, block, 0, st, xcm, gcm, d, R, part);
-    RedSeg &g = J.s[J.nseg++];
-    g.part = part;
-    g.dw = dw;
-    g.db = db;
-    g.nw = 9LL * kCi[l] * kCo[l];
-    g.nslots = slots;
-    g.nout = slot_floats(l);
-    g.e0 = J.total;
-    J.total += g.nout;
+    add_seg(l, slots, part, dw, db, J);
 }
 
 static void wgrad_reduce(const RedJob &J, float *tmp, ConvDims d, hipStream_t st)
@@ -933,13 +1282,12 @@ static void to_cm(const void *in, ConvDims d, uint16_t *out, hipStream_t st)
 hipError_t cnn_layer_forward(int l, const void *prep, const void *in, int64_t n, int h, int w, float *out_f32,
                              uint16_t *out_bf, hipStream_t st)
 {
-    conv_launch(l, false, in, ConvDims{n, h, w}, prep, l < 3, out_bf, out_f32, nullptr, nullptr, nullptr, st);
+    conv_launch(l, false, in, ConvDims{n, h, w}, prep, l < 3, out_bf, out_f32, st);
     return hipGetLastError();
 }
 
 hipError_t cnn_layer_backward(int l, const void *prep, const void *in, const uint16_t *dy, int64_t n, int h, int w,
-                              float *dw, float *db, float *dx_f32, uint16_t *dx_masked, const uint16_t *mask_cm,
-                              void *scratch, hipStream_t st)
+                              float *dw, float *db, float *dx_f32, void *scratch, hipStream_t st)
 {
     const ConvDims d{n, h, w};
     const uint64_t cm = al256((uint64_t)n * h * w * 32 * 2);
@@ -955,18 +1303,15 @@ hipError_t cnn_layer_backward(int l, const void *prep, const void *in, const uin
     else
         to_cm<32, false>(dy, d, gcm, st);
     wgrad_launch(l, xcm, gcm, d, part, dw, db, st);
-    if (l > 0 && (dx_f32 || dx_masked))
-        conv_launch(l, true, dy, d, prep, false, nullptr, dx_f32, dx_masked, mask_cm, nullptr, st);
+    if (l > 0 && dx_f32) conv_launch(l, true, dy, d, prep, false, nullptr, dx_f32, st);
     return hipGetLastError();
 }
 
 // Workspace of the whole-network calls: 3 hidden activations (BF16, 32 ch),
 // output (FP32, 2 ch), output gradient (BF16, 2 ch), two hidden gradients
-// (BF16, 32 ch), channel-major copies of the input, the activations and the
-// gradients, gradient vector, loss partials, weight-gradient slots.
+// (BF16, 32 ch), gradient vector, loss partials, weight-gradient slots.
 struct CnnWs {
     uint16_t *act[3], *gout, *gh[2];
-    uint16_t *x_cm, *act_cm[3], *gout_cm, *gh_cm[2];
     float *out, *grad, *part;
     double *lpart, *loss;
     uint64_t total;
@@ -989,10 +1334,6 @@ static CnnWs ws_layout(void *base, int64_t n, int h, int w)
     s.out = reinterpret_cast<float *>(take(P * 2 * 4));
     s.gout = reinterpret_cast<uint16_t *>(take(P * 2 * 2));
     for (int k = 0; k < 2; ++k) s.gh[k] = reinterpret_cast<uint16_t *>(take(P * 32 * 2));
-    s.x_cm = reinterpret_cast<uint16_t *>(take(P * 3 * 2));
-    for (int k = 0; k < 3; ++k) s.act_cm[k] = reinterpret_cast<uint16_t *>(take(P * 32 * 2));
-    s.gout_cm = reinterpret_cast<uint16_t *>(take(P * 2 * 2));
-    for (int k = 0; k < 2; ++k) s.gh_cm[k] = reinterpret_cast<uint16_t *>(take(P * 32 * 2));
     s.grad = reinterpret_cast<float *>(take(QSQ_CNN_PARAMS * 4));
     s.lpart = reinterpret_cast<double *>(take(kLossBlocks * 8));
     s.loss = reinterpret_cast<double *>(take(8));
@@ -1003,22 +1344,18 @@ static CnnWs ws_layout(void *base, int64_t n, int h, int w)
 
 uint64_t cnn_workspace_bytes(int64_t n, int h, int w) { return ws_layout(nullptr, n, h, w).total; }
 
-// forward through the four layers; with cm, also the channel-major copies of
-// the hidden activations (for the weight gradients of a training step)
-static void forward_layers(const void *prep, const float *x, ConvDims d, float *out, const CnnWs &s, bool cm,
-                           hipStream_t st)
+// forward through the four layers
+static void forward_layers(const void *prep, const float *x, ConvDims d, float *out, const CnnWs &s, hipStream_t st)
 {
-    conv_launch(0, false, x, d, prep, true, s.act[0], nullptr, nullptr, nullptr, cm ? s.act_cm[0] : nullptr, st);
-    conv_launch(1, false, s.act[0], d, prep, true, s.act[1], nullptr, nullptr, nullptr, cm ? s.act_cm[1] : nullptr,
-                st);
-    conv_launch(2, false, s.act[1], d, prep, true, s.act[2], nullptr, nullptr, nullptr, cm ? s.act_cm[2] : nullptr,
-                st);
-    conv_launch(3, false, s.act[2], d, prep, false, nullptr, out, nullptr, nullptr, nullptr, st);
+    conv_launch(0, false, x, d, prep, true, s.act[0], nullptr, st);
+    conv_launch(1, false, s.act[0], d, prep, true, s.act[1], nullptr, st);
+    conv_launch(2, false, s.act[1], d, prep, true, s.act[2], nullptr, st);
+    conv_launch(3, false, s.act[2], d, prep, false, nullptr, out, st);
 }
 
 hipError_t cnn_forward(const void *prep, const float *x, int64_t n, int h, int w, float *out, void *ws, hipStream_t st)
 {
-    forward_layers(prep, x, ConvDims{n, h, w}, out, ws_layout(ws, n, h, w), false, st);
+    forward_layers(prep, x, ConvDims{n, h, w}, out, ws_layout(ws, n, h, w), st);
     return hipGetLastError();
 }
 
@@ -1029,34 +1366,33 @@ hipError_t cnn_train_step(float *params, float *adam_m, float *adam_v, int64_t t
     const CnnWs s = ws_layout(ws, n, h, w);
     const ConvDims d{n, h, w};
     const int64_t P = n * h * w;
-    to_cm<3, true>(x, d, s.x_cm, st);
-    forward_layers(prep, x, d, s.out, s, true, st);
+    forward_layers(prep, x, d, s.out, s, st);
     const int lb = (int)(blocks_for(P, 256) < kLossBlocks ? blocks_for(P, 256) : kLossBlocks);
-    hipLaunchKernelGGL(k_loss, dim3(lb), dim3(256), 0, st, s.out, mask, logq, P, lam, s.gout, s.lpart, w, s.gout_cm);
+    hipLaunchKernelGGL(k_loss, dim3(lb), dim3(256), 0, st, s.out, mask, logq, P, lam, s.gout, s.lpart);
     hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(256), 0, st, s.lpart, lb, loss_out ? loss_out : s.loss);
     float *g = grad_out ? grad_out : s.grad;
-    // layer 4 .. 1: weight gradients, then the input gradient masked by the
-    // ReLU of the layer below (its BF16 activation > 0)
-    // (each layer's weight-gradient slots in a region of their own; one
-    // reduction of all four layers after the last)
-    const uint16_t *gin = s.gout, *gin_cm = s.gout_cm;
+    // layers 4 .. 2: weight gradients and the input gradient masked by the
+    // ReLU of the layer below (its BF16 activation > 0); layer 2's kernel takes
+    // layer 1's weight gradient along.  Each layer's slots in a region of their
+    // own; one reduction of all four layers after the last.
     RedJob J{};
-    float *part = s.part;
+    float *part[4], *next = s.part;
     for (int l = 3; l >= 0; --l) {
-        const uint16_t *xcm = l == 0 ? s.x_cm : s.act_cm[l - 1];
-        float *dw = g + master_w(l), *db = dw + 9 * kCi[l] * kCo[l];
-        wgrad_slots_launch(l, xcm, gin_cm, d, part, dw, db, J, st);
-        part += slot_bytes(d, l) / 4;
-        if (l > 0) {
-            // the input gradient of layer 1 feeds only layer 0's weight
-            // gradient: its channel-major copy alone
-            uint16_t *gnext = l > 1 ? s.gh[l % 2] : nullptr, *gnext_cm = s.gh_cm[l % 2];
-            conv_launch(l, true, gin, d, prep, false, nullptr, nullptr, gnext, s.act_cm[l - 1], gnext_cm, st);
-            gin = gnext;
-            gin_cm = gnext_cm;
-        }
+        part[l] = next;
+        next += slot_bytes(d, l) / 4;
     }
-    wgrad_reduce(J, part, d, st);
+    const float *none = nullptr;
+    const int R3 = wgrad_rows(d, 3), R1 = wgrad_rows(d, 1);   // (layers 1 and 2 alike)
+    const int64_t u3 = wgrad_slots(d, 3), u1 = wgrad_slots(d, 1);
+    hipLaunchKernelGGL((k_bwd<2, false>), dim3((unsigned)u3), dim3(256), 0, st, s.gout, s.act[2], none, d, R3,
+                       bwd_mat(prep, 3), s.gh[0], part[3], (float *)nullptr);
+    hipLaunchKernelGGL((k_bwd<32, false>), dim3((unsigned)u1), dim3(256), 0, st, s.gh[0], s.act[1], none, d, R1,
+                       bwd_mat(prep, 2), s.gh[1], part[2], (float *)nullptr);
+    hipLaunchKernelGGL((k_bwd<32, true>), dim3((unsigned)u1), dim3(256), 0, st, s.gh[1], s.act[0], x, d, R1,
+                       bwd_mat(prep, 1), (uint16_t *)nullptr, part[1], part[0]);
+    for (int l = 3; l >= 0; --l)
+        add_seg(l, l == 3 ? u3 : u1, part[l], g + master_w(l), g + master_w(l) + 9 * kCi[l] * kCo[l], J);
+    wgrad_reduce(J, next, d, st);
     // Kingma & Ba's defaults; every constant is formed in FP64 and rounded once
     const double b1 = 0.9, b2 = 0.999;
     const float c1 = (float)(1.0 - pow(b1, (double)t)), c2 = (float)(1.0 - pow(b2, (double)t));

@@ -865,7 +865,7 @@ int qsq_cnn_layer_backward(int layer, const void *prep, const void *in, const ui
     if (layer == 0 && dx) return fail(QSQ_ERR_INVALID_ARG, "layer 0 has no input gradient");
     rc = check_ws(scratch, scratch_bytes, qsq::cnn_wgrad_scratch_bytes(n, h, w));
     if (rc) return rc;
-    hipError_t e = qsq::cnn_layer_backward(layer, prep, in, dy, n, h, w, dw, db, dx, nullptr, nullptr, scratch,
+    hipError_t e = qsq::cnn_layer_backward(layer, prep, in, dy, n, h, w, dw, db, dx, scratch,
                                            static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return hip_fail(e, "qsq_cnn_layer_backward");
     return ok();
