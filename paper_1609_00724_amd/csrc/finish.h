@@ -385,9 +385,7 @@ __device__ __forceinline__ double fin_value(const char *recs, const FinAxis &a, 
 // a0 b0 + a1 b1 + a2 b2 over the quad's components
 __device__ __forceinline__ double quad_dot(double a, double b)
 {
-#pragma clang fp contract(off)
-    const double p = a * b;
-    return quad_get<0>(p) + quad_get<1>(p) + quad_get<2>(p);
+    return fma(quad_get<2>(a), quad_get<2>(b), fma(quad_get<0>(a), quad_get<0>(b), quad_get<1>(a * b)));
 }
 
 __device__ __forceinline__ int quad_perm_i(int v, bool next)
@@ -402,8 +400,7 @@ __device__ __forceinline__ double quad_turn(double v, bool next)
 
 __device__ __forceinline__ double quad_cross_len(double a, double b)
 {
-#pragma clang fp contract(off)
-    const double x = quad_turn(a, true) * quad_turn(b, false) - quad_turn(a, false) * quad_turn(b, true);
+    const double x = fma(quad_turn(a, true), quad_turn(b, false), -(quad_turn(a, false) * quad_turn(b, true)));
     return sqrt(quad_dot(x, x));
 }
 
@@ -418,10 +415,9 @@ __device__ __forceinline__ EndDots end_dots(double a, double b)
 }
 __device__ __forceinline__ double end_bracket(const EndDots &e, double &areas)
 {
-#pragma clang fp contract(off)
     const double aa = __shfl_xor(e.aa, 4), bb = __shfl_xor(e.bb, 4), ab = __shfl_xor(e.ab, 4);
     areas = e.area * __shfl_xor(e.area, 4);
-    return e.aa * bb + aa * e.bb - 2.0 * ab * e.ab;
+    return fma(-2.0 * ab, e.ab, fma(e.aa, bb, aa * e.bb));
 }
 
 // A wave takes 16 seeds.  First its quads land the half-lines that left the

@@ -1567,23 +1567,21 @@ __device__ void ck54_pos(const S *__restrict__ nodes, const Geom &g, double sigm
 // secant point if that root is not strictly inside.
 __device__ __forceinline__ double landing_guess(double g0, double s0, double g1, double hs)
 {
-#pragma clang fp contract(off)
     const double sec = -g0 * hs / (g1 - g0);
-    const double cq = (g1 - g0 - s0 * hs) / (hs * hs);
-    const double disc = s0 * s0 - 4.0 * cq * g0;
+    const double cq = fma(-s0, hs, g1 - g0) / (hs * hs);
+    const double disc = fma(s0, s0, -(4.0 * cq * g0));
     const double den = s0 + sqrt(fmax(disc, 0.0));
     const double h = den > 0.0 ? -2.0 * g0 / den : -1.0;
     return (h > 0.0 && h < hs) ? h : sec;
 }
 
 // next trial length of the regula falsi between (a, ga < 0) and (b, gb > 0).
-// (Here and in the Q assembly products and sums round one by one: the
+// (Here and in the Q assembly the fused operations are spelled out: the
 // one-lane and the four-lane kernels of the same step then give the same bits,
 // however the compiler would have fused each of them.)
 __device__ __forceinline__ double landing_secant(double a, double ga, double b, double gb)
 {
-#pragma clang fp contract(off)
-    return (a * gb - b * ga) / (gb - ga);
+    return fma(a, gb, -(b * ga)) / (gb - ga);
 }
 
 // v[d] for a run-time d in 0..2 as selects (a dynamic index would put the
@@ -1846,32 +1844,23 @@ __global__ void __launch_bounds__(256) k_land_euler(TraceJob job)
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ double dot3(const double *a, const double *b)
 {
-#pragma clang fp contract(off)
-    return a[0] * b[0] + a[1] * b[1] + a[2] * b[2];
+    return fma(a[2], b[2], fma(a[0], b[0], a[1] * b[1]));
 }
 
 __device__ __forceinline__ double cross_len(const double *a, const double *b)
 {
-#pragma clang fp contract(off)
-    const double c0 = a[1] * b[2] - a[2] * b[1];
-    const double c1 = a[2] * b[0] - a[0] * b[2];
-    const double c2 = a[0] * b[1] - a[1] * b[0];
-    return sqrt(c0 * c0 + c1 * c1 + c2 * c2);
+    const double c[3] = {fma(a[1], b[2], -(a[2] * b[1])), fma(a[2], b[0], -(a[0] * b[2])), fma(a[0], b[1], -(a[1] * b[0]))};
+    return sqrt(dot3(c, c));
 }
 
 // a - u s
-__device__ __forceinline__ double less_along(double a, double u, double s)
-{
-#pragma clang fp contract(off)
-    return a - u * s;
-}
+__device__ __forceinline__ double less_along(double a, double u, double s) { return fma(-u, s, a); }
 
 // a_F^2 b_B^2 + a_B^2 b_F^2 - 2 (a_B . b_B)(a_F . b_F)
 __device__ __forceinline__ double q_bracket(const double *aF, const double *bF, const double *aB,
                                             const double *bB)
 {
-#pragma clang fp contract(off)
-    return dot3(aF, aF) * dot3(bB, bB) + dot3(aB, aB) * dot3(bF, bF) - 2.0 * dot3(aB, bB) * dot3(aF, bF);
+    return fma(-2.0 * dot3(aB, bB), dot3(aF, bF), fma(dot3(aF, aF), dot3(bB, bB), dot3(aB, aB) * dot3(bF, bF)));
 }
 
 template <typename S, int MODE, bool BATCH>
