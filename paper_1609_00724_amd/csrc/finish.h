@@ -449,7 +449,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(interp
                 if constexpr (BATCH) {
                     const SetDesc &sd = job.sets[job.set_of[i]];
                     a = fin_axis(sd.g, c);
-                    recs = static_cast<const char *>(sd.nodes);
+                    recs = in_global<char>(sd.nodes);
                     gtol = sd.gtol;
                 }
                 double x = job.rec.y[c * P + r], d1 = job.rec.y[(3 + c) * P + r], d2 = job.rec.y[(6 + c) * P + r];
@@ -485,7 +485,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(interp
             if constexpr (BATCH) {
                 const SetDesc &sd = job.sets[job.set_of[i]];
                 a = fin_axis(sd.g, c);
-                recs = static_cast<const char *>(sd.nodes);
+                recs = in_global<char>(sd.nodes);
                 seeds = sd.seeds;
                 ss = os = sd.n;
                 li = i - sd.off;

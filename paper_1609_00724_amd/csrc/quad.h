@@ -523,7 +523,7 @@ __global__ void __launch_bounds__(kQuadWg) k_trace_quad(TraceJob job)
             if constexpr (BATCH) {
                 const SetDesc &sd = job.sets[job.set_of[dir ? rec - job.rec.cap : rec]];
                 g = quad_geom<T, S>(sd.g, c, c3 == 3);
-                recs = static_cast<const char *>(sd.nodes);
+                recs = in_global<char>(sd.nodes);
                 h_init = sd.h_init;
                 hmin = sd.hmin;
                 hmax = (T)sd.h_max;

@@ -48,6 +48,14 @@ constexpr double e1 = b1 - 2825.0 / 27648.0, e3 = b3 - 18575.0 / 48384.0,
 // ---------------------------------------------------------------------------
 // node loads
 // ---------------------------------------------------------------------------
+// A pointer read from a table in memory, as one into global memory: the
+// compiler cannot tell and would take flat loads, which also wait on LDS
+template <typename P>
+__device__ __forceinline__ const P *in_global(const void *p)
+{
+    return (const P *)(const __attribute__((address_space(1))) P *)reinterpret_cast<uintptr_t>(p);
+}
+
 template <typename T>
 struct V4 {
     T x, y, z, w;
@@ -549,57 +557,127 @@ __device__ __forceinline__ T rhs_cached(__amdgpu_buffer_rsrc_t rsrc, int bytes, 
 }
 
 // Per-lane cache of the 8 corner records (direction part, 24 floats) of the
-// cell a lane evaluated last, kept in registers.  A wave in which some lane's
-// stage point moved to another cell issues one gather (a branch taken by the
-// whole wave): the lanes that moved load their new corners, the others pass
-// out-of-range offsets (no memory access) and keep their registers by a
-// select.  A wave whose lanes all stayed in their cells issues no load and
-// waits for none.  No branch under the lane mask, so the 24 values keep their
-// registers from stage to stage without copies.  The node values and the
+// cell a lane evaluated last, kept in registers; the cell before it is parked
+// in the lane's LDS slot, and a lane that moves back into it takes its corners
+// from there instead of memory.  Only the lanes that moved load (the memory
+// pipeline returns data for active lanes alone); a wave whose lanes all stayed
+// in their cells issues no load and waits for none.  The node values and the
 // arithmetic are those of the direct gather: the results are the same bit for
 // bit.  The key is the cell's node index within the field (below 2 GiB).
-// Named scalars (not an array) so that they live in plain registers.
-struct Corner {
-    float x, y, z;
-};
-struct Brick {
-    Corner c000, c100, c010, c110, c001, c101, c011, c111;
+//
+// The corners are vector variables that every load fills in place (`pin` keeps
+// the compiler from splitting them into scalars); only the lanes that move back
+// copy, from a second set, so that their LDS reads and the others' loads are
+// under way together.  From scalars each stage copied 50 registers: 4.87e8
+// vector instructions for the stepping of a 1024 x 1024 map, 4.19e8 so.  (Two
+// slots and reads straight into the corners leave out those copies too, but
+// wait for one after the other: 0.92 of the speed.)
+__device__ __forceinline__ uint32_t lds_address(const void *p)
+{
+    return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char *)p;
+}
+
+// eight corners of 3 values (a + 2b + 4c), loaded with 12 bytes each
+struct CellNodes {
+    typedef float Part __attribute__((ext_vector_type(3)));
+    Part v0, v1, v2, v3, v4, v5, v6, v7;
+    static constexpr int kPlanes = 8;
+
+    template <int C, int I>
+    __device__ __forceinline__ float get() const
+    {
+        return (C == 0 ? v0 : C == 1 ? v1 : C == 2 ? v2 : C == 3 ? v3 : C == 4 ? v4 : C == 5 ? v5 : C == 6 ? v6 : v7)[I];
+    }
+    __device__ __forceinline__ void pin()
+    {
+        asm volatile("" : "+v"(v0), "+v"(v1), "+v"(v2), "+v"(v3), "+v"(v4), "+v"(v5), "+v"(v6), "+v"(v7));
+    }
+    // to the lane's slot, eight planes of a wave's 16-byte rows
+    __device__ __forceinline__ void put(float4 *slot) const
+    {
+        asm volatile("ds_write_b96 %0, %1\n\t"
+                     "ds_write_b96 %0, %2 offset:1024\n\t"
+                     "ds_write_b96 %0, %3 offset:2048\n\t"
+                     "ds_write_b96 %0, %4 offset:3072\n\t"
+                     "ds_write_b96 %0, %5 offset:4096\n\t"
+                     "ds_write_b96 %0, %6 offset:5120\n\t"
+                     "ds_write_b96 %0, %7 offset:6144\n\t"
+                     "ds_write_b96 %0, %8 offset:7168" ::"v"(lds_address(slot)),
+                     "v"(v0), "v"(v1), "v"(v2), "v"(v3), "v"(v4), "v"(v5), "v"(v6), "v"(v7)
+                     : "memory");
+    }
+    __device__ __forceinline__ void get(const float4 *slot)
+    {
+        const f32x4 *p = reinterpret_cast<const f32x4 *>(slot);
+        v0 = p[0].xyz;
+        v1 = p[64].xyz;
+        v2 = p[128].xyz;
+        v3 = p[192].xyz;
+        v4 = p[256].xyz;
+        v5 = p[320].xyz;
+        v6 = p[384].xyz;
+        v7 = p[448].xyz;
+    }
 };
 
-#ifndef QSQ_SECOND_CELL
-#define QSQ_SECOND_CELL 1
-#endif
+// the same 24 values as a direction record packs them, six 16-byte parts
+struct CellDirs {
+    typedef float Part __attribute__((ext_vector_type(4)));
+    Part v0, v1, v2, v3, v4, v5;
+    static constexpr int kPlanes = 6;
 
-typedef uint32_t u32x3_t __attribute__((ext_vector_type(3)));
+    template <int C, int I>
+    __device__ __forceinline__ float get() const
+    {
+        constexpr int e = 3 * C + I, p = e / 4;
+        return (p == 0 ? v0 : p == 1 ? v1 : p == 2 ? v2 : p == 3 ? v3 : p == 4 ? v4 : v5)[e % 4];
+    }
+    __device__ __forceinline__ void pin()
+    {
+        asm volatile("" : "+v"(v0), "+v"(v1), "+v"(v2), "+v"(v3), "+v"(v4), "+v"(v5));
+    }
+    __device__ __forceinline__ void put(float4 *slot) const
+    {
+        Part *p = reinterpret_cast<Part *>(slot);
+        p[0] = v0;
+        p[64] = v1;
+        p[128] = v2;
+        p[192] = v3;
+        p[256] = v4;
+        p[320] = v5;
+    }
+    __device__ __forceinline__ void get(const float4 *slot)
+    {
+        const Part *p = reinterpret_cast<const Part *>(slot);
+        v0 = p[0];
+        v1 = p[64];
+        v2 = p[128];
+        v3 = p[192];
+        v4 = p[256];
+        v5 = p[320];
+    }
+};
+
+// a lane's cached cell: its corners, the keys of the present and the previous
+// cell, the LDS address of the present cell's slot (flip - at: the other slot's)
+template <typename Cell>
+struct CellCache {
+    Cell c = {};
+    int key = -1, prev = -1;
+    float4 *slot = nullptr;
+};
 
 // the direction part of a node record, loaded straight into a corner
 template <typename S>
-__device__ __forceinline__ void load_corner(__amdgpu_buffer_rsrc_t rsrc, int off, Corner &c)
+__device__ __forceinline__ CellNodes::Part load_corner(__amdgpu_buffer_rsrc_t rsrc, int off)
 {
     if constexpr (std::is_same<S, float>::value) {
-        const u32x3_t v = __builtin_amdgcn_raw_buffer_load_b96(rsrc, off, 0, 0);
-        c.x = __uint_as_float(v.x);
-        c.y = __uint_as_float(v.y);
-        c.z = __uint_as_float(v.z);
+        return __builtin_bit_cast(CellNodes::Part, __builtin_amdgcn_raw_buffer_load_b96(rsrc, off, 0, 0));
     } else {
-        load_dir<S>(rsrc, off, c.x, c.y, c.z);
+        float x, y, z;
+        load_dir<S>(rsrc, off, x, y, z);
+        return CellNodes::Part{x, y, z};
     }
-}
-
-
-// the 24 direction values of a cell's corners packed in six float4 (corner
-// order a + 2b + 4c, 3 values each): the parked cell's LDS slot and the
-// direction records share this packing
-__device__ __forceinline__ void unpack_cell(const float4 v[6], Brick &br)
-{
-    br.c000 = Corner{v[0].x, v[0].y, v[0].z};
-    br.c100 = Corner{v[0].w, v[1].x, v[1].y};
-    br.c010 = Corner{v[1].z, v[1].w, v[2].x};
-    br.c110 = Corner{v[2].y, v[2].z, v[2].w};
-    br.c001 = Corner{v[3].x, v[3].y, v[3].z};
-    br.c101 = Corner{v[3].w, v[4].x, v[4].y};
-    br.c011 = Corner{v[4].z, v[4].w, v[5].x};
-    br.c111 = Corner{v[5].y, v[5].z, v[5].w};
 }
 
 // record layouts of the register cache
@@ -612,11 +690,10 @@ constexpr int kLayoutNodes = 0, kLayoutBricks = 1, kLayoutDirs = 2;
 // 8 nbx nby - 4 from an odd one.  DIRS: `dirs` holds the field's direction
 // records, the cell's 24 values in six 16-byte loads (global addresses: the
 // records may exceed 2 GiB), keyed by the cell's index.
-template <typename T, typename S, int MODE, int LAYOUT = kLayoutNodes>
-__device__ __forceinline__ T rhs_regs(__amdgpu_buffer_rsrc_t rsrc, int bytes, const float4 *__restrict__ dirs,
+template <typename T, typename S, int MODE, int LAYOUT, typename Cell, typename Late>
+__device__ __forceinline__ T rhs_regs(__amdgpu_buffer_rsrc_t rsrc, const float4 *__restrict__ dirs,
                                       const Geom &g, const int ib[3], const T q[3], T sigma, const T d1[3],
-                                      const T d2[3], T kx[3], T k1[3], T k2[3], int &cell, Brick &br, float4 *slot,
-                                      int stride, int &cell2)
+                                      const T d2[3], T kx[3], T k1[3], T k2[3], CellCache<Cell> &cc, Late late)
 {
     int c[3];
     T t[3];
@@ -639,58 +716,47 @@ __device__ __forceinline__ T rhs_regs(__amdgpu_buffer_rsrc_t rsrc, int bytes, co
         sz = g.n[0] * g.n[1];
         b = c[2] * sz + c[1] * sy + c[0];
     }
-    const bool miss = b != cell;
-    if (miss) {
-        // only the lanes that moved load (the memory pipeline returns data for
-        // active lanes alone), the direction part only (12 bytes of FP32)
-        constexpr int NB = node_bytes<S>();
-#if QSQ_SECOND_CELL
-        // the cell left behind is parked in the lane's LDS slot; a lane that
-        // moves back into it takes its corners from there instead of memory
-        const bool back = b == cell2;
-        float4 keep[kCachePlanes];
-        if (back) {
-#pragma unroll
-            for (int j = 0; j < kCachePlanes; ++j) keep[j] = slot[j * stride];
+    Cell &v = cc.c;
+    if (b != cc.key) {
+        const bool back = b == cc.prev;
+        cc.prev = cc.key;
+        cc.key = b;
+        Cell old;
+        if (back) old.get(cc.slot);
+        v.put(cc.slot);
+        if (!back) {
+            if constexpr (LAYOUT == kLayoutDirs) {
+                const CellDirs::Part *p = reinterpret_cast<const CellDirs::Part *>(dirs + 6 * (int64_t)b);
+                v = Cell{p[0], p[1], p[2], p[3], p[4], p[5]};
+            } else {
+                constexpr int NB = node_bytes<S>();
+                const int o = NB * b;
+                const int ox = NB * sx, oy = NB * sy, oz = NB * sz;
+                v.v0 = load_corner<S>(rsrc, o);
+                v.v1 = load_corner<S>(rsrc, o + ox);
+                v.v2 = load_corner<S>(rsrc, o + oy);
+                v.v3 = load_corner<S>(rsrc, o + oy + ox);
+                v.v4 = load_corner<S>(rsrc, o + oz);
+                v.v5 = load_corner<S>(rsrc, o + oz + ox);
+                v.v6 = load_corner<S>(rsrc, o + oz + oy);
+                v.v7 = load_corner<S>(rsrc, o + oz + oy + ox);
+            }
         }
-        slot[0 * stride] = make_float4(br.c000.x, br.c000.y, br.c000.z, br.c100.x);
-        slot[1 * stride] = make_float4(br.c100.y, br.c100.z, br.c010.x, br.c010.y);
-        slot[2 * stride] = make_float4(br.c010.z, br.c110.x, br.c110.y, br.c110.z);
-        slot[3 * stride] = make_float4(br.c001.x, br.c001.y, br.c001.z, br.c101.x);
-        slot[4 * stride] = make_float4(br.c101.y, br.c101.z, br.c011.x, br.c011.y);
-        slot[5 * stride] = make_float4(br.c011.z, br.c111.x, br.c111.y, br.c111.z);
-        cell2 = cell;
         if (back) {
-            unpack_cell(keep, br);
-        } else
-#endif
-        if constexpr (LAYOUT == kLayoutDirs) {
-            const float4 *p = dirs + 6 * (int64_t)b;
-            float4 v[6];
-#pragma unroll
-            for (int j = 0; j < 6; ++j) v[j] = p[j];
-            unpack_cell(v, br);
-        } else {
-            const int o = NB * b;
-            const int ox = NB * sx, oy = NB * sy, oz = NB * sz;
-            load_corner<S>(rsrc, o, br.c000);
-            load_corner<S>(rsrc, o + ox, br.c100);
-            load_corner<S>(rsrc, o + oy, br.c010);
-            load_corner<S>(rsrc, o + oy + ox, br.c110);
-            load_corner<S>(rsrc, o + oz, br.c001);
-            load_corner<S>(rsrc, o + oz + ox, br.c101);
-            load_corner<S>(rsrc, o + oz + oy, br.c011);
-            load_corner<S>(rsrc, o + oz + oy + ox, br.c111);
+            old.pin();
+            v = old;
         }
-        cell = b;
     }
+    late();
+    v.pin();
     T val[3], dx[3], dy[3], dz[3];
-#define QSQ_COMPB(F, k)                                                                               \
-    lerp_tree<T>((T)br.c000.F, (T)br.c100.F, (T)br.c010.F, (T)br.c110.F, (T)br.c001.F, (T)br.c101.F,  \
-                 (T)br.c011.F, (T)br.c111.F, t[0], t[1], t[2], val[k], dx[k], dy[k], dz[k])
-    QSQ_COMPB(x, 0);
-    QSQ_COMPB(y, 1);
-    QSQ_COMPB(z, 2);
+#define QSQ_COMPB(I)                                                                                            \
+    lerp_tree<T>((T)v.template get<0, I>(), (T)v.template get<1, I>(), (T)v.template get<2, I>(),               \
+                 (T)v.template get<3, I>(), (T)v.template get<4, I>(), (T)v.template get<5, I>(),               \
+                 (T)v.template get<6, I>(), (T)v.template get<7, I>(), t[0], t[1], t[2], val[I], dx[I], dy[I], dz[I])
+    QSQ_COMPB(0);
+    QSQ_COMPB(1);
+    QSQ_COMPB(2);
 #undef QSQ_COMPB
     const T ihx = (T)g.ih[0], ihy = (T)g.ih[1], ihz = (T)g.ih[2];
     T u[3], G[3][3];
@@ -703,7 +769,10 @@ __device__ __forceinline__ T rhs_regs(__amdgpu_buffer_rsrc_t rsrc, int bytes, co
             G[2][i] = dz[i] * ihz;
         }
     } else {
-        const T bb = val[0] * val[0] + val[1] * val[1] + val[2] * val[2];
+        // (the order of the sum that the four-lane kernel takes for the same call)
+        const T bb = std::is_same<S, float>::value
+                         ? fma(val[2], val[2], fma(val[1], val[1], val[0] * val[0]))
+                         : fma(val[2], val[2], fma(val[0], val[0], val[1] * val[1]));
         const T bn = sqrt(bb);
         const T inv = bn > (T)1e-300 ? (T)1 / bn : (T)0;
         T Gb[3][3];
@@ -758,21 +827,19 @@ constexpr int kGatherDirect = 0, kGatherLds = 1, kGatherRegs = 2, kGatherCells =
               kGatherDirs = 5;
 
 // one RHS evaluation of the stepping kernel
-template <typename T, typename S, int MODE, int GATHER>
+template <typename T, typename S, int MODE, int GATHER, typename Cell, typename Late>
 __device__ __forceinline__ T rhs_step(const S *__restrict__ nodes, __amdgpu_buffer_rsrc_t rsrc, int bytes,
                                       const Geom &g, const int ib[3], const T q[3], T sigma, const T d1[3],
-                                      const T d2[3], T kx[3], T k1[3], T k2[3], int cc[3], float4 *slot,
-                                      int stride, int &cell, Brick &br)
+                                      const T d2[3], T kx[3], T k1[3], T k2[3], int lc[3], float4 *slot,
+                                      int stride, CellCache<Cell> &cc, Late late)
 {
     if constexpr (GATHER == kGatherLds)
-        return rhs_cached<T, S, MODE>(rsrc, bytes, g, ib, q, sigma, d1, d2, kx, k1, k2, cc, slot, stride);
+        return rhs_cached<T, S, MODE>(rsrc, bytes, g, ib, q, sigma, d1, d2, kx, k1, k2, lc, slot, stride);
     else if constexpr (GATHER == kGatherRegs || GATHER == kGatherBricks || GATHER == kGatherDirs)
-        // (cc[0], the LDS variant's cell key, keys the register cache's parked
-        // cell; the direction records' variant gets them as `nodes`)
+        // (the direction records' variant gets them as `nodes`)
         return rhs_regs<T, S, MODE,
                         GATHER == kGatherBricks ? kLayoutBricks : GATHER == kGatherDirs ? kLayoutDirs : kLayoutNodes>(
-            rsrc, bytes, reinterpret_cast<const float4 *>(nodes), g, ib, q, sigma, d1, d2, kx, k1, k2, cell, br, slot,
-            stride, cc[0]);
+            rsrc, reinterpret_cast<const float4 *>(nodes), g, ib, q, sigma, d1, d2, kx, k1, k2, cc, late);
     else
         return rhs<T, S, MODE, GATHER == kGatherCells>(nodes, g, ib, q, sigma, d1, d2, kx, k1, k2);
 }
@@ -971,7 +1038,7 @@ __global__ void __launch_bounds__(256) k_seed_pass(TraceJob job)
             job.set_of[i] = set;
             const SetDesc &sd = job.sets[set];
             gl = sd.g;
-            nodes = static_cast<const S *>(sd.nodes);
+            nodes = in_global<S>(sd.nodes);
             sp = sd.seeds;
             ss = sd.n;
             li = i - sd.off;
@@ -1094,13 +1161,45 @@ static __global__ void k_land_compact(TraceJob job)
 // ---------------------------------------------------------------------------
 // k_trace: persistent stepping kernel
 // ---------------------------------------------------------------------------
+// Waves per SIMD, least and most.  Left alone, the compiler moves the deviation
+// slopes of every stage to the end of the step (the positions do not need
+// them) and holds 9 corner differences a stage for them: 210 .. 250 registers,
+// two waves.  With each stage's slopes formed while the next stage's corners
+// are on their way (`late` in rhs_regs) 168 do: three waves, stepping of a 1024
+// x 1024 map 1.64 -> 1.36 ms (together with the corners above), the first
+// pass of a 256^3 volume from brick records 89.4 -> 82.6 ms, where the L1 takes
+// a lane's record per cycle 81 % of the time.  The other gathers are bound by
+// the caches behind it, which three waves' cells overflow: direction records
+// 43.8 ms with two waves, 46.2 with three; batched fields 3.1 against 3.6.
+template <typename T, int GATHER, bool EULER>
+constexpr int trace_waves(int most)
+{
+    const bool three = EULER || GATHER == kGatherRegs || GATHER == kGatherBricks;
+    return most ? (sizeof(T) == 4 && !three ? 2 : 8) : three ? 3 : 1;
+}
+
+// values formed here, not where they are used last
+template <typename T>
+__device__ __forceinline__ void hold(T v[3])
+{
+    asm volatile("" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]));
+}
+
+// a value that all lanes hold, in scalar registers
+__device__ __forceinline__ float uniform(float v)
+{
+    return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v)));
+}
+__device__ __forceinline__ double uniform(double v) { return v; }
+
 // (the Euler variants fit 3 waves per SIMD: one evaluation's state per step)
 template <typename T, typename S, int MODE, int GATHER, bool BATCH, bool EULER = false>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(EULER ? 3 : 1))) k_trace(TraceJob job)
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(trace_waves<T, GATHER, EULER>(0), trace_waves<T, GATHER, EULER>(1)))) k_trace(TraceJob job)
 {
     static_assert(GATHER == kGatherDirect || (!BATCH && sizeof(T) == 4),
                   "cell caches: one field per launch, FP32 corner values");
     static_assert(GATHER != kGatherDirs || std::is_same<S, float>::value, "direction records: FP32 storage");
+    constexpr bool REGS = GATHER == kGatherRegs || GATHER == kGatherBricks || GATHER == kGatherDirs;
     constexpr bool CACHED =
         GATHER == kGatherLds || GATHER == kGatherRegs || GATHER == kGatherBricks || GATHER == kGatherDirs;
     // field and step limits of the lane's line: launch constants for one
@@ -1121,28 +1220,54 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(EULER 
     T D1[3] = {0, 0, 0}, D2[3] = {0, 0, 0};
     T h = 0, sigma = 1;
     int attempts = 0;
-    int64_t rec = 0;
+    int rec = 0;
     bool active = false, done = false, have_k1 = false;
     T Kx[6][3], K1[6][3], K2[6][3];
 
-    const T rtol = (T)o.rtol, atol = (T)o.atol;
-    T hmax = (T)o.h_max;
-    T ih[3] = {(T)g.ih[0], (T)g.ih[1], (T)g.ih[2]};
-    unsigned long long c_att = 0, c_ev = 0, c_act = 0, c_land = 0;   // work counters
+    const T rtol = uniform((T)o.rtol), atol = uniform((T)o.atol);
+    T hmax = uniform((T)o.h_max);
+    T ih[3] = {uniform((T)g.ih[0]), uniform((T)g.ih[1]), uniform((T)g.ih[2])};
+    // work counters, the wave's, summed from lane masks: attempts, first
+    // evaluations of a step, lines begun, lines handed to the landing
+    unsigned long long c_att = 0, c_first = 0, c_act = 0, c_land = 0;
+    bool tried = false, first = false, landed = false;   // of the lane's last attempt
     // cached-gather state
     const uint64_t nrec = GATHER == kGatherBricks
                               ? 8 * (uint64_t)((g.n[0] + 1) / 2) * ((g.n[1] + 1) / 2) * ((g.n[2] + 1) / 2)
                               : (uint64_t)g.n[0] * g.n[1] * g.n[2];
     const int cbytes = CACHED ? (int)(node_bytes<S>() * nrec) : 0;
     const __amdgpu_buffer_rsrc_t rsrc = node_rsrc(GATHER == kGatherBricks ? job.bricks : job.nodes, cbytes);
-    int cache_cell[3] = {-1, -1, -1};
     // LDS cell cache: kCachePlanes planes of blockDim.x float4 (dynamic size)
     extern __shared__ float4 lds_cache[];
+    int lds_cell[3] = {-1, -1, -1};
     const int stride = (int)blockDim.x;
     float4 *slot = lds_cache + threadIdx.x;
-    // register cell cache: the corners of the cell a lane evaluated last
-    int reg_cell = -1;
-    Brick reg_brick = {};
+    // register cell cache: a wave's slots together
+    using Cell = std::conditional_t<GATHER == kGatherDirs, CellDirs, CellNodes>;
+    CellCache<Cell> cell;
+    cell.slot = lds_cache + (int)(threadIdx.x >> 6) * 64 * Cell::kPlanes + lane;
+    // the brick variant's address registers make 168 too few: position and
+    // length wait in LDS while the stages run (two planes of a wave's 16-byte
+    // rows behind the slots)
+    typedef double f64x2 __attribute__((ext_vector_type(2)));
+    constexpr bool PARK = GATHER == kGatherBricks && !EULER;   // (the launcher adds the planes)
+    f64x2 *park = reinterpret_cast<f64x2 *>(lds_cache + Cell::kPlanes * blockDim.x) + (int)(threadIdx.x >> 6) * 128 + lane;
+    auto leave = [&] {
+        if constexpr (PARK) {
+            park[0] = f64x2{X[0], X[1]};
+            park[64] = f64x2{X[2], s};
+        }
+    };
+    auto fetch = [&] {
+        if constexpr (PARK) {
+            asm volatile("" ::: "memory");
+            const f64x2 u = park[0], v = park[64];
+            X[0] = u.x;
+            X[1] = u.y;
+            X[2] = v.x;
+            s = v.y;
+        }
+    };
 
     // Work distribution.  The work list is split into nparts contiguous parts
     // (one, or kParts with the partition bit of the launch word), each with
@@ -1165,6 +1290,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(EULER 
     bool first_fill = true;
     for (;;) {
         // ---- refill idle lanes
+        c_att += __popcll(__ballot(tried));
+        c_first += __popcll(__ballot(first));
+        c_land += __popcll(__ballot(landed));
+        tried = first = landed = false;
         const uint64_t need = __ballot(!active && !done);
         if (need) {
             const int j = __popcll(need & ((1ull << lane) - 1ull));   // rank among idle lanes
@@ -1188,10 +1317,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(EULER 
                             p = p + 1 < nparts ? p + 1 : 0;
                         }
                     }
-                    b = __shfl(b, leader);
-                    part = __shfl(p, leader);
-                    spent = __shfl(t, leader);
-                    const int64_t fresh = (int64_t)b;
+                    part = __builtin_amdgcn_readlane(p, leader);
+                    spent = __builtin_amdgcn_readlane(t, leader);
+                    const int64_t fresh = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(b >> 32), leader) << 32) |
+                                                    (uint32_t)__builtin_amdgcn_readlane((int)b, leader));
                     const int64_t fend = spent < nparts ? min(fresh + kChunk, pbeg(part + 1)) : fresh;
                     const int64_t got = fend - fresh;
                     if (j < avail)
@@ -1207,6 +1336,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(EULER 
                 }
             }
             first_fill = false;
+            c_act += __popcll(__ballot(!active && !done && item >= 0));
             if (!active && !done) {
                 if (item < 0) {
                     // no item this round; done once every part is used up
@@ -1218,7 +1348,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(EULER 
                     if constexpr (BATCH) {
                         const SetDesc &sd = job.sets[job.set_of[dir ? rec - job.rec.cap : rec]];
                         gl = sd.g;
-                        nodes = static_cast<const S *>(sd.nodes);
+                        nodes = in_global<S>(sd.nodes);
                         h_init = sd.h_init;
                         hmin = sd.hmin;
                         hmax = (T)sd.h_max;
@@ -1236,11 +1366,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(EULER 
                         D2[k] = (T)job.rec.y[(6 + k) * P + rec];
                     }
                     s = 0.0;
+                    leave();
                     h = (T)h_init;
                     attempts = 0;
                     have_k1 = false;
                     active = true;
-                    ++c_act;
                 }
             }
         }
@@ -1255,6 +1385,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(EULER 
         if (!active) continue;
 
         // ---- one step attempt (oracle order: step cap, null, trial, accept/reject, exit)
+        fetch();
         int stop = -1;
         if (attempts >= o.max_steps) stop = QSQ_END_MAX_STEPS;
 
@@ -1270,8 +1401,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(EULER 
             }
             if (!EULER && !have_k1) {
                 const T un2 = rhs_step<T, S, MODE, GATHER>(nodes, rsrc, cbytes, g, ib, fb, (T)1, D1, D2, Kx[0], K1[0],
-                                                           K2[0], cache_cell, slot, stride, reg_cell, reg_brick);
-                ++c_ev;
+                                                           K2[0], lds_cell, slot, stride, cell, [] {});
+                first = true;
                 if (un2 < (T)1e-12) stop = QSQ_END_NULL;   // NaN: not a null (the step reports it)
                 have_k1 = true;
             }
@@ -1281,9 +1412,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(EULER 
             // per fixed step h, the whole state advanced along it
             if (stop < 0) {
                 const T un2 = rhs_step<T, S, MODE, GATHER>(nodes, rsrc, cbytes, g, ib, fb, (T)1, D1, D2, Kx[0],
-                                                           K1[0], K2[0], cache_cell, slot, stride, reg_cell,
-                                                           reg_brick);
-                ++c_ev;
+                                                           K1[0], K2[0], lds_cell, slot, stride, cell, [] {});
+                first = true;
                 if (un2 < (T)1e-12) stop = QSQ_END_NULL;   // NaN: not a null (the step reports it)
             }
             if (stop < 0) {
@@ -1304,7 +1434,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(EULER 
                     fsum += ((T)Xn[i] + D1n[i]) + D2n[i];
                 }
                 ++attempts;
-                ++c_att;
+                tried = true;
                 if (!isfinite(fsum)) {
                     stop = QSQ_END_NONFINITE;
                 } else if (outside_box(g, Xn[0], Xn[1], Xn[2])) {
@@ -1313,7 +1443,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(EULER 
                                          (double)D2[0], (double)D2[1], (double)D2[2]};
                     put_rec(job.rec, rec, y, s, (double)hs, kPendingLand, attempts);
                     active = false;
-                    ++c_land;
+                    landed = true;
                 } else {
 #pragma unroll
                     for (int i = 0; i < 3; ++i) {
@@ -1361,7 +1491,12 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(EULER 
             d2[i] = fma(hsig, a2, D2[i]);                                                           \
         }                                                                                           \
         rhs_step<T, S, MODE, GATHER>(nodes, rsrc, cbytes, g, ib, q, (T)1, d1, d2, Kx[ST], K1[ST], K2[ST], \
-                                     cache_cell, slot, stride, reg_cell, reg_brick);               \
+                                     lds_cell, slot, stride, cell, [&] {          \
+            if constexpr (ST > 1) {                                                                 \
+                hold(K1[ST - 1]);                                                                   \
+                hold(K2[ST - 1]);                                                                   \
+            }                                                                                       \
+        });                                                                                         \
     }
             QSQ_STAGE(1, (T)ck::a21)
             QSQ_STAGE(2, (T)ck::a31, (T)ck::a32)
@@ -1370,6 +1505,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(EULER 
             QSQ_STAGE(5, (T)ck::a61, (T)ck::a62, (T)ck::a63, (T)ck::a64, (T)ck::a65)
 #undef QSQ_STAGE
             // 5th-order solution (propagated) and the error estimate y5 - y4
+            fetch();
             double Xn[3];
             T D1n[3], D2n[3];
             T err = 0, fsum = 0;
@@ -1395,8 +1531,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(EULER 
             }
             finite = isfinite(fsum);
             ++attempts;
-            ++c_att;
-            c_ev += 5;
+            tried = true;
             if (!finite) {
                 stop = QSQ_END_NONFINITE;
             } else if (err > (T)1) {
@@ -1410,7 +1545,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(EULER 
                                      (double)D2[0], (double)D2[1], (double)D2[2]};
                 put_rec(job.rec, rec, y, s, (double)hs, kPendingLand, attempts);
                 active = false;
-                ++c_land;
+                landed = true;
             } else {
 #pragma unroll
                 for (int i = 0; i < 3; ++i) {
@@ -1427,9 +1562,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(EULER 
                     const T f = err > (T)0 ? (T)0.9 * (T)exp2((T)-0.2 * (T)log2(err)) : (T)5;
                     h = hs * (f < (T)5 ? f : (T)5);
                 }
+                leave();
             }
         }
         if (stop >= 0) {
+            fetch();
             const double y[9] = {X[0], X[1], X[2], (double)D1[0], (double)D1[1], (double)D1[2],
                                  (double)D2[0], (double)D2[1], (double)D2[2]};
             put_rec(job.rec, rec, y, s, 0.0, stop, attempts);
@@ -1437,19 +1574,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(EULER 
         }
     }
     if (job.work) {
-        // wave-level sums, one atomic per counter per wave
+        // one atomic per counter per wave (an adaptive step evaluates 5 more slopes)
+        const unsigned long long sum[4] = {c_att, c_first + (EULER ? 0 : 5 * c_att), c_act, c_land};
+        if (lane == 0 && (sum[0] | sum[1] | sum[2] | sum[3])) {   // waves that stepped nothing add nothing
 #pragma unroll
-        for (int o2 = 32; o2 >= 1; o2 >>= 1) {
-            c_att += __shfl_xor(c_att, o2);
-            c_ev += __shfl_xor(c_ev, o2);
-            c_act += __shfl_xor(c_act, o2);
-            c_land += __shfl_xor(c_land, o2);
-        }
-        if (lane == 0 && (c_att | c_ev | c_act | c_land)) {   // waves that stepped nothing add nothing
-            atomicAdd(&job.work[0], c_att);
-            atomicAdd(&job.work[1], c_ev);
-            atomicAdd(&job.work[2], c_act);
-            atomicAdd(&job.work[3], c_land);
+            for (int k = 0; k < 4; ++k) atomicAdd(&job.work[k], sum[k]);
         }
     }
 }
@@ -1637,7 +1766,7 @@ __global__ void __launch_bounds__(256) k_land(TraceJob job)
         if constexpr (BATCH) {
             const SetDesc &sd = job.sets[job.set_of[i]];
             gl = sd.g;
-            nodes = static_cast<const S *>(sd.nodes);
+            nodes = in_global<S>(sd.nodes);
             gtol = sd.gtol;
         }
         const Geom &g = gl;
@@ -1736,7 +1865,7 @@ __global__ void __launch_bounds__(256) k_land_final(TraceJob job)
         if constexpr (BATCH) {
             const SetDesc &sd = job.sets[job.set_of[i]];
             gl = sd.g;
-            nodes = static_cast<const S *>(sd.nodes);
+            nodes = in_global<S>(sd.nodes);
         }
         const Geom &g = gl;
         const double sigma = dir ? -1.0 : 1.0;
@@ -1781,7 +1910,7 @@ __global__ void __launch_bounds__(256) k_land_euler(TraceJob job)
         if constexpr (BATCH) {
             const SetDesc &sd = job.sets[job.set_of[i]];
             gl = sd.g;
-            nodes = static_cast<const S *>(sd.nodes);
+            nodes = in_global<S>(sd.nodes);
         }
         const Geom &g = gl;
         const double sigma = dir ? -1.0 : 1.0;
@@ -1882,7 +2011,7 @@ __global__ void __launch_bounds__(256) k_assemble(TraceJob job)
         if constexpr (BATCH) {
             const SetDesc &sd = job.sets[job.set_of[i]];
             gl = sd.g;
-            nodes = static_cast<const S *>(sd.nodes);
+            nodes = in_global<S>(sd.nodes);
             seeds = sd.seeds;
             ss = os = sd.n;
             li = i - sd.off;
@@ -2178,15 +2307,15 @@ static hipError_t launch_typed(const TraceJob &job, hipStream_t st)
                 dirs_kern = trace_kernel<T, S, MODE, kGatherDirs, false>(euler);
         if (dirs_kern) {
             kern = dirs_kern;
-            lds = QSQ_SECOND_CELL ? kCachePlanes * wg * sizeof(float4) : 0;
+            lds = CellDirs::kPlanes * wg * sizeof(float4);
         } else if (gather == 5 && job.bricks && brick_bytes < limit) {
             kern = trace_kernel<T, S, MODE, kGatherBricks, false>(euler);
-            lds = QSQ_SECOND_CELL ? kCachePlanes * wg * sizeof(float4) : 0;
+            lds = (CellNodes::kPlanes + 2) * wg * sizeof(float4);
         } else if (gather == 4 && job.cells) {
             kern = trace_kernel<T, S, MODE, kGatherCells, false>(euler);
         } else if ((gather == 3 || gather == 5 || gather == 6 || gather == 0) && fits) {
             kern = trace_kernel<T, S, MODE, kGatherRegs, false>(euler);
-            lds = QSQ_SECOND_CELL ? kCachePlanes * wg * sizeof(float4) : 0;
+            lds = CellNodes::kPlanes * wg * sizeof(float4);
         } else if (gather == 2 && fits) {
             kern = trace_kernel<T, S, MODE, kGatherLds, false>(euler);
             lds = kCachePlanes * wg * sizeof(float4);
@@ -2389,12 +2518,12 @@ static bool quad_addressable(const Geom &g, int storage)
 // Largest work list that the four-lane kernel takes under an automatic gather
 // (0: none; a named gather always gets the one-lane kernel).  A list that fits
 // the grid lasts as long as its longest line, and four lanes a line shorten
-// that chain: 64 000 half-lines of 224 x 224 x 112 cells at a 1-cell cap take
-// 1.09 ms against 2.10 (8 cells: 0.43 against 0.53).  A longer list is bound
-// by VALU issue, where four lanes a line cost 1.7 times the instructions and
-// the refills weigh more the shorter the lines: 128 000 half-lines 1.71
-// against 2.25 ms (64^2 x 32 cells at 8 cells a step 0.42 against 0.40),
-// 512 000 4.07 against 4.41 (1.02 against 0.87).  So lines of 32 steps or more
+// that chain: 60 000 half-lines of 192 x 192 x 96 cells at a 1-cell cap take
+// 0.91 ms against 1.67 (4 cells: 0.55 against 0.91), 240 000 1.98 against 2.55.
+// A longer list is bound by VALU issue, where four lanes a line cost 1.7 times
+// the instructions and the refills weigh more the shorter the lines: 520 000
+// half-lines 3.36 against 3.54 ms; 64^2 x 32 cells at 8 cells a step 128 000
+// 0.42 against 0.40, 512 000 1.02 against 0.87.  So lines of 32 steps or more
 // across the box's longest edge go four lanes each up to 2^19, shorter ones up
 // to 2^16.  FP64 stepping keeps half as many waves resident and a batch
 // reloads its grid with every line: up to 2^17 (FP64, 128^2 x 64 cells at 1
