@@ -1167,7 +1167,7 @@ static __global__ void k_land_compact(TraceJob job)
 // two waves.  With each stage's slopes formed while the next stage's corners
 // are on their way (`late` in rhs_regs) 168 do: three waves, stepping of a 1024
 // x 1024 map 1.64 -> 1.36 ms (together with the corners above), the first
-// pass of a 256^3 volume from brick records 89.4 -> 82.6 ms, where the L1 takes
+// pass over a 384 x 384 x 256 rope from brick records 89.4 -> 82.6 ms, the L1 taking
 // a lane's record per cycle 81 % of the time.  The other gathers are bound by
 // the caches behind it, which three waves' cells overflow: direction records
 // 43.8 ms with two waves, 46.2 with three; batched fields 3.1 against 3.6.
