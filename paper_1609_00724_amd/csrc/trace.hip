@@ -1006,7 +1006,10 @@ __device__ __forceinline__ int64_t seed_count(const TraceJob &j)
 // seed pass (FP64, one thread per seed): frame of eq. (9), and the half-lines
 // that end at once -- seed outside the box, a null at the seed, or a seed on a
 // face with its (signed) field pointing out (zero length, lowest such face).
-// The others are flagged for stepping.
+// The others are flagged for stepping.  Bound by its writes (200 B a seed).  The
+// faces are taken in an unrolled loop from the last to the first, all indices
+// known: a search that ends at the first hit put the seed's arrays in scratch
+// memory (168 B a lane), and 1.3 M seeds took 134 us against 63 (4.1 TB/s).
 // ---------------------------------------------------------------------------
 // set holding global seed i: the last set whose first seed is <= i (empty
 // sets share their offset with the next set and are skipped)
@@ -1065,19 +1068,21 @@ __global__ void __launch_bounds__(256) k_seed_pass(TraceJob job)
                     y0[3 + k] = a[k] / sc[k];
                     y0[6 + k] = b[k] / sc[k];
                 }
+#pragma unroll
                 for (int dir = 0; dir < 2; ++dir) {
                     const double sg = dir ? -1.0 : 1.0;
-                    int face = -1;
-                    for (int f = 0; f < 6 && face < 0; ++f) {
+                    st[dir] = kPendingStep;
+#pragma unroll
+                    for (int f = 5; f >= 0; --f) {   // the lowest face wins
                         const int d = f >> 1;
                         const bool on = (f & 1) ? x0[d] == g.hi[d] : x0[d] == g.lo[d];
                         const double out = (f & 1) ? sg * nn[d] : -sg * nn[d];
-                        if (on && out > 0.0) face = f;
+                        if (on && out > 0.0) st[dir] = f;
                     }
-                    st[dir] = face >= 0 ? face : kPendingStep;
                 }
             }
         }
+#pragma unroll
         for (int dir = 0; dir < 2; ++dir) {
             put_rec(job.rec, dir * job.rec.cap + i, y0, 0.0, 0.0, st[dir], 0);
             job.rec.flag[dir * n + i] = st[dir] == kPendingStep ? 1 : 0;
