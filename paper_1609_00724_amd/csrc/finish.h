@@ -114,10 +114,11 @@ __device__ __forceinline__ void fin_stencil(const char *recs, const FinAxis &a, 
 }
 
 // 1 / |v| over the quad's three components (0 for |v| <= 1e-300); bn = |v|
+template <typename S, int MODE>
 __device__ __forceinline__ double fin_inverse(double val, double &bn)
 {
     const double v0 = quad_get<0>(val), v1 = quad_get<1>(val), v2 = quad_get<2>(val);
-    bn = sqrt(fma(v2, v2, fma(v0, v0, v1 * v1)));
+    bn = sqrt(norm2<double, S, MODE>(v0, v1, v2));
     return bn > 1e-300 ? 1.0 / bn : 0.0;
 }
 
@@ -133,7 +134,7 @@ __device__ __forceinline__ double fin_u(const char *recs, const FinAxis &a, int 
         fin_corners<S>(recs + (c3 == 3 ? 2 : c3) * value_bytes<S>(), a, ib, q, t, cell);
         val = fin_lerp(cell, t);
     }
-    return normalize_first<MODE>() ? val : val * fin_inverse(val, bn);
+    return normalize_first<MODE>() ? val : val * fin_inverse<S, MODE>(val, bn);
 }
 
 // right-hand side for the lane's components: sigma (u, J d1, J d2)
@@ -157,7 +158,7 @@ __device__ __forceinline__ void fin_rhs(const char *recs, const FinAxis &a, int 
         for (int j = 0; j < 3; ++j) G[j] = Gb[j];
     } else {
         double bn;
-        const double inv = fin_inverse(val, bn);
+        const double inv = fin_inverse<S, MODE>(val, bn);
         u = val * inv;
         const double u0 = quad_get<0>(u), u1 = quad_get<1>(u), u2 = quad_get<2>(u);
 #pragma unroll
@@ -378,7 +379,7 @@ __device__ __forceinline__ double fin_value(const char *recs, const FinAxis &a, 
         mag = quad_get<3>(val);
         return val;
     }
-    const double inv = fin_inverse(val, mag);
+    const double inv = fin_inverse<S, MODE>(val, mag);
     return val * inv;
 }
 

@@ -185,7 +185,7 @@ __device__ __forceinline__ void quad_stencil(const char *recs, int n, uint32_t s
 // deviations d1, d2 (the lane's components); returns |u|^2 if NORM2.  `recs`
 // points at the records, `c3` is the lane's place in its quad.  Record keys and byte
 // offsets fit 32 bits and the axis products 24 bits (the launcher checks).
-template <typename T, typename S, int MODE, bool FIRST, bool NORM2>
+template <typename T, typename S, int MODE, bool NORM2>
 __device__ __forceinline__ T quad_rhs(const char *recs, const QuadGeom<T> &g, int c3, const QuadRef<T> &r, T q, T d1,
                                       T d2, T &kx, T &k1, T &k2, QuadCell<T> &cell)
 {
@@ -232,12 +232,7 @@ __device__ __forceinline__ T quad_rhs(const char *recs, const QuadGeom<T> &g, in
         }
     } else {
         const T v[3] = {quad_get<0>(val), quad_get<1>(val), quad_get<2>(val)};
-        // the order in which the one-lane kernel's |B|^2 comes out of the
-        // compiler: the register cache's (FP32 records and stepping, one
-        // field) starts from the first component, the direct gather's from
-        // the second
-        const T bb = FIRST ? fma(v[2], v[2], fma(v[1], v[1], v[0] * v[0])) : fma(v[2], v[2], fma(v[0], v[0], v[1] * v[1]));
-        const T bn = sqrt(bb);
+        const T bn = sqrt(norm2<T, S, MODE>(v[0], v[1], v[2]));
         const T inv = bn > (T)1e-300 ? (T)1 / bn : (T)0;
         const T uu[3] = {v[0] * inv, v[1] * inv, v[2] * inv};
         u = val * inv;
@@ -288,7 +283,7 @@ __device__ __forceinline__ bool quad_any(bool f)
 // One step attempt of the quad's line (the one-lane kernel's order: step cap,
 // null, trial, accept or reject, exit); writes the end record and clears
 // st.active when the line ends.  Every branch is taken by whole quads.
-template <typename T, typename S, int MODE, bool FIRST, bool EULER>
+template <typename T, typename S, int MODE, bool EULER>
 __device__ __forceinline__ void quad_attempt(const char *recs, const QuadGeom<T> &g, const StepOpts &o, T rtol,
                                              T atol, T hmax, double hmin, int c3,
                                              const Records &rec, QuadState<T> &st, QuadCell<T> &cell, QuadCount &cnt)
@@ -303,7 +298,7 @@ __device__ __forceinline__ void quad_attempt(const char *recs, const QuadGeom<T>
         ref = quad_ref<T>(g, (int)fl);
         fb = (T)(xg - fl);
         if (EULER || !st.have_k1) {
-            const T un2 = quad_rhs<T, S, MODE, FIRST, true>(recs, g, c3, ref, fb, st.D1, st.D2, st.Kx0, st.K10,
+            const T un2 = quad_rhs<T, S, MODE, true>(recs, g, c3, ref, fb, st.D1, st.D2, st.Kx0, st.K10,
                                                              st.K20, cell);
             ++cnt.ev;
             if (un2 < (T)1e-12) stop = QSQ_END_NULL;   // NaN: not a null (the step reports it)
@@ -341,7 +336,7 @@ __device__ __forceinline__ void quad_attempt(const char *recs, const QuadGeom<T>
             a1 = fma(c_[j], K1[j], a1);                                                                            \
             a2 = fma(c_[j], K2[j], a2);                                                                            \
         }                                                                                                          \
-        quad_rhs<T, S, MODE, FIRST, false>(recs, g, c3, ref, fma(hsig * ax, g.iha, fb), fma(hsig, a1, st.D1),        \
+        quad_rhs<T, S, MODE, false>(recs, g, c3, ref, fma(hsig * ax, g.iha, fb), fma(hsig, a1, st.D1),        \
                                             fma(hsig, a2, st.D2), Kx[ST], K1[ST], K2[ST], cell);                   \
     }
             QSQ_QSTAGE(1, (T)ck::a21)
@@ -499,8 +494,6 @@ __device__ __forceinline__ void quad_count(unsigned long long *work, const QuadC
 template <typename T, typename S, int MODE, bool BATCH, bool EULER>
 __global__ void __launch_bounds__(kQuadWg) k_trace_quad(TraceJob job)
 {
-    constexpr bool FIRST =
-        !BATCH && std::is_same<T, float>::value && std::is_same<S, float>::value && interp_order<MODE>() == 1;
     const StepOpts &o = job.o;
     const int c3 = (int)(threadIdx.x & 3), c = c3 == 3 ? 2 : c3;
     const int64_t total = *job.rec.n_work;
@@ -540,6 +533,6 @@ __global__ void __launch_bounds__(kQuadWg) k_trace_quad(TraceJob job)
             st.have_k1 = false;
             ++cnt.act;
         },
-        [&] { quad_attempt<T, S, MODE, FIRST, EULER>(recs, g, o, rtol, atol, hmax, hmin, c3, job.rec, st, cell, cnt); });
+        [&] { quad_attempt<T, S, MODE, EULER>(recs, g, o, rtol, atol, hmax, hmin, c3, job.rec, st, cell, cnt); });
     if (job.work) quad_count(job.work, cnt);
 }

@@ -133,8 +133,7 @@ __device__ __forceinline__ T geo_rhs(const S *nodes, const GeoAxis &a, int c, do
         }
     } else {
         const T v[3] = {quad_get<0>(val), quad_get<1>(val), quad_get<2>(val)};
-        const T bb = fma(v[2], v[2], fma(v[0], v[0], v[1] * v[1]));
-        const T bn = sqrt(bb);
+        const T bn = sqrt(norm2<T, S, MODE>(v[0], v[1], v[2]));
         const T inv = bn > (T)1e-300 ? (T)1 / bn : (T)0;
         const T uu[3] = {v[0] * inv, v[1] * inv, v[2] * inv};
         u = val * inv;
@@ -308,7 +307,7 @@ __device__ __forceinline__ double geo_step_x(const S *nodes, const GeoAxis &a, i
         double u = val;
         if (!normalize_first<MODE>()) {
             const double v[3] = {quad_get<0>(val), quad_get<1>(val), quad_get<2>(val)};
-            const double bn = sqrt(fma(v[2], v[2], fma(v[0], v[0], v[1] * v[1])));
+            const double bn = sqrt(norm2<double, S, MODE>(v[0], v[1], v[2]));
             u = val * (bn > 1e-300 ? 1.0 / bn : 0.0);
         }
         double k = sigma * u;

@@ -262,9 +262,22 @@ __device__ __forceinline__ void stencil_sum(const S *__restrict__ nodes, const G
     }
 }
 
+// |v|^2 of a field vector interpolated in T from records of type S.  Every
+// evaluator of a call's types forms it here: the order of the sum shows in the
+// results, and they depend neither on the gather nor on the size of the call.
+// (Trilinear FP32 records stepped in FP32 begin with the first component, all
+// others with the second: what the register cache and the direct loads gave
+// when the order was the compiler's.)
+template <typename T, typename S, int MODE>
+__device__ __forceinline__ T norm2(T v0, T v1, T v2)
+{
+    constexpr bool first = std::is_same<T, float>::value && std::is_same<S, float>::value && MODE >> 1 == 0;
+    return first ? fma(v2, v2, fma(v1, v1, v0 * v0)) : fma(v2, v2, fma(v0, v0, v1 * v1));
+}
+
 // u, the physical gradient rows and |B| from the interpolated components
 // (value and grid-unit derivatives; val[3] = interpolated |B| in PAPER mode)
-template <typename T, int MODE, bool MAG>
+template <typename T, typename S, int MODE, bool MAG>
 __device__ __forceinline__ void field_finish(const double ih[3], const T val[4], const T dx[4], const T dy[4],
                                              const T dz[4], T u[3], T G[3][3], T &mag)
 {
@@ -280,8 +293,7 @@ __device__ __forceinline__ void field_finish(const double ih[3], const T val[4],
         if (MAG) mag = val[3];
     } else {
         // u = B/|B|, grad u = (I - u u^T) grad B / |B|
-        const T bb = fma(val[2], val[2], fma(val[0], val[0], val[1] * val[1]));
-        const T bn = sqrt(bb);
+        const T bn = sqrt(norm2<T, S, MODE>(val[0], val[1], val[2]));
         const T inv = bn > (T)1e-300 ? (T)1 / bn : (T)0;
         T Gb[3][3];
 #pragma unroll
@@ -324,7 +336,7 @@ __device__ __forceinline__ void field_at(const S *__restrict__ nodes, const Geom
         // |B| is the 4th component in PAPER mode; INTERP_NORMALIZE takes |interpolated B|
         constexpr int NC = (MAG && normalize_first<MODE>()) ? 4 : 3;
         stencil_sum<K, NC, T, S>(nodes, g, s0, w, dw, val, dx, dy, dz);
-        field_finish<T, MODE, MAG>(g.ih, val, dx, dy, dz, u, G, mag);
+        field_finish<T, S, MODE, MAG>(g.ih, val, dx, dy, dz, u, G, mag);
         return;
     }
     int64_t o[8];
@@ -352,7 +364,7 @@ __device__ __forceinline__ void field_at(const S *__restrict__ nodes, const Geom
     if (MAG && normalize_first<MODE>())
         val[3] = lerp_val<T>((T)n000.w, (T)n100.w, (T)n010.w, (T)n110.w, (T)n001.w, (T)n101.w, (T)n011.w,
                              (T)n111.w, t[0], t[1], t[2]);
-    field_finish<T, MODE, MAG>(g.ih, val, dx, dy, dz, u, G, mag);
+    field_finish<T, S, MODE, MAG>(g.ih, val, dx, dy, dz, u, G, mag);
 }
 
 // The interpolated direction u alone (no gradient): the same operations as
@@ -393,8 +405,7 @@ __device__ __forceinline__ void field_u(const S *__restrict__ nodes, const Geom 
 #pragma unroll
         for (int i = 0; i < 3; ++i) u[i] = val[i];
     } else {
-        const T bb = fma(val[2], val[2], fma(val[0], val[0], val[1] * val[1]));
-        const T bn = sqrt(bb);
+        const T bn = sqrt(norm2<T, S, MODE>(val[0], val[1], val[2]));
         const T inv = bn > (T)1e-300 ? (T)1 / bn : (T)0;
 #pragma unroll
         for (int i = 0; i < 3; ++i) u[i] = val[i] * inv;
@@ -535,8 +546,7 @@ __device__ __forceinline__ T rhs_cached(__amdgpu_buffer_rsrc_t rsrc, int bytes, 
             G[2][i] = dz[i] * ihz;
         }
     } else {
-        const T bb = val[0] * val[0] + val[1] * val[1] + val[2] * val[2];
-        const T bn = sqrt(bb);
+        const T bn = sqrt(norm2<T, S, MODE>(val[0], val[1], val[2]));
         const T inv = bn > (T)1e-300 ? (T)1 / bn : (T)0;
         T Gb[3][3];
 #pragma unroll
@@ -769,11 +779,7 @@ __device__ __forceinline__ T rhs_regs(__amdgpu_buffer_rsrc_t rsrc, const float4 
             G[2][i] = dz[i] * ihz;
         }
     } else {
-        // (the order of the sum that the four-lane kernel takes for the same call)
-        const T bb = std::is_same<S, float>::value
-                         ? fma(val[2], val[2], fma(val[1], val[1], val[0] * val[0]))
-                         : fma(val[2], val[2], fma(val[0], val[0], val[1] * val[1]));
-        const T bn = sqrt(bb);
+        const T bn = sqrt(norm2<T, S, MODE>(val[0], val[1], val[2]));
         const T inv = bn > (T)1e-300 ? (T)1 / bn : (T)0;
         T Gb[3][3];
 #pragma unroll
@@ -914,7 +920,7 @@ __device__ __forceinline__ void field_at_geo(const S *__restrict__ nodes, const 
     if (MAG && normalize_first<MODE>())
         val[3] = lerp_val<T>((T)n000.w, (T)n100.w, (T)n010.w, (T)n110.w, (T)n001.w, (T)n101.w, (T)n011.w,
                              (T)n111.w, t[0], t[1], t[2]);
-    field_finish<T, MODE, MAG>(ih, val, dx, dy, dz, u, G, mag);
+    field_finish<T, S, MODE, MAG>(ih, val, dx, dy, dz, u, G, mag);
 }
 
 // metric factors of eq. (2) and (8) at a physical point: (r cos theta, r, 1)
