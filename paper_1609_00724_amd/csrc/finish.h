@@ -163,8 +163,8 @@ __device__ __forceinline__ void fin_rhs(const char *recs, const FinAxis &a, int 
         const double u0 = quad_get<0>(u), u1 = quad_get<1>(u), u2 = quad_get<2>(u);
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
-            const double ug = u0 * quad_get<0>(Gb[j]) + u1 * quad_get<1>(Gb[j]) + u2 * quad_get<2>(Gb[j]);
-            G[j] = (Gb[j] - u * ug) * inv;
+            const double ug = along(u0, u1, u2, quad_get<0>(Gb[j]), quad_get<1>(Gb[j]), quad_get<2>(Gb[j]));
+            G[j] = fma(-u, ug, Gb[j]) * inv;
         }
     }
     k[0] = sigma * u;
@@ -177,7 +177,7 @@ __device__ __forceinline__ void fin_ref(const FinAxis &a, double x, int &ib, dou
 {
     const double xg = (x - a.o) * a.ih, fl = floor(fmin(fmax(xg, -1e9), 1e9));
     ib = (int)fl;
-    fb = xg - fl;
+    fb = fma(x - a.o, a.ih, -fl);
 }
 
 // the same as field_at_x forms it (the product rounded before the subtraction)

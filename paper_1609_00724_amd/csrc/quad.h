@@ -239,8 +239,8 @@ __device__ __forceinline__ T quad_rhs(const char *recs, const QuadGeom<T> &g, in
         const T Gb[3] = {dx * g.iht[0], dy * g.iht[1], dz * g.iht[2]};
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
-            const T ug = uu[0] * quad_get<0>(Gb[j]) + uu[1] * quad_get<1>(Gb[j]) + uu[2] * quad_get<2>(Gb[j]);
-            G[j] = (Gb[j] - u * ug) * inv;
+            const T ug = along(uu[0], uu[1], uu[2], quad_get<0>(Gb[j]), quad_get<1>(Gb[j]), quad_get<2>(Gb[j]));
+            G[j] = fma(-u, ug, Gb[j]) * inv;
         }
         if (NORM2) n2 = jdot(uu[0], uu[1], uu[2], uu[0], uu[1], uu[2]);
     }
@@ -296,7 +296,7 @@ __device__ __forceinline__ void quad_attempt(const char *recs, const QuadGeom<T>
         const double xg = (st.X - g.o) * g.ih;
         const double fl = floor(xg);
         ref = quad_ref<T>(g, (int)fl);
-        fb = (T)(xg - fl);
+        fb = (T)fma(st.X - g.o, g.ih, -fl);
         if (EULER || !st.have_k1) {
             const T un2 = quad_rhs<T, S, MODE, true>(recs, g, c3, ref, fb, st.D1, st.D2, st.Kx0, st.K10,
                                                              st.K20, cell);
@@ -316,7 +316,7 @@ __device__ __forceinline__ void quad_attempt(const char *recs, const QuadGeom<T>
         double Xn;
         T D1n, D2n, err = 0, fpart;
         if constexpr (EULER) {
-            Xn = st.X + (double)(hsig * st.Kx0);
+            Xn = advance(st.X, hsig, st.Kx0);
             D1n = fma(hsig, st.K10, st.D1);
             D2n = fma(hsig, st.K20, st.D2);
             fpart = ((T)Xn + D1n) + D2n;
@@ -351,7 +351,7 @@ __device__ __forceinline__ void quad_attempt(const char *recs, const QuadGeom<T>
             const T ex = ck_e(Kx[0], Kx[2], Kx[3], Kx[4], Kx[5]);
             const T e1 = ck_e(K1[0], K1[2], K1[3], K1[4], K1[5]);
             const T e2 = ck_e(K2[0], K2[2], K2[3], K2[4], K2[5]);
-            Xn = st.X + (double)(hsig * bx);
+            Xn = advance(st.X, hsig, bx);
             D1n = fma(hsig, b1, st.D1);
             D2n = fma(hsig, b2, st.D2);
             const T xo = (T)st.X, xn = (T)Xn;

@@ -140,8 +140,8 @@ __device__ __forceinline__ T geo_rhs(const S *nodes, const GeoAxis &a, int c, do
         const T Gb[3] = {dx * ihx, dy * ihy, dz * ihz};
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
-            const T ug = uu[0] * quad_get<0>(Gb[j]) + uu[1] * quad_get<1>(Gb[j]) + uu[2] * quad_get<2>(Gb[j]);
-            G[j] = (Gb[j] - u * ug) * inv;
+            const T ug = along(uu[0], uu[1], uu[2], quad_get<0>(Gb[j]), quad_get<1>(Gb[j]), quad_get<2>(Gb[j]));
+            G[j] = fma(-u, ug, Gb[j]) * inv;
         }
         if (NORM2) n2 = jdot(uu[0], uu[1], uu[2], uu[0], uu[1], uu[2]);
     }
@@ -198,7 +198,7 @@ __device__ __forceinline__ void geo_attempt(const S *nodes, const GeoAxis &a, co
             a1 = fma(c_[j], K1[j], a1);                                                                            \
             a2 = fma(c_[j], K2[j], a2);                                                                            \
         }                                                                                                          \
-        geo_rhs<T, S, MODE, false>(nodes, a, c, st.X + (double)(hs * ax), st.sigma, fma(hs, a1, st.D1),            \
+        geo_rhs<T, S, MODE, false>(nodes, a, c, advance(st.X, hs, ax), st.sigma, fma(hs, a1, st.D1),                \
                                    fma(hs, a2, st.D2), Kx[ST], K1[ST], K2[ST], cell);                              \
     }
         QSQ_GEO_STAGES(QSQ_GSTAGE)
@@ -208,7 +208,7 @@ __device__ __forceinline__ void geo_attempt(const S *nodes, const GeoAxis &a, co
                         ck_b5(K2[0], K2[2], K2[3], K2[5])};
         const T e[3] = {ck_e(Kx[0], Kx[2], Kx[3], Kx[4], Kx[5]), ck_e(K1[0], K1[2], K1[3], K1[4], K1[5]),
                         ck_e(K2[0], K2[2], K2[3], K2[4], K2[5])};
-        const double Xn = st.X + (double)(hs * b[0]);
+        const double Xn = advance(st.X, hs, b[0]);
         const T yo[3] = {(T)st.X, st.D1, st.D2};
         const T yn[3] = {(T)Xn, fma(hs, b[1], st.D1), fma(hs, b[2], st.D2)};
         T err = 0, fsum = 0;

@@ -29,6 +29,12 @@
 
 namespace qsq {
 
+// One line is computed by different kernels in different calls (one lane or
+// four, any gather, landing apart or together with Q), and has to come out the
+// same.  So the compiler fuses nothing here on its own: every fused
+// multiply-add of this file and the headers it includes is written as one.
+#pragma clang fp contract(off)
+
 // ---------------------------------------------------------------------------
 // Cash-Karp 5(4) coefficients (Cash & Karp 1990, the stepper of Sect. 3.4)
 // ---------------------------------------------------------------------------
@@ -149,24 +155,25 @@ __device__ __forceinline__ void axis_stencil(int c, T t, int n, int &s, T w[K], 
 {
     if constexpr (K == 4) {
         const T t2 = t * t, t3 = t2 * t;
-        w[0] = (T)0.5 * (-t3 + (T)2 * t2 - t);
-        w[1] = (T)0.5 * ((T)3 * t3 - (T)5 * t2 + (T)2);
-        w[2] = (T)0.5 * ((T)-3 * t3 + (T)4 * t2 + t);
-        w[3] = (T)0.5 * (t3 - t2);
-        dw[0] = (T)0.5 * ((T)-3 * t2 + (T)4 * t - (T)1);
-        dw[1] = (T)0.5 * ((T)9 * t2 - (T)10 * t);
-        dw[2] = (T)0.5 * ((T)-9 * t2 + (T)8 * t + (T)1);
-        dw[3] = (T)0.5 * ((T)3 * t2 - (T)2 * t);
+        const T a2 = (T)3 * t2, b2 = (T)9 * t2, a3 = (T)3 * t3;
+        w[0] = (T)0.5 * (fma((T)2, t2, -t3) - t);
+        w[1] = (T)0.5 * (fma((T)-5, t2, a3) + (T)2);
+        w[2] = (T)0.5 * (fma((T)4, t2, -a3) + t);
+        w[3] = (T)0.5 * fma(t, t2, -t2);
+        dw[0] = (T)0.5 * (fma((T)4, t, -a2) - (T)1);
+        dw[1] = (T)0.5 * fma((T)-10, t, b2);
+        dw[2] = (T)0.5 * (fma((T)8, t, -b2) + (T)1);
+        dw[3] = (T)0.5 * fma((T)-2, t, a2);
         s = c - 1;
     } else {
         const bool low = t < (T)0.5;
         const T u = low ? t : t - (T)1;
         w[0] = u * (u - (T)0.5);
-        w[1] = (T)1 - (T)2 * u * u;
+        w[1] = fma(-u, (T)2 * u, (T)1);
         w[2] = u * (u + (T)0.5);
-        dw[0] = (T)2 * u - (T)0.5;
+        dw[0] = fma((T)2, u, (T)-0.5);
         dw[1] = (T)-4 * u;
-        dw[2] = (T)2 * u + (T)0.5;
+        dw[2] = fma((T)2, u, (T)0.5);
         s = low ? c - 1 : c;
     }
     if (s < 0) {
@@ -179,8 +186,8 @@ __device__ __forceinline__ void axis_stencil(int c, T t, int n, int &s, T w[K], 
         }
         w[K - 1] = (T)0;
         dw[K - 1] = (T)0;
-        w[0] += (T)3 * a, w[1] -= (T)3 * a, w[2] += a;
-        dw[0] += (T)3 * da, dw[1] -= (T)3 * da, dw[2] += da;
+        w[0] = fma((T)3, a, w[0]), w[1] = fma((T)-3, a, w[1]), w[2] += a;
+        dw[0] = fma((T)3, da, dw[0]), dw[1] = fma((T)-3, da, dw[1]), dw[2] += da;
         s = 0;
     } else if (s + K - 1 > n - 1) {
         // node n folded onto nodes n-1, n-2, n-3 (weights 3, -3, 1); the
@@ -198,8 +205,8 @@ __device__ __forceinline__ void axis_stencil(int c, T t, int n, int &s, T w[K], 
             nw[k + shift] += w[k];
             ndw[k + shift] += dw[k];
         }
-        nw[0] += a, nw[1] -= (T)3 * a, nw[2] += (T)3 * a;
-        ndw[0] += da, ndw[1] -= (T)3 * da, ndw[2] += (T)3 * da;
+        nw[0] += a, nw[1] = fma((T)-3, a, nw[1]), nw[2] = fma((T)3, a, nw[2]);
+        ndw[0] += da, ndw[1] = fma((T)-3, da, ndw[1]), ndw[2] = fma((T)3, da, ndw[2]);
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             w[k] = nw[k];
@@ -262,6 +269,13 @@ __device__ __forceinline__ void stencil_sum(const S *__restrict__ nodes, const G
     }
 }
 
+// u . g, beginning with the second component
+template <typename T>
+__device__ __forceinline__ T along(T u0, T u1, T u2, T g0, T g1, T g2)
+{
+    return fma(u2, g2, fma(u0, g0, u1 * g1));
+}
+
 // |v|^2 of a field vector interpolated in T from records of type S.  Every
 // evaluator of a call's types forms it here: the order of the sum shows in the
 // results, and they depend neither on the gather nor on the size of the call.
@@ -272,7 +286,7 @@ template <typename T, typename S, int MODE>
 __device__ __forceinline__ T norm2(T v0, T v1, T v2)
 {
     constexpr bool first = std::is_same<T, float>::value && std::is_same<S, float>::value && MODE >> 1 == 0;
-    return first ? fma(v2, v2, fma(v1, v1, v0 * v0)) : fma(v2, v2, fma(v0, v0, v1 * v1));
+    return first ? fma(v2, v2, fma(v1, v1, v0 * v0)) : along(v0, v1, v2, v0, v1, v2);
 }
 
 // u, the physical gradient rows and |B| from the interpolated components
@@ -305,9 +319,9 @@ __device__ __forceinline__ void field_finish(const double ih[3], const T val[4],
         }
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
-            const T ug = u[0] * Gb[j][0] + u[1] * Gb[j][1] + u[2] * Gb[j][2];
+            const T ug = along(u[0], u[1], u[2], Gb[j][0], Gb[j][1], Gb[j][2]);
 #pragma unroll
-            for (int i = 0; i < 3; ++i) G[j][i] = (Gb[j][i] - u[i] * ug) * inv;
+            for (int i = 0; i < 3; ++i) G[j][i] = fma(-u[i], ug, Gb[j][i]) * inv;
         }
         if (MAG) mag = bn;
     }
@@ -412,8 +426,7 @@ __device__ __forceinline__ void field_u(const S *__restrict__ nodes, const Geom 
     }
 }
 
-// a0 b0 + a1 b1 + a2 b2 with the fused operations spelled out, so that the
-// rounding does not depend on how the compiler contracts the expression
+// a0 b0 + a1 b1 + a2 b2, beginning with the first component
 template <typename T>
 __device__ __forceinline__ T jdot(T a0, T a1, T a2, T b0, T b1, T b2)
 {
@@ -558,9 +571,9 @@ __device__ __forceinline__ T rhs_cached(__amdgpu_buffer_rsrc_t rsrc, int bytes, 
         }
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
-            const T ug = u[0] * Gb[j][0] + u[1] * Gb[j][1] + u[2] * Gb[j][2];
+            const T ug = along(u[0], u[1], u[2], Gb[j][0], Gb[j][1], Gb[j][2]);
 #pragma unroll
-            for (int i = 0; i < 3; ++i) G[j][i] = (Gb[j][i] - u[i] * ug) * inv;
+            for (int i = 0; i < 3; ++i) G[j][i] = fma(-u[i], ug, Gb[j][i]) * inv;
         }
     }
     return rhs_from(sigma, u, G, d1, d2, kx, k1, k2);
@@ -791,9 +804,9 @@ __device__ __forceinline__ T rhs_regs(__amdgpu_buffer_rsrc_t rsrc, const float4 
         }
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
-            const T ug = u[0] * Gb[j][0] + u[1] * Gb[j][1] + u[2] * Gb[j][2];
+            const T ug = along(u[0], u[1], u[2], Gb[j][0], Gb[j][1], Gb[j][2]);
 #pragma unroll
-            for (int i = 0; i < 3; ++i) G[j][i] = (Gb[j][i] - u[i] * ug) * inv;
+            for (int i = 0; i < 3; ++i) G[j][i] = fma(-u[i], ug, Gb[j][i]) * inv;
         }
     }
     return rhs_from(sigma, u, G, d1, d2, kx, k1, k2);
@@ -812,6 +825,10 @@ __device__ __forceinline__ T ck_e(T k0, T k2, T k3, T k4, T k5)
 {
     return fma((T)ck::e6, k5, fma((T)ck::e5, k4, fma((T)ck::e4, k3, fma((T)ck::e3, k2, (T)ck::e1 * k0))));
 }
+
+// position x moved by h k: FP64 stepping fuses, FP32 adds the rounded product
+__device__ __forceinline__ double advance(double x, float h, float k) { return x + (double)(h * k); }
+__device__ __forceinline__ double advance(double x, double h, double k) { return fma(h, k, x); }
 
 // atol + rtol max(|old|, |new|)
 template <typename T>
@@ -971,11 +988,11 @@ __device__ __forceinline__ void frame_of(const double n[3], double a[3], double 
     const double sg = copysign(1.0, n[2]);
     const double p = -1.0 / (sg + n[2]);
     const double q = n[0] * n[1] * p;
-    a[0] = 1.0 + sg * n[0] * n[0] * p;
+    a[0] = fma(sg * n[0] * n[0], p, 1.0);
     a[1] = sg * q;
     a[2] = -sg * n[0];
     b[0] = q;
-    b[1] = sg + n[1] * n[1] * p;
+    b[1] = fma(n[1] * n[1], p, sg);
     b[2] = -n[1];
 }
 
@@ -1061,7 +1078,7 @@ __global__ void __launch_bounds__(256) k_seed_pass(TraceJob job)
         } else {
             double u[3], G[3][3], mag;
             field_at_x<S, MODE, false>(nodes, g, x0, u, G, mag);
-            const double un = sqrt(u[0] * u[0] + u[1] * u[1] + u[2] * u[2]);
+            const double un = sqrt(along(u[0], u[1], u[2], u[0], u[1], u[2]));
             if (un < 1e-6) {
                 st[0] = st[1] = QSQ_END_NULL;
             } else {
@@ -1408,7 +1425,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(trace_
                 const double xg = (X[d] - g.o[d]) * g.ih[d];
                 const double fl = floor(xg);
                 ib[d] = (int)fl;
-                fb[d] = (T)(xg - fl);
+                fb[d] = (T)fma(X[d] - g.o[d], g.ih[d], -fl);
             }
             if (!EULER && !have_k1) {
                 const T un2 = rhs_step<T, S, MODE, GATHER>(nodes, rsrc, cbytes, g, ib, fb, (T)1, D1, D2, Kx[0], K1[0],
@@ -1439,7 +1456,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(trace_
                 T D1n[3], D2n[3], fsum = 0;
 #pragma unroll
                 for (int i = 0; i < 3; ++i) {
-                    Xn[i] = X[i] + (double)(hsig * Kx[0][i]);
+                    Xn[i] = advance(X[i], hsig, Kx[0][i]);
                     D1n[i] = fma(hsig, K1[0][i], D1[i]);
                     D2n[i] = fma(hsig, K2[0][i], D2[i]);
                     fsum += ((T)Xn[i] + D1n[i]) + D2n[i];
@@ -1529,7 +1546,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(trace_
                 const T ex = ck_e(Kx[0][i], Kx[2][i], Kx[3][i], Kx[4][i], Kx[5][i]);
                 const T e1 = ck_e(K1[0][i], K1[2][i], K1[3][i], K1[4][i], K1[5][i]);
                 const T e2 = ck_e(K2[0][i], K2[2][i], K2[3][i], K2[4][i], K2[5][i]);
-                Xn[i] = X[i] + (double)(hsig * bx);
+                Xn[i] = advance(X[i], hsig, bx);
                 D1n[i] = fma(hsig, b1, D1[i]);
                 D2n[i] = fma(hsig, b2, D2[i]);
                 const T xo = (T)X[i], xn = (T)Xn[i];
@@ -1615,7 +1632,7 @@ __device__ void ck54_fp64(const S *__restrict__ nodes, const Geom &g, double sig
         const double xg = (y[d] - g.o[d]) * g.ih[d];
         const double fl = floor(fmin(fmax(xg, -1e9), 1e9));
         ib[d] = (int)fl;
-        fb[d] = xg - fl;
+        fb[d] = fma(y[d] - g.o[d], g.ih[d], -fl);
     }
 #pragma unroll
     for (int st = 0; st < 6; ++st) {
@@ -1668,7 +1685,7 @@ __device__ void ck54_pos(const S *__restrict__ nodes, const Geom &g, double sigm
         const double xg = (y[d] - g.o[d]) * g.ih[d];
         const double fl = floor(fmin(fmax(xg, -1e9), 1e9));
         ib[d] = (int)fl;
-        fb[d] = xg - fl;
+        fb[d] = fma(y[d] - g.o[d], g.ih[d], -fl);
     }
 #pragma unroll
     for (int st = 0; st < 6; ++st) {
@@ -1715,10 +1732,7 @@ __device__ __forceinline__ double landing_guess(double g0, double s0, double g1,
     return (h > 0.0 && h < hs) ? h : sec;
 }
 
-// next trial length of the regula falsi between (a, ga < 0) and (b, gb > 0).
-// (Here and in the Q assembly the fused operations are spelled out: the
-// one-lane and the four-lane kernels of the same step then give the same bits,
-// however the compiler would have fused each of them.)
+// next trial length of the regula falsi between (a, ga < 0) and (b, gb > 0)
 __device__ __forceinline__ double landing_secant(double a, double ga, double b, double gb)
 {
     return fma(a, gb, -(b * ga)) / (gb - ga);

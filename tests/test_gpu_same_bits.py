@@ -48,3 +48,49 @@ def test_gathers_and_batches(charges, storage, mode, stepper):  # noqa: F811
     ref = runs["gather 1"]
     assert ((ref["status"] & 0xFF) <= 5).sum() > 1500
     assert [k for k, r in runs.items() if not _equal(r, ref)] == []
+
+
+@pytest.mark.parametrize("stepper", ["ck54", "euler"])
+@pytest.mark.parametrize("mode", ["paper", "interp_normalize"])
+@pytest.mark.parametrize("storage,order", [("f32", "linear"), ("bf16", "linear"), ("f64", "linear"), ("f32", "quadratic"),
+                                           ("f64", "quadratic"), ("f32", "cubic"), ("f64", "cubic")])
+def test_ends_by_call_size(charges, storage, order, mode, stepper):  # noqa: F811
+    """Landing and Q of a small call (four lanes a half-line) against the same
+    seeds in a call past 2^18 seeds (one lane, an assembly of its own)."""
+    import torch
+
+    import paper_1609_00724_amd as q
+    b, origin, spacing = charges
+    dt = np.float64 if storage == "f64" else np.float32
+    # 20 nodes along z: folded stencils at both faces and plain ones between
+    b = [torch.from_numpy(np.ascontiguousarray(c[:20].astype(dt))).cuda() for c in b]
+    f = q.field_init(*b, origin, spacing, storage=storage, mode=mode, order=order)
+    h, n = min(spacing), 3000
+    s = _seeds(n, 5)
+    s[:, 2] *= 19 / 26   # into the box, the bottom and top faces kept
+    pad = torch.tensor([[2.0, 0.0, 0.0]], dtype=torch.float64, device="cuda").expand((1 << 18) + 1, 3)   # outside: no work
+    kw = dict(rtol=1e-4, atol=1e-4, h_init=0.2 * h, h_max=2 * h, stepper=stepper, want_steps=True)
+    a = q.trace(f, s, **kw)
+    r = q.trace(f, torch.cat([s, pad]), **kw)
+    torch.cuda.synchronize()
+    r = {k: v[..., :n] for k, v in r.items()}
+    assert ((a["status"] & 0xFF) <= 5).sum() > 2000
+    assert [k for k in a if not torch.equal(a[k].nan_to_num(-7.0), r[k].nan_to_num(-7.0))] == []
+
+
+@pytest.mark.parametrize("storage,mode", [("f32", "paper"), ("bf16", "interp_normalize"), ("f64", "interp_normalize")])
+def test_batch_ends_by_call_size(charges, storage, mode):  # noqa: F811
+    """The same for a batch, whose larger calls begin past 2^20 seeds."""
+    import torch
+
+    from paper_1609_00724_amd.api import TraceBatchPlan, make_opts
+    f, g = _field(charges, storage, mode), _field([[np.ascontiguousarray(c[:20]) for c in charges[0]], *charges[1:]], storage, mode)
+    h, n = min(charges[2]), 2000
+    s, t = _seeds(n, 6), _seeds(n, 7)
+    t[:, 2] *= 19 / 26
+    pad = torch.tensor([[2.0, 0.0, 0.0]], dtype=torch.float64, device="cuda").expand((1 << 20) + 1, 3)
+    o = make_opts(1e-4, 1e-4, h_init=0.2 * h, h_max=2 * h)
+    a = TraceBatchPlan([(f, s), (g, t)], o, want_steps=True).run()
+    b = TraceBatchPlan([(f, s), (g, t), (f, pad)], o, want_steps=True).run()
+    torch.cuda.synchronize()
+    assert [(i, k) for i in range(2) for k in a[i] if not torch.equal(a[i][k].nan_to_num(-7.0), b[i][k].nan_to_num(-7.0))] == []
