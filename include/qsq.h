@@ -182,7 +182,8 @@ typedef struct qsq_trace_opts {
 
 /* Launch-shape word of qsq_trace_opts.launch (what an autotuner varies):
  *   lanes  resident-lane target of the persistent stepping launch, in units of
- *          256 lanes per compute unit, 1..15 (0: 8)
+ *          256 lanes per compute unit, 1..15 (0: automatic, by the types, the
+ *          field's size and the number of half-lines; at most 8)
  *   wg     workgroup size code: 0 = 256, 1 = 64, 2 = 128 lanes
  *   gather 0 = automatic: work lists short enough that the longest line sets
  *          the time (the list's length is compared on the device) are stepped

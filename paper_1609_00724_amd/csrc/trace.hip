@@ -25,6 +25,7 @@
 #include <mutex>
 #include <type_traits>
 
+#include "launch_rules.h"
 #include "qsq_internal.h"
 
 namespace qsq {
@@ -2307,6 +2308,22 @@ constexpr int64_t kFinishMax = (int64_t)1 << 18, kFinishMaxBatch = (int64_t)1 <<
 // record bytes that 32-bit offsets reach, with room for the neighbours' offsets
 constexpr uint64_t kCacheLimit = ((uint64_t)1 << 31) - ((uint64_t)1 << 26);
 
+// what the launch rules look at
+static StepCall step_call(const TraceJob &job, bool step64, bool batch, int64_t n_max)
+{
+    const Geom &g = job.g;
+    StepCall c{};
+    c.step64 = step64;
+    c.euler = job.o.stepper == QSQ_STEPPER_EULER;
+    c.batch = batch;
+    c.record = job.storage == QSQ_F64 ? 32 : job.storage == QSQ_F32 ? 16 : 8;
+    c.field = (uint64_t)g.n[0] * (uint64_t)g.n[1] * (uint64_t)g.n[2] * (uint64_t)c.record;
+    c.spread = job.spatial_bits > 0;
+    c.halves = 2 * n_max;
+    c.cap = (c.euler ? job.o.h_init : job.o.h_max) * fmax(fmax(g.ih[0], g.ih[1]), g.ih[2]);
+    return c;
+}
+
 // the stepping kernel of a gather variant for the job's stepper
 template <typename T, typename S, int MODE, int GATHER, bool BATCH>
 static const void *trace_kernel(bool euler)
@@ -2343,11 +2360,12 @@ static hipError_t launch_typed(const TraceJob &job, hipStream_t st)
     // target per CU, capped by what the kernel's registers and LDS let stay
     // resident, so that every workgroup of the persistent launch runs from the
     // start (the first item of each lane is its global index)
-    const int lanes = (job.o.launch & 15) ? (job.o.launch & 15) : 8;
+    int lanes = job.o.launch & 15;
     const int wg_code = (job.o.launch >> 4) & 3, gather = (job.o.launch >> 6) & 7;
     const int wg = wg_code == 1 ? 64 : wg_code == 2 ? 128 : 256;
     const void *kern;
     size_t lds = 0;
+    StepLoads loads = kLoadsDirect;
     constexpr bool cacheable = sizeof(T) == 4 && interp_order<MODE>() == 1 &&
                                (std::is_same<S, float>::value || std::is_same<S, Bf16>::value);
     if constexpr (cacheable && !BATCH) {
@@ -2366,17 +2384,22 @@ static hipError_t launch_typed(const TraceJob &job, hipStream_t st)
                 dirs_kern = trace_kernel<T, S, MODE, kGatherDirs, false>(euler);
         if (dirs_kern) {
             kern = dirs_kern;
+            loads = kLoadsDirs;
             lds = CellDirs::kPlanes * wg * sizeof(float4);
         } else if (gather == 5 && job.bricks && brick_bytes < limit) {
             kern = trace_kernel<T, S, MODE, kGatherBricks, false>(euler);
             lds = (CellNodes::kPlanes + 2) * wg * sizeof(float4);
+            loads = kLoadsRegs;
         } else if (gather == 4 && job.cells) {
             kern = trace_kernel<T, S, MODE, kGatherCells, false>(euler);
+            loads = kLoadsCells;
         } else if ((gather == 3 || gather == 5 || gather == 6 || gather == 0) && fits) {
             kern = trace_kernel<T, S, MODE, kGatherRegs, false>(euler);
             lds = CellNodes::kPlanes * wg * sizeof(float4);
+            loads = kLoadsRegs;
         } else if (gather == 2 && fits) {
             kern = trace_kernel<T, S, MODE, kGatherLds, false>(euler);
+            loads = kLoadsLds;
             lds = kCachePlanes * wg * sizeof(float4);
         } else {
             kern = trace_kernel<T, S, MODE, kGatherDirect, false>(euler);
@@ -2384,6 +2407,11 @@ static hipError_t launch_typed(const TraceJob &job, hipStream_t st)
     } else {
         (void)gather;
         kern = trace_kernel<T, S, MODE, kGatherDirect, BATCH>(euler);
+    }
+    if (lanes == 0) {
+        // (a unit of 256 lanes a compute unit is one wave per SIMD)
+        lanes = interp_order<MODE>() == 1 ? auto_waves(step_call(job, sizeof(T) == 8, BATCH, n_max), loads) : 0;
+        if (lanes == 0) lanes = 8;
     }
     const int64_t resident = (int64_t)cus * resident_blocks(kern, wg, lds);
     int64_t cap_blocks = (int64_t)cus * lanes * (256 / wg);

@@ -1,0 +1,67 @@
+"""The rules of the automatic launch word (csrc/launch_rules.h), on the CPU: the
+calls that earlier rules made slower, each with its neighbours on the other side
+of the line."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PROGRAM = r"""
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include "launch_rules.h"
+using namespace qsq;
+// argv: question, then key=value pairs
+int main(int argc, char **argv)
+{
+    StepCall c{};
+    int loads = kLoadsDirect;
+    for (int i = 2; i < argc; ++i) {
+        char *v = strchr(argv[i], '=');
+        *v++ = 0;
+        const char *k = argv[i];
+        const double x = atof(v);
+        if (!strcmp(k, "step64")) c.step64 = x != 0;
+        if (!strcmp(k, "euler")) c.euler = x != 0;
+        if (!strcmp(k, "batch")) c.batch = x != 0;
+        if (!strcmp(k, "record")) c.record = (int)x;
+        if (!strcmp(k, "field")) c.field = (uint64_t)x;
+        if (!strcmp(k, "spread")) c.spread = x != 0;
+        if (!strcmp(k, "halves")) c.halves = (int64_t)x;
+        if (!strcmp(k, "cap")) c.cap = x;
+        if (!strcmp(k, "loads")) loads = (int)x;
+    }
+    if (!strcmp(argv[1], "waves")) printf("%d\n", auto_waves(c, (StepLoads)loads));
+}
+"""
+
+DIRECT, CELLS, LDS, REGS, DIRS = range(5)
+
+
+@pytest.fixture(scope="module")
+def ask(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+    (d / "p.cpp").write_text(PROGRAM)
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_1609_00724_amd", "csrc"),
+                    "-o", d / "p", d / "p.cpp"], check=True)
+
+    def run(question, n=(128, 128, 64), seeds=250000, **kw):
+        kw = dict(dict(record=16, spread=1, cap=1.0, halves=2 * seeds), **kw)
+        kw["field"] = n[0] * n[1] * n[2] * kw["record"]
+        out = subprocess.run([d / "p", question, *(f"{k}={v}" for k, v in kw.items())], check=True, capture_output=True)
+        return int(out.stdout)
+    return run
+
+
+def test_fp64_stepping_keeps_one_wave_where_two_overflow_the_caches(ask):
+    # 224 x 224 x 112 FP32 records, FP64 stepping: 6.6 ms with one, 11.0 with two
+    assert ask("waves", (224, 224, 112), step64=1) == 1
+    assert ask("waves", (224, 224, 112), 10**6, step64=1) == 1
+    assert ask("waves", (64, 64, 32), 140000, step64=1) == 1     # two lines a lane: uneven ends
+    assert ask("waves", (64, 64, 32), 500000, step64=1) == 0     # the caches hold it
+    assert ask("waves", (224, 224, 112), 500000, step64=1, spread=0) == 0
+    assert ask("waves", (224, 224, 112), step64=1, euler=1) == 0
+    assert ask("waves", (224, 224, 112), step64=1, batch=1) == 0
