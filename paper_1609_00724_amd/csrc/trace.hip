@@ -1200,10 +1200,14 @@ static __global__ void k_land_compact(TraceJob job)
 // a lane's record per cycle 81 % of the time.  The other gathers are bound by
 // the caches behind it, which three waves' cells overflow: direction records
 // 43.8 ms with two waves, 46.2 with three; batched fields 3.1 against 3.6.
-template <typename T, int GATHER, bool EULER>
+// BF16 node records have the widening of each value on top, and 168 registers
+// spill (500 000 lines of 224 x 224 x 112 cells, 4-cell cap: 3.27 ms with three
+// waves, 2.64 with two).
+template <typename T, typename S, int GATHER, bool EULER>
 constexpr int trace_waves(int most)
 {
-    const bool three = EULER || GATHER == kGatherRegs || GATHER == kGatherBricks;
+    const bool three =
+        EULER || (GATHER == kGatherRegs && !std::is_same<S, Bf16>::value) || GATHER == kGatherBricks;
     return most ? (sizeof(T) == 4 && !three ? 2 : 8) : three ? 3 : 1;
 }
 
@@ -1223,7 +1227,7 @@ __device__ __forceinline__ double uniform(double v) { return v; }
 
 // (the Euler variants fit 3 waves per SIMD: one evaluation's state per step)
 template <typename T, typename S, int MODE, int GATHER, bool BATCH, bool EULER = false>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(trace_waves<T, GATHER, EULER>(0), trace_waves<T, GATHER, EULER>(1)))) k_trace(TraceJob job)
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(trace_waves<T, S, GATHER, EULER>(0), trace_waves<T, S, GATHER, EULER>(1)))) k_trace(TraceJob job)
 {
     static_assert(GATHER == kGatherDirect || (!BATCH && sizeof(T) == 4),
                   "cell caches: one field per launch, FP32 corner values");
@@ -1243,6 +1247,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(trace_
     const int lane = (int)(threadIdx.x & 63);
     const int64_t total = *job.rec.n_work;
     if (total <= job.quad_max) return;   // the four-lane kernel's call, or nothing to do
+    if (total > job.few_from && (int)blockIdx.x >= job.few) return;
 
     // lane state
     double X[3] = {0, 0, 0}, s = 0.0;
@@ -2191,6 +2196,7 @@ static __global__ void k_part_counters(TraceJob job, int blocks, int wg, int npa
         if (p == 0) job.counter[kPartCounter] = (unsigned long long)qblocks * (kQuadWg / 64) * 16;
         return;
     }
+    if (total > job.few_from) blocks = job.few;
     const int64_t nb = p < blocks ? (blocks - p + nparts - 1) / nparts : 0;
     job.counter[kPartCounter + p] = (unsigned long long)(total * p / nparts + nb * wg);
 }
@@ -2318,7 +2324,6 @@ static StepCall step_call(const TraceJob &job, bool step64, bool batch, int64_t 
     c.batch = batch;
     c.record = job.storage == QSQ_F64 ? 32 : job.storage == QSQ_F32 ? 16 : 8;
     c.field = (uint64_t)g.n[0] * (uint64_t)g.n[1] * (uint64_t)g.n[2] * (uint64_t)c.record;
-    c.spread = job.spatial_bits > 0;
     c.halves = 2 * n_max;
     c.cap = (c.euler ? job.o.h_init : job.o.h_max) * fmax(fmax(g.ih[0], g.ih[1]), g.ih[2]);
     return c;
@@ -2389,7 +2394,7 @@ static hipError_t launch_typed(const TraceJob &job, hipStream_t st)
         } else if (gather == 5 && job.bricks && brick_bytes < limit) {
             kern = trace_kernel<T, S, MODE, kGatherBricks, false>(euler);
             lds = (CellNodes::kPlanes + 2) * wg * sizeof(float4);
-            loads = kLoadsRegs;
+            loads = kLoadsBricks;
         } else if (gather == 4 && job.cells) {
             kern = trace_kernel<T, S, MODE, kGatherCells, false>(euler);
             loads = kLoadsCells;
@@ -2408,16 +2413,24 @@ static hipError_t launch_typed(const TraceJob &job, hipStream_t st)
         (void)gather;
         kern = trace_kernel<T, S, MODE, kGatherDirect, BATCH>(euler);
     }
-    if (lanes == 0) {
-        // (a unit of 256 lanes a compute unit is one wave per SIMD)
-        lanes = interp_order<MODE>() == 1 ? auto_waves(step_call(job, sizeof(T) == 8, BATCH, n_max), loads) : 0;
-        if (lanes == 0) lanes = 8;
-    }
+    // workgroups that stay resident; of a trace's list that turns out to be
+    // spread (only the device knows its length), the first `few`
     const int64_t resident = (int64_t)cus * resident_blocks(kern, wg, lds);
-    int64_t cap_blocks = (int64_t)cus * lanes * (256 / wg);
-    if (cap_blocks > resident) cap_blocks = resident;
+    auto cap_blocks = [&](bool spread) {
+        int units = lanes;   // (256 lanes a compute unit: one wave per SIMD)
+        if (units == 0 && interp_order<MODE>() == 1) {
+            StepCall c = step_call(job, sizeof(T) == 8, BATCH, n_max);
+            c.spread = spread;
+            units = auto_waves(c, loads);
+        }
+        const int64_t b = (int64_t)cus * (units ? units : 8) * (256 / wg);
+        return b < resident ? b : resident;
+    };
     const int64_t want = (2 * n_max + wg - 1) / wg;
-    const int blocks = (int)(want < cap_blocks ? want : cap_blocks);
+    const int blocks = (int)(want < cap_blocks(false) ? want : cap_blocks(false));
+    TraceJob js = job;
+    js.few = job.spatial_bits > 0 && cap_blocks(true) < blocks ? (int)cap_blocks(true) : blocks;
+    js.few_from = spread_halves(n_max);
     const int nparts = (job.o.launch >> 9) & 1 ? kParts : 1;
     // few half-lines: four lanes each.  The count is known on the device
     // only, so where it may fall on either side both kernels are launched and
@@ -2434,11 +2447,11 @@ static hipError_t launch_typed(const TraceJob &job, hipStream_t st)
             qblocks = (int)(need < cus ? cus : need < full ? need : full);
         }
     }
-    hipLaunchKernelGGL(k_part_counters, dim3(1), dim3(64), 0, st, job, blocks, wg, nparts, qblocks);
+    hipLaunchKernelGGL(k_part_counters, dim3(1), dim3(64), 0, st, js, blocks, wg, nparts, qblocks);
     const bool prof = profiling();
     void *tok = nullptr;
     if (prof) prof_begin(kProfStep, st, &tok);
-    void *args[] = {const_cast<TraceJob *>(&job)};
+    void *args[] = {&js};
     hipError_t le = hipSuccess;
     if (quad) le = hipLaunchKernel(quad, dim3(qblocks), dim3(kQuadWg), args, 0, st);
     if (le == hipSuccess && (!quad || 2 * n_max > job.quad_max))

@@ -94,3 +94,34 @@ def test_batch_ends_by_call_size(charges, storage, mode):  # noqa: F811
     b = TraceBatchPlan([(f, s), (g, t), (f, pad)], o, want_steps=True).run()
     torch.cuda.synchronize()
     assert [(i, k) for i in range(2) for k in a[i] if not torch.equal(a[i][k].nan_to_num(-7.0), b[i][k].nan_to_num(-7.0))] == []
+
+
+@pytest.mark.parametrize("step", ["f32", "f64"])
+@pytest.mark.parametrize("parts", [False, True])
+def test_spread_lists_keep_to_fewer_workgroups(step, parts):
+    """A list that the device finds spread leaves the last workgroups of the
+    launch unused: every line is still traced, once, with the same result, and
+    so is each of a list that is not (seeds on the bottom face)."""
+    import torch
+
+    import paper_1609_00724_amd as q
+    from paper_1609_00724_amd import _abi as A
+    from paper_1609_00724_amd.api import TracePlan, make_opts
+    n, seeds = (121, 121, 61) if step == "f64" else (97, 81, 41), 290000   # above the rules' lines (8 and 4 MB; 2^19 half-lines)
+    b = synth.sample_charges(synth.point_charges(7, 4), n, dtype=np.float32)
+    f = q.field_init(*(torch.from_numpy(c).cuda() for c in b), *synth.grid_geometry(n))
+    h = min(f.spacing)
+    gather = A.GATHER_REGS if step == "f32" else A.GATHER_DIRECT
+    for bottom in (False, True):
+        s = synth.random_seeds(3, seeds)
+        if bottom:
+            s[:, 2] = 0.0
+        soa = torch.from_numpy(np.ascontiguousarray(s.T)).cuda()
+        r = []
+        for lanes in (0, 1):
+            plan = TracePlan(seeds, soa.device, want_steps=True, want_work=True)
+            r.append(plan.run(f, soa, make_opts(1e-2, 1e-2, h_init=h, h_max=8 * h, step_dtype=step,
+                                                launch=A.launch_word(lanes, 256, gather, parts=parts))))
+        torch.cuda.synchronize()
+        assert _equal(*r)
+        assert int(r[0]["work"][2]) > (1.5 if not bottom else 0.5) * seeds
