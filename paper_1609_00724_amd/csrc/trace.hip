@@ -1199,7 +1199,12 @@ static __global__ void k_land_compact(TraceJob job)
 // pass over a 384 x 384 x 256 rope from brick records 89.4 -> 82.6 ms, the L1 taking
 // a lane's record per cycle 81 % of the time.  The other gathers are bound by
 // the caches behind it, which three waves' cells overflow: direction records
-// 43.8 ms with two waves, 46.2 with three; batched fields 3.1 against 3.6.
+// 43.8 ms with two waves, 46.2 with three; batched fields 3.1 against 3.6; direct
+// loads of one field, 500 000 half-lines of 224 x 224 x 112 cells at a 1-cell cap,
+// FP32 records 9.4 against 10.9, FP64 15.8 against 20.7, BF16 6.6 against 9.6.  Cell
+// records (contiguous, no line shared with the next cell's) take all three that
+// fit: FP32 5.7 with two and 6.0 with three there, but over 128 x 128 x 64 cells
+// 200 000 half-lines 1.78 against 1.52, BF16 1.43 against 1.32.
 // BF16 node records have the widening of each value on top, and 168 registers
 // spill (500 000 lines of 224 x 224 x 112 cells, 4-cell cap: 3.27 ms with three
 // waves, 2.64 with two).
@@ -1208,7 +1213,8 @@ constexpr int trace_waves(int most)
 {
     const bool three =
         EULER || (GATHER == kGatherRegs && !std::is_same<S, Bf16>::value) || GATHER == kGatherBricks;
-    return most ? (sizeof(T) == 4 && !three ? 2 : 8) : three ? 3 : 1;
+    const bool any = sizeof(T) == 8 || three || GATHER == kGatherCells;
+    return most ? (any ? 8 : 2) : three ? 3 : 1;
 }
 
 // values formed here, not where they are used last
