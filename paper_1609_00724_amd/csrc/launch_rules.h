@@ -52,4 +52,40 @@ inline int auto_waves(const StepCall &c, StepLoads loads)
 // a list of more half-lines than this, of n seeds, is spread
 inline int64_t spread_halves(int64_t n) { return n + n / 2; }
 
+// Longest work list (half-lines) that is stepped with four lanes a line; edge: the
+// box's longest edge in longest steps.  A list that fits the grid lasts as long
+// as its longest line, and four lanes a line shorten that chain: 60 000
+// half-lines of 192 x 192 x 96 cells at a 1-cell cap take 0.91 ms against 1.67 (4
+// cells: 0.55 against 0.91), 240 000 1.98 against 2.55.  A longer list is bound by
+// VALU issue, where four lanes a line cost 1.7 times the instructions and the
+// refills weigh more the shorter the lines: 520 000 half-lines 3.36 against 3.54
+// ms; 64^2 x 32 cells at 8 cells a step 128 000 0.42 against 0.40, 512 000 1.02
+// against 0.87.  So lines of 32 steps or more across the box's longest edge go
+// four lanes each up to 2^19, shorter ones up to 2^16.  (FP32 stepping over BF16
+// records, 64^2 x 32 cells at 1 cell, 500 000: 1.60 against 1.76; over FP64 records,
+// which one lane loads directly, 2.00 against 2.86.)  FP64 stepping keeps half as
+// many waves resident and a batch reloads its grid with every line: up to 2^17
+// (FP64, 128^2 x 64 cells at 1 cell: 128 000 half-lines 1.53 against 1.74 ms, 256 000
+// 2.45 against 2.34).
+//   An Euler step has one evaluation, and one lane's does little beside it.  While
+// the caches hold a field of FP32 or BF16 records, lists of up to 2^17 gain (128^2
+// x 64 cells, FP32 records: 64 000 half-lines 0.77 against 1.25 ms, 128 000 1.21
+// against 1.30, 256 000 1.55 against 1.47), of FP64 stepping up to 2^16 (64 000 0.89
+// against 1.16, 128 000 1.37 against 1.32); over 90 MB of them the adaptive
+// steps' lists do (256 000 2.76 ms both ways, 500 000 4.16 against 4.74, FP64 stepping
+// 128 000 2.33 against 3.03), and so over FP64 records of any size (64^2 x 32 cells, 500
+// 000: 1.44 against 2.14; FP64 stepping 128 000 0.76 against 0.79) and in a batch (12
+// fields, 89 000 seeds, FP64 stepping 1.13 against 1.46).
+//   Quadratic and cubic stencils have 27 and 64 records: loading a row of them
+// across the quad beats one lane's loads at any length (cubic, 4 cells a step:
+// 4000 half-lines 1.5 against 2.5 ms, 10^6 13.8 against 15.3; FP64 stepping 1.7 to
+// 2.7 times).
+inline int64_t quad_list(const StepCall &c, double edge, int order)
+{
+    if (order > 1) return (int64_t)1 << 30;
+    if (!(edge >= 32.0)) return (int64_t)1 << 16;
+    if (c.euler && !c.batch && c.record < 32 && c.field <= (uint64_t)64 << 20) return (int64_t)1 << (c.step64 ? 16 : 17);
+    return (int64_t)1 << (c.step64 || c.batch ? 17 : 19);
+}
+
 }  // namespace qsq

@@ -2621,35 +2621,16 @@ static bool quad_addressable(const Geom &g, int storage)
     return xy < ((uint64_t)1 << 23) && (uint64_t)g.n[2] < ((uint64_t)1 << 23) && xy * (uint64_t)g.n[2] * rec < kCacheLimit;
 }
 
-// Largest work list that the four-lane kernel takes under an automatic gather
-// (0: none; a named gather always gets the one-lane kernel).  A list that fits
-// the grid lasts as long as its longest line, and four lanes a line shorten
-// that chain: 60 000 half-lines of 192 x 192 x 96 cells at a 1-cell cap take
-// 0.91 ms against 1.67 (4 cells: 0.55 against 0.91), 240 000 1.98 against 2.55.
-// A longer list is bound by VALU issue, where four lanes a line cost 1.7 times
-// the instructions and the refills weigh more the shorter the lines: 520 000
-// half-lines 3.36 against 3.54 ms; 64^2 x 32 cells at 8 cells a step 128 000
-// 0.42 against 0.40, 512 000 1.02 against 0.87.  So lines of 32 steps or more
-// across the box's longest edge go four lanes each up to 2^19, shorter ones up
-// to 2^16.  FP64 stepping keeps half as many waves resident and a batch
-// reloads its grid with every line: up to 2^17 (FP64, 128^2 x 64 cells at 1
-// cell: 128 000 half-lines 1.53 against 1.74 ms, 256 000 2.45 against 2.34).
-static int64_t quad_limit(const Geom &g, double h_max, int storage, bool f32, bool batch, int order)
+// largest work list that the four-lane kernel takes under an automatic gather
+// (0: none; a named gather always gets the one-lane kernel)
+static int64_t quad_limit(const TraceJob &job, const Geom &g, double h_init, double h_max, bool step64, bool batch, int order)
 {
-    if (!quad_addressable(g, storage)) return 0;
-    // 27 and 64 records a stencil: loading a row of them across the quad beats
-    // one lane's loads at any length (cubic, 4 cells a step: 4000 half-lines
-    // 1.5 against 2.5 ms, 10^6 13.8 against 15.3; FP64 stepping 1.7 to 2.7 times)
-    if (order > 1) return (int64_t)1 << 30;
+    if (!quad_addressable(g, job.storage)) return 0;
+    TraceJob j = job;
+    j.g = g;
+    const StepCall c = step_call(j, step64, batch, 0);
     const double edge = fmax(fmax(g.hi[0] - g.lo[0], g.hi[1] - g.lo[1]), g.hi[2] - g.lo[2]);
-    if (!(edge >= 32.0 * h_max)) return (int64_t)1 << 16;
-    return (int64_t)1 << (f32 && !batch ? 19 : 17);
-}
-
-// longest step of a line
-static double step_cap(const StepOpts &o, double h_init, double h_max)
-{
-    return o.stepper == QSQ_STEPPER_EULER ? h_init : h_max;
+    return quad_list(c, edge / (c.euler ? h_init : h_max), order);
 }
 
 hipError_t launch_trace(const TraceJob &job, int step_dtype, hipStream_t st)
@@ -2659,8 +2640,7 @@ hipError_t launch_trace(const TraceJob &job, int step_dtype, hipStream_t st)
     j.quad_ok = quad_addressable(job.g, job.storage);
     j.quad_max = 0;
     if (((job.o.launch >> 6) & 7) == 0 && job.mode < 8)
-        j.quad_max = quad_limit(job.g, step_cap(job.o, job.o.h_init, job.o.h_max), job.storage, step_dtype == QSQ_F32, false,
-                                ((job.mode >> 1) & 3) + 1);
+        j.quad_max = quad_limit(job, job.g, job.o.h_init, job.o.h_max, step_dtype == QSQ_F64, false, ((job.mode >> 1) & 3) + 1);
     return dispatch<false>(j, step_dtype, st);
 }
 
@@ -2697,7 +2677,7 @@ hipError_t launch_trace_batch(const TraceJob &job, const SetDesc *host_sets, int
         j.quad_max = (int64_t)1 << 30;
         for (int k = 0; k < nsets; ++k) {
             const SetDesc &d = host_sets[k];
-            const int64_t q = quad_limit(d.g, step_cap(job.o, d.h_init, d.h_max), job.storage, step_dtype == QSQ_F32, true, 1);
+            const int64_t q = quad_limit(job, d.g, d.h_init, d.h_max, step_dtype == QSQ_F64, true, 1);
             if (q < j.quad_max) j.quad_max = q;
         }
     }
