@@ -49,6 +49,22 @@ inline int auto_waves(const StepCall &c, StepLoads loads)
     return 0;
 }
 
+// Largest call, in seeds, whose ends k_finish takes; a larger one is landed by
+// one lane per half-line over a compacted list and assembled in a kernel of its
+// own.  k_finish replaces eight launches, and its chain is a third as long: 2000
+// seeds at 8 cells a step 260 -> 203 us, 200 000 592 -> 530 us; over the 1.3 M seeds of
+// a 1024^2 map, where FP64 issue is the bound and four lanes cost more of it, it
+// takes 0.84 ms against 0.53.  A batch reloads a grid per seed in every kernel: 570
+// 000 seeds 0.67 against 0.73 ms, 1.2 M 0.83 against 0.90.  A trilinear Euler step is
+// landed without a root find, and the separate kernels overtake sooner: landing and
+// Q of 60 000 random seeds 31 against 39 us, 131 072 58 and 52, 200 000 85 and 74; in a
+// batch 109 000 43 and 47, 217 000 75 and 69.
+inline int64_t finish_seeds(const StepCall &c, int order)
+{
+    if (c.euler && order == 1) return (int64_t)1 << 17;
+    return (int64_t)1 << (c.batch ? 20 : 18);
+}
+
 // a list of more half-lines than this, of n seeds, is spread
 inline int64_t spread_halves(int64_t n) { return n + n / 2; }
 

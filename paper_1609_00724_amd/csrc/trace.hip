@@ -2308,15 +2308,6 @@ static int resident_blocks(const void *kern, int wg, size_t lds)
     return n;
 }
 
-// Largest call whose ends k_finish takes, one field and batched; a larger one
-// is landed by one lane per half-line over a compacted list and assembled in a
-// kernel of its own.  k_finish replaces eight launches, and its chain is a third
-// as long: 2000 seeds at 8 cells a step 260 -> 203 us, 200 000 592 -> 530 us;
-// over the 1.3 M seeds of a 1024^2 map, where FP64 issue is the bound and four
-// lanes cost more of it, it takes 0.84 ms against 0.53.  A batch reloads a
-// grid per seed in every kernel: 570 000 seeds 0.67 against 0.73 ms.
-constexpr int64_t kFinishMax = (int64_t)1 << 18, kFinishMaxBatch = (int64_t)1 << 20;
-
 // record bytes that 32-bit offsets reach, with room for the neighbours' offsets
 constexpr uint64_t kCacheLimit = ((uint64_t)1 << 31) - ((uint64_t)1 << 26);
 
@@ -2467,7 +2458,7 @@ static hipError_t launch_typed(const TraceJob &job, hipStream_t st)
     {
         // (the higher orders' stencils take 32-bit byte offsets; the launch
         // word has no say, so that it never changes a result)
-        if ((interp_order<MODE>() == 1 || job.quad_ok) && n_max <= (BATCH ? kFinishMaxBatch : kFinishMax)) {
+        if ((interp_order<MODE>() == 1 || job.quad_ok) && n_max <= finish_seeds(step_call(job, sizeof(T) == 8, BATCH, n_max), interp_order<MODE>())) {
             const int64_t fb = (4 * n_max + 255) / 256;
             const int fblocks = (int)(fb < (int64_t)cus * 32 ? fb : (int64_t)cus * 32);
             if (prof) prof_begin(kProfLand, st, &tok);
