@@ -138,37 +138,49 @@ __global__ void __launch_bounds__(256) k_brick_records(const R *__restrict__ nod
 // Direction records: for each cell (x fastest) the direction part (3 FP32
 // values) of its 8 corner records in the order a + 2b + 4c of corner
 // (i+a, j+b, k+c), 96 contiguous bytes, so that a cell's corners come in six
-// 16-byte loads from at most two 128-byte lines.  One workgroup per 256 cells
-// of a row: the four node rows go through LDS, and each thread writes 16
-// consecutive bytes at a time, past the caches (nothing here reads the records
-// back).  Bound by the writes: 256 x 256 x 128 nodes take 150 us (792 MB at
-// 5.3 TB/s, what a fill reaches); 12-byte cached stores took 240 us, and 282
-// with every thread finding its cell by 64-bit divisions.
+// 16-byte loads from at most two 128-byte lines.  One workgroup per 256 cells at
+// most: a stretch of a long row (all of about the same length), or as many short
+// rows of one z layer as make 256 cells.  Their node rows go through LDS, and each
+// thread writes 16 consecutive bytes at a time, past the caches (nothing here
+// reads the records back).  Bound by the writes: 256 x 256 x 128 nodes take 150 us
+// (792 MB at 5.3 TB/s, what a fill reaches); 12-byte cached stores took 240 us, and
+// 282 with every thread finding its cell by 64-bit divisions.  17 x 17 x 2048 nodes,
+// one row a workgroup 34 us, 16 rows 18; 258 x 256 x 127, stretches of 256 and 1
+// 265 us, of 129 and 128 189.
 constexpr int kDirCells = 256;
 
+// cells: of a stretch (with one of them a row, the whole row), rows: per workgroup
 __global__ void __launch_bounds__(256) k_cell_dirs(const float4 *__restrict__ nodes, int nx, int ny, int chunks,
-                                                   int64_t units, float *__restrict__ dirs)
+                                                   int cells, int rows, int groups, int64_t units,
+                                                   float *__restrict__ dirs)
 {
-    __shared__ float4 stage[4][kDirCells + 1];
+    // two layers of rows + 1 node rows; (rows + 1)(cells + 1) <= 2 (kDirCells + 1)
+    __shared__ float4 stage[4 * (kDirCells + 1)];
     const int cx = nx - 1, cy = ny - 1;
     for (int64_t u = blockIdx.x; u < units; u += gridDim.x) {
-        const int64_t row = u / chunks;
-        const int x0 = (int)(u % chunks) * kDirCells, nc = cx - x0 < kDirCells ? cx - x0 : kDirCells;
-        const int64_t j = row % cy, k = row / cy;
+        const int x0 = (int)(u % chunks) * cells, nc = cx - x0 < cells ? cx - x0 : cells;
+        const int64_t rest = u / chunks, k = rest / groups;
+        const int j = (int)(rest % groups) * rows, nr = cy - j < rows ? cy - j : rows;
         const float4 *base = nodes + (k * ny + j) * nx + x0;
-        for (int x = (int)threadIdx.x; x <= nc; x += 256)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) stage[r][x] = base[(int64_t)((r >> 1) * ny + (r & 1)) * nx + x];
+        const int w = nc + 1, layer = (nr + 1) * w;   // staged row; layer
+        for (int e = (int)threadIdx.x; e < layer; e += 256) {
+            const int r = e / w;
+            const int64_t o = (int64_t)r * nx + (e - r * w);
+            stage[e] = base[o];
+            stage[layer + e] = base[(int64_t)nx * ny + o];
+        }
         __syncthreads();
         typedef float f32x4 __attribute__((ext_vector_type(4)));
-        f32x4 *out = reinterpret_cast<f32x4 *>(dirs + (row * cx + x0) * 24);
-        for (int q = (int)threadIdx.x; q < 6 * nc; q += 256) {
-            const int c = q / 6, w = 4 * (q - 6 * c);   // floats w .. w + 3 of cell c
+        f32x4 *out = reinterpret_cast<f32x4 *>(dirs + ((k * cy + j) * cx + x0) * 24);
+        for (int q = (int)threadIdx.x; q < 6 * nr * nc; q += 256) {
+            const int c = q / 6, p = 4 * (q - 6 * c);   // floats p .. p + 3 of cell c of the workgroup's
+            const int n = c + c / nc;                   // its staged node in the first layer
             f32x4 o;
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
-                const int v = (w + t) / 3;
-                o[t] = reinterpret_cast<const float *>(&stage[v >> 1][c + (v & 1)])[w + t - 3 * v];
+                const int v = (p + t) / 3;
+                const float4 *node = stage + ((v & 4) ? layer : 0) + ((v & 2) ? w : 0) + (v & 1) + n;
+                o[t] = reinterpret_cast<const float *>(node)[p + t - 3 * v];
             }
             __builtin_nontemporal_store(o, out + q);
         }
@@ -184,11 +196,13 @@ uint64_t cell_dir_bytes(const qsq_grid *g)
 hipError_t launch_cell_dirs(const qsq_field *f, void *ws, hipStream_t st)
 {
     const int64_t nx = f->grid.n[0], ny = f->grid.n[1];
-    const int64_t chunks = (nx - 1 + kDirCells - 1) / kDirCells, units = chunks * (ny - 1) * (f->grid.n[2] - 1);
+    const int64_t cx = nx - 1, cy = ny - 1, chunks = (cx + kDirCells - 1) / kDirCells, cells = (cx + chunks - 1) / chunks;
+    const int64_t fit = kDirCells / cells, rows = chunks > 1 ? 1 : fit < cy ? fit : cy, groups = (cy + rows - 1) / rows;
+    const int64_t units = chunks * groups * (f->grid.n[2] - 1);
     const int64_t cap = (int64_t)device_cu_count() * 64;
     hipLaunchKernelGGL(k_cell_dirs, dim3((unsigned)(units < cap ? units : cap)), dim3(256), 0, st,
-                       static_cast<const float4 *>(f->nodes), (int)nx, (int)ny, (int)chunks, units,
-                       static_cast<float *>(ws));
+                       static_cast<const float4 *>(f->nodes), (int)nx, (int)ny, (int)chunks, (int)cells, (int)rows,
+                       (int)groups, units, static_cast<float *>(ws));
     return hipGetLastError();
 }
 

@@ -21,3 +21,10 @@ def test_direction_records(n):
                         for c in (0, 1) for b_ in (0, 1) for a in (0, 1)], 3)
     got = f.dirs_ws.view(torch.float32)[:want.numel()].reshape(want.shape)
     assert torch.equal(got, want)
+
+
+# rows of one layer together: whole groups and a remainder, the longest row that
+# still pairs (128 cells), the shortest (1), and long rows in equal stretches
+@pytest.mark.parametrize("n", [(2, 300, 3), (3, 129, 2), (9, 40, 3), (18, 33, 3), (86, 8, 3), (129, 6, 3), (130, 4, 3), (771, 3, 3)])
+def test_direction_records_of_short_and_uneven_rows(n):
+    test_direction_records(n)
