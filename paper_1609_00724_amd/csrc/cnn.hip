@@ -158,10 +158,9 @@ __global__ void k_prepare(const float *params, uint16_t *prep)
 // (kConvRows + 2, pixels x - 1 .. x + 64, zeros outside the image) in LDS with
 // all loads in flight at once; lane (i, kg) then reads pixels x0 + i - 1,
 // x0 + i, x0 + i + 1, channels 8 kg .. 8 kg + 7, of each row from there, in a
-// window of three rows sliding down the strip.  Inputs with CI < 32 channels
-// (FP32 with 3, BF16 with 2) are staged the same way, as BF16 with cpad(CI)
-// channels per pixel, and the 9 taps' channels packed along K (cpad(CI) per
-// tap) are read from there.  Outputs (each nullable): BF16 activations (ReLU
+// window of three rows sliding down the strip.  The network input (3 channels,
+// FP32) is staged the same way, as BF16 with cpad(3) channels per pixel, and the
+// 9 taps' channels packed along K (cpad(3) per tap) are read from there.  Outputs (each nullable): BF16 activations (ReLU
 // applied) and FP32 values.  A BF16 NHWC output of 32 channels goes
 // through LDS so that each lane stores one pixel's 8 channels (16 bytes) and
 // the wave a row's 1 KB with one store.  One tile's tensors are addressed
@@ -197,13 +196,13 @@ struct Row3 {
     bf16x8 m, z, p;   // the lane's pixel shifted by -1, 0, +1
 };
 
-template <int CI, int CO, bool SRC_F32>
+template <int CI, int CO>
 __global__ void __launch_bounds__(256) k_conv(const void *__restrict__ in, ConvDims d,
                                               const uint16_t *__restrict__ wm, const float *__restrict__ bias,
                                               bool relu, uint16_t *__restrict__ out_bf, float *__restrict__ out_f32)
 {
     constexpr int NT = ntile(CO), COP = 16 * NT, NK = nchunk(CI), R = kConvRows;
-    static_assert(CI >= 32 ? !SRC_F32 : (CI == 3) == SRC_F32, "FP32 input has 3 channels, BF16 input 2 or 32");
+    static_assert(CI == 32 || CI == 3, "BF16 activations of 32 channels, or the FP32 network input");
     const int lane = (int)(threadIdx.x & 63);
     // workgroup: R rows of a 64-pixel column chunk of one image; wave s (a
     // scalar, so that the buffer resources below are too) the 16-pixel strip
@@ -259,13 +258,9 @@ __global__ void __launch_bounds__(256) k_conv(const void *__restrict__ in, ConvD
             for (int j = 0; j < WPT; ++j) tmp[k][j] = 0u;
             if (q < NPX && yy >= 0 && yy < d.h && px >= 0 && px < d.w) {
                 const int64_t pix = (img * d.h + yy) * d.w + px;
-                if constexpr (SRC_F32) {
-                    const float *pf = static_cast<const float *>(in) + pix * 3;
-                    tmp[k][0] = (uint32_t)f2bf(pf[0]) | ((uint32_t)f2bf(pf[1]) << 16);
-                    tmp[k][1] = (uint32_t)f2bf(pf[2]);
-                } else {
-                    tmp[k][0] = *reinterpret_cast<const uint32_t *>(static_cast<const uint16_t *>(in) + pix * 2);
-                }
+                const float *pf = static_cast<const float *>(in) + pix * 3;
+                tmp[k][0] = (uint32_t)f2bf(pf[0]) | ((uint32_t)f2bf(pf[1]) << 16);
+                tmp[k][1] = (uint32_t)f2bf(pf[2]);
             }
         }
 #pragma unroll
@@ -399,190 +394,6 @@ __global__ void __launch_bounds__(256) k_conv(const void *__restrict__ in, ConvD
 }
 
 // ---------------------------------------------------------------------------
-// Channel-major row copies.  The weight gradient contracts over pixels, and a
-// matrix-core operand takes 8 consecutive K values per lane, so its operands
-// are read from copies of the activations and gradients laid out per image
-// row as [channel][x] (BF16): cm[((img h + y) C + c) w + x], made by k_to_cm from
-// NHWC data.  (The per-layer check calls take this way; a training step's
-// backward pass is k_bwd below.)
-// ---------------------------------------------------------------------------
-template <int C, bool SRC_F32>
-__global__ void k_to_cm(const void *in, int64_t rows, int w, uint16_t *out)
-{
-    if constexpr (C <= 4) {
-        // one pixel per thread: its C values read together, one store per
-        // channel row (consecutive threads write consecutive pixels)
-        const int64_t total = rows * w;
-        for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < total;
-             p += (int64_t)gridDim.x * blockDim.x) {
-            const int64_t row = p / w, x = p % w;
-#pragma unroll
-            for (int c = 0; c < C; ++c)
-                out[(row * C + c) * w + x] = SRC_F32 ? f2bf(static_cast<const float *>(in)[p * C + c])
-                                                     : static_cast<const uint16_t *>(in)[p * C + c];
-        }
-    } else {
-        const int64_t total = rows * C * w;
-        for (int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; o < total;
-             o += (int64_t)gridDim.x * blockDim.x) {
-            const int x = (int)(o % w), c = (int)((o / w) % C);
-            const int64_t row = o / ((int64_t)w * C), e = (row * w + x) * C + c;
-            out[o] = SRC_F32 ? f2bf(static_cast<const float *>(in)[e]) : static_cast<const uint16_t *>(in)[e];
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Weight and bias gradients of one layer: dW[tap][ci][co] = sum over pixels
-// of x[p + tap - (1,1)][ci] dy[p][co], db[co] = sum of dy[p][co], from the
-// channel-major copies.  MFMA: M = 16 input channels, N = 16 output
-// channels, K = 32 pixels of a row.  A workgroup takes R rows of one image
-// and a 64-pixel column chunk, one wave per (input tile, output tile) pair;
-// each wave covers the whole chunk as two K halves: lane (i, kg) reads
-// pixels x0 + 8 kg .. + 7 and x0 + 32 + 8 kg .. + 7 of channel i (two aligned
-// 16-byte buffer loads per row, zeros outside the tile).  The pixel pairs
-// either side, for the operands shifted by one pixel (byte-align of adjacent
-// dwords), come from the neighbouring lanes (kg - 1, kg + 1, and across the
-// two halves) by ds_bpermute; only the chunk's outer edges are loaded, and
-// only where the chunk does not end at the image edge.  Each wave slides a
-// window of three input rows down its R rows, four at a time, and writes its
-// sums to the workgroup's slot; k_wgrad_reduce1/2 add the slots in a fixed
-// order (deterministic).
-// ---------------------------------------------------------------------------
-struct Shift3 {
-    bf16x8 m, z, p;   // pixels shifted by -1, 0, +1
-};
-
-// one input row of a lane: the two 8-pixel chunks and the pixel pairs either
-// side of each
-struct XRow {
-    uint32_t d[2][4], lft[2], rgt[2];
-};
-
-__device__ __forceinline__ Shift3 shift3(const uint32_t (&d)[4], uint32_t lft, uint32_t rgt)
-{
-    const uint32_t e12 = __builtin_amdgcn_alignbyte(d[1], d[0], 2), e34 = __builtin_amdgcn_alignbyte(d[2], d[1], 2),
-                   e56 = __builtin_amdgcn_alignbyte(d[3], d[2], 2);
-    Shift3 s;
-    s.z = __builtin_bit_cast(bf16x8, make_uint4(d[0], d[1], d[2], d[3]));
-    s.m = __builtin_bit_cast(bf16x8, make_uint4(__builtin_amdgcn_alignbyte(d[0], lft, 2), e12, e34, e56));
-    s.p = __builtin_bit_cast(bf16x8, make_uint4(e12, e34, e56, __builtin_amdgcn_alignbyte(rgt, d[3], 2)));
-    return s;
-}
-
-template <int CI, int CO>
-__global__ void __launch_bounds__(256) k_wgrad(const uint16_t *__restrict__ xcm, const uint16_t *__restrict__ gcm,
-                                               ConvDims d, int R, float *__restrict__ part)
-{
-    constexpr int TO = ntile(CO);
-    constexpr int SLOT = 9 * CI * CO + CO;   // dW (tap, ci, co) then db (co): the parameter order
-    const int lane = (int)(threadIdx.x & 63), wid = (int)(threadIdx.x >> 6);
-    const int a = wid / TO, b = wid % TO;
-    const int i = lane & 15, kg = lane >> 4;
-    const int cpr = (d.w + 63) / 64, rb = d.h / R;
-    const int64_t unit = blockIdx.x;
-    const int x0 = (int)(unit % cpr) * 64, y0 = (int)((unit / cpr) % rb) * R;
-    const int64_t img = unit / ((int64_t)cpr * rb);
-    const int c = a * 16 + i, co = b * 16 + i;
-    const int64_t npix = (int64_t)d.h * d.w;
-    const int xbytes = (int)(npix * CI * 2), gbytes = (int)(npix * CO * 2);
-    const __amdgpu_buffer_rsrc_t xrs = buf_rsrc(xcm + img * npix * CI, xbytes);
-    const __amdgpu_buffer_rsrc_t grs = buf_rsrc(gcm + img * npix * CO, gbytes);
-    // byte offset of pixel x of row yy of channel ch (out of range: zeros)
-    auto xoff = [&](int yy, int x) {
-        return c < CI && yy >= 0 && yy < d.h && x >= 0 && x < d.w ? ((yy * CI + c) * d.w + x) * 2 : xbytes;
-    };
-    const bool edge_l = x0 > 0, edge_r = x0 + 64 < d.w;   // chunk edges inside the image
-    const int up = ((lane + 48) & 63) << 2, dn = ((lane + 16) & 63) << 2;   // ds_bpermute addresses of kg - 1, kg + 1
-    auto xrow = [&](int yy) {
-        XRow r;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const u32x4 q = __builtin_amdgcn_raw_buffer_load_b128(xrs, xoff(yy, x0 + 32 * h + 8 * kg), 0, 0);
-            r.d[h][0] = q.x;
-            r.d[h][1] = q.y;
-            r.d[h][2] = q.z;
-            r.d[h][3] = q.w;
-        }
-        // pixel pairs left of each chunk: lane kg - 1's last dword (for kg = 0
-        // of the second half: lane kg = 3 of the first half)
-        const uint32_t l0 = (uint32_t)__builtin_amdgcn_ds_bpermute(up, (int)r.d[0][3]);
-        const uint32_t l1 = (uint32_t)__builtin_amdgcn_ds_bpermute(up, (int)r.d[1][3]);
-        const uint32_t r0 = (uint32_t)__builtin_amdgcn_ds_bpermute(dn, (int)r.d[0][0]);
-        const uint32_t r1 = (uint32_t)__builtin_amdgcn_ds_bpermute(dn, (int)r.d[1][0]);
-        uint32_t el = 0, er = 0;
-        if (edge_l) el = __builtin_amdgcn_raw_buffer_load_b32(xrs, kg == 0 ? xoff(yy, x0 - 2) : xbytes, 0, 0);
-        if (edge_r) er = __builtin_amdgcn_raw_buffer_load_b32(xrs, kg == 3 ? xoff(yy, x0 + 64) : xbytes, 0, 0);
-        r.lft[0] = kg > 0 ? l0 : el;
-        r.lft[1] = kg > 0 ? l1 : l0;
-        r.rgt[0] = kg < 3 ? r0 : r1;
-        r.rgt[1] = kg < 3 ? r1 : er;
-        return r;
-    };
-    auto grow = [&](int yy, int h) {
-        const int x = x0 + 32 * h + 8 * kg;
-        const u32x4 q = __builtin_amdgcn_raw_buffer_load_b128(
-            grs, co < CO && yy < d.h && x < d.w ? ((yy * CO + co) * d.w + x) * 2 : gbytes, 0, 0);
-        return __builtin_bit_cast(bf16x8, q);
-    };
-    f32x4 acc[9];
-#pragma unroll
-    for (int tp = 0; tp < 9; ++tp) acc[tp] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float dbs = 0.0f;   // bias gradient (waves of input tile 0 only)
-    // rows go four at a time: all loads of a group are issued before its
-    // products, so their latencies overlap (R is a multiple of 4)
-    XRow win[6];   // input rows y - 1 .. y + 4
-    win[0] = xrow(y0 - 1);
-    win[1] = xrow(y0);
-    for (int rr = 0; rr < R; rr += 4) {
-        const int y = y0 + rr;
-        bf16x8 gb[4][2];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            win[2 + k] = xrow(y + 1 + k);
-            gb[k][0] = grow(y + k, 0);
-            gb[k][1] = grow(y + k, 1);
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            if (a == 0) {
-#pragma unroll
-                for (int j = 0; j < 8; ++j) dbs += (float)gb[k][0][j] + (float)gb[k][1][j];
-            }
-#pragma unroll
-            for (int ty = 0; ty < 3; ++ty)
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const XRow &xr = win[k + ty];
-                    const Shift3 xs3 = shift3(xr.d[h], xr.lft[h], xr.rgt[h]);
-                    acc[3 * ty + 0] = mfma(xs3.m, gb[k][h], acc[3 * ty + 0]);
-                    acc[3 * ty + 1] = mfma(xs3.z, gb[k][h], acc[3 * ty + 1]);
-                    acc[3 * ty + 2] = mfma(xs3.p, gb[k][h], acc[3 * ty + 2]);
-                }
-        }
-        win[0] = win[4];
-        win[1] = win[5];
-    }
-    // lane holds D[ci = a 16 + 4 kg + r][co = b 16 + i]; the slot keeps the
-    // real channels only
-    float *slot = part + unit * SLOT;
-    if (co < CO) {
-#pragma unroll
-        for (int tp = 0; tp < 9; ++tp)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int ci = a * 16 + 4 * kg + r;
-                if (ci < CI) slot[(tp * CI + ci) * CO + co] = acc[tp][r];
-            }
-    }
-    if (a == 0) {
-        dbs += __shfl_xor(dbs, 16);
-        dbs += __shfl_xor(dbs, 32);
-        if (kg == 0 && co < CO) slot[9 * CI * CO + co] = dbs;
-    }
-}
-
-// ---------------------------------------------------------------------------
 // Backward pass of a layer with 32 input channels, in one kernel: the input
 // gradient dx = conv(dy, transposed flipped weights), masked where the layer's
 // input activation is 0 (ReLU), and the weight and bias gradients
@@ -602,10 +413,12 @@ __global__ void __launch_bounds__(256) k_wgrad(const uint16_t *__restrict__ xcm,
 //     group reads 4 pixels of 16 channels and gets 4 pixels of its lane's
 //     channel); three reads give 12 pixels, and so the operands of the three
 //     taps of a row.
-// The mask comes from the staged activations by the same reads.  FIRST (layer
-// 1): dx, wanted by layer 0's weight gradient alone, stays in LDS, where
+// The mask comes from the staged activations by the same reads.  kBwdFirst
+// (layer 1): dx, wanted by layer 0's weight gradient alone, stays in LDS, where
 // dW0[tap][ci][co] = sum of x0[p + tap - (1,1)][ci] dx[p][co] is formed too
-// (M = 27 (tap, ci) pairs in two tiles).  Sums go to the workgroup's slots.
+// (M = 27 (tap, ci) pairs in two tiles).  Sums go to the workgroup's slots.  A layer
+// on its own takes the same kernel: kBwdPlain stores dx as it stands (FP32, no
+// mask; not where dx32 is null), kBwdInput forms layer 0's sums from its dy.
 // Bound by HBM: dy and x read once, dx written once.  256 tiles of 64 x 64, as
 // an input gradient and a weight gradient apart (which also needed channel-major
 // copies of x and dy from the kernels before them) and here: CO = 2 (138 MB)
@@ -613,9 +426,6 @@ __global__ void __launch_bounds__(256) k_wgrad(const uint16_t *__restrict__ xcm,
 // TB/s), FIRST (147 MB) 52 + 47 + layer 0's 24 and 70 us (2.1 TB/s: the chain
 // through LDS with two waves per SIMD, 218 registers).
 // ---------------------------------------------------------------------------
-#ifndef QSQ_BWD_STEP
-#define QSQ_BWD_STEP 2
-#endif
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
@@ -633,14 +443,19 @@ __device__ __forceinline__ bf16x8 join8(s16x4 a, s16x4 b)
     return __builtin_bit_cast(bf16x8, v);
 }
 
-constexpr int kBwdStep = 2, kRing = kBwdStep + 2, kBwdPx = 66, kBwdRow = 68;   // staged pixels; a row's room
+// rows a step; staged rows (the step's and one either side); staged pixels; a row's room
+constexpr int kBwdStep = 2, kBwdHalo = 2, kRing = kBwdStep + kBwdHalo, kBwdPx = 66, kBwdRow = 68;
+enum BwdOut { kBwdMasked, kBwdFirst, kBwdPlain, kBwdInput };
 
-template <int CO, bool FIRST>
+template <int CO, BwdOut OUT>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k_bwd(const uint16_t *__restrict__ dy, const uint16_t *__restrict__ x,
                                              const float *__restrict__ x0, ConvDims d, int R,
                                              const uint16_t *__restrict__ wm, uint16_t *__restrict__ dx,
-                                             float *__restrict__ part, float *__restrict__ part0)
+                                             float *__restrict__ dx32, float *__restrict__ part,
+                                             float *__restrict__ part0)
 {
+    constexpr bool FIRST = OUT == kBwdFirst || OUT == kBwdInput;   // layer 0's sums too
+    constexpr bool BACK = OUT != kBwdInput;                        // dx and dW
     static_assert(CO == 32 || !FIRST, "layer 0's weight gradient goes with a 32-channel layer");
     constexpr int NK = nchunk(CO);
     constexpr int SLOT = 9 * 32 * CO + CO, SLOT0 = 9 * 3 * 32 + 32;
@@ -662,7 +477,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
     const int64_t unit = blockIdx.x;
     const int xc = (int)(unit % cpr) * 64, y0 = (int)((unit / cpr) % rb) * R;
     const int64_t img = unit / ((int64_t)cpr * rb), npix = (int64_t)d.h * d.w;
-    const __amdgpu_buffer_rsrc_t xrs = buf_rsrc(x + img * npix * 32, (int)(npix * 64));
+    const __amdgpu_buffer_rsrc_t xrs = buf_rsrc(BACK ? x + img * npix * 32 : nullptr, (int)(npix * 64));
     const __amdgpu_buffer_rsrc_t yrs = buf_rsrc(dy + img * npix * CO, (int)(npix * CO * 2));
     const __amdgpu_buffer_rsrc_t grs = buf_rsrc(dx ? dx + img * npix * 32 : nullptr, (int)(npix * 64));
     const __amdgpu_buffer_rsrc_t zrs = buf_rsrc(FIRST ? x0 + img * npix * 3 : nullptr, (int)(npix * 12));
@@ -683,12 +498,14 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
     u32x4 tx[PER], ty[CO == 32 ? PER : 1];
     uint32_t ts[PERS], tz[FIRST ? PERS : 1][2];
     auto fetch = [&](int r0, int rows) {
+        if constexpr (BACK) {
 #pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const int e = tid + 256 * k, r = e / XCH, c = e % XCH;
-            const int off = r < rows ? xoff(r0 + r, c) : (int)(npix * 64);
-            tx[k] = __builtin_amdgcn_raw_buffer_load_b128(xrs, off, 0, 0);
-            if constexpr (CO == 32) ty[k] = __builtin_amdgcn_raw_buffer_load_b128(yrs, off, 0, 0);
+            for (int k = 0; k < PER; ++k) {
+                const int e = tid + 256 * k, r = e / XCH, c = e % XCH;
+                const int off = r < rows ? xoff(r0 + r, c) : (int)(npix * 64);
+                tx[k] = __builtin_amdgcn_raw_buffer_load_b128(xrs, off, 0, 0);
+                if constexpr (CO == 32) ty[k] = __builtin_amdgcn_raw_buffer_load_b128(yrs, off, 0, 0);
+            }
         }
         if constexpr (CO == 2) {
 #pragma unroll
@@ -711,13 +528,15 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
         }
     };
     auto put = [&](int r0, int rows) {
+        if constexpr (BACK) {
 #pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const int e = tid + 256 * k, r = e / XCH, c = e % XCH;
-            if (r < rows) {
-                const int q = slot_of(r0 + r) * XRO + c;
-                lx[q] = __builtin_bit_cast(uint4, tx[k]);
-                if constexpr (CO == 32) reinterpret_cast<uint4 *>(lyb)[q] = __builtin_bit_cast(uint4, ty[k]);
+            for (int k = 0; k < PER; ++k) {
+                const int e = tid + 256 * k, r = e / XCH, c = e % XCH;
+                if (r < rows) {
+                    const int q = slot_of(r0 + r) * XRO + c;
+                    lx[q] = __builtin_bit_cast(uint4, tx[k]);
+                    if constexpr (CO == 32) reinterpret_cast<uint4 *>(lyb)[q] = __builtin_bit_cast(uint4, ty[k]);
+                }
             }
         }
         if constexpr (CO == 2 || FIRST) {
@@ -747,7 +566,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
 #pragma unroll
     for (int kc = 0; kc < NK; ++kc)
 #pragma unroll
-        for (int t = 0; t < 2; ++t) bw[kc][t] = ld_bf16x8(wm + ((int64_t)(kc * 32 + t * 16 + i) * 32 + 8 * kg));
+        for (int t = 0; t < 2; ++t)
+            if constexpr (BACK) bw[kc][t] = ld_bf16x8(wm + ((int64_t)(kc * 32 + t * 16 + i) * 32 + 8 * kg));
     const int a = CO == 32 ? wv >> 1 : wv & 1, b = CO == 32 ? wv & 1 : 0;
     const int hfirst = CO == 32 ? 0 : wv >> 1, hlast = CO == 32 ? 2 : hfirst + 1;   // the wave's halves of the chunk
     f32x4 acc[9], acc0 = {0.f, 0.f, 0.f, 0.f};
@@ -758,18 +578,26 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
     // element offset of a transposing read: pixel 8 kg + i / 4, channel 4 (i % 4) of a row
     const int tro = (8 * kg + (i >> 2)) * 32 + 4 * (i & 3);
 
-    fetch(0, 2);
-    put(0, 2);
-    fetch(2, kBwdStep);
+    fetch(0, kBwdHalo);
+    put(0, kBwdHalo);
+    fetch(kBwdHalo, kBwdStep);
     for (int g = 0; g < R; g += kBwdStep) {
-        put(g + 2, kBwdStep);
+        put(g + kBwdHalo, kBwdStep);
         __syncthreads();
-        if (g + kBwdStep < R) fetch(g + 2 + kBwdStep, kBwdStep);
+        if (g + kBwdStep < R) fetch(g + kBwdHalo + kBwdStep, kBwdStep);
         int ro[kRing];   // ring slots of rows g .. g + 3
 #pragma unroll
         for (int k = 0; k < kRing; ++k) ro[k] = slot_of(g + k);
+        if constexpr (!BACK) {
+            // layer 0's output gradient: dy rows g, g + 1 of the workgroup's, zeros past the image
+#pragma unroll
+            for (int k = 0; k < kBwdStep; ++k) {
+                const int px = xc + (tid >> 2), off = px < d.w ? (((y0 + g + k) * d.w + px) * 32 + 8 * (tid & 3)) * 2 : (int)(npix * 64);
+                reinterpret_cast<u32x4 *>(lg)[k * 256 + tid] = __builtin_amdgcn_raw_buffer_load_b128(yrs, off, 0, 0);
+            }
+        }
         // --- input gradient
-        if (x0s < d.w) {
+        if (BACK && x0s < d.w) {
             Row3 win[3];
             auto lds3 = [&](int k) {
                 const uint4 *p = reinterpret_cast<const uint4 *>(lyb) + (ro[k] * kBwdRow + 16 * wv + i) * 4 + kg;
@@ -815,8 +643,17 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
                         for (int t = 0; t < 2; ++t) o[t] = mfma(op, bw[kc][t], o[t]);
                     }
                 }
-                // lane: pixels 4 kg + r of the strip, channel 16 t + i; its
-                // mask by a transposing read of the staged activations
+                // lane: pixels 4 kg + r of the strip, channel 16 t + i
+                if constexpr (OUT == kBwdPlain) {
+                    if (!dx32) continue;
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            dx32[(img * npix + (int64_t)(y0 + g + rr) * d.w + x0s + 4 * kg + r) * 32 + 16 * t + i] = o[t][r];
+                    continue;
+                }
+                // its mask by a transposing read of the staged activations
                 const uint16_t *xm = reinterpret_cast<const uint16_t *>(lx) +
                                      (ro[rr + 1] * kBwdRow + 16 * wv + 1 + 4 * kg + (i >> 2)) * 32 + 4 * (i & 3);
                 uint16_t *stage = FIRST ? lg + (rr * 64 + 16 * wv) * 32 : lg + wv * 16 * 32;
@@ -840,65 +677,67 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
                     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
                 }
             }
-        } else if constexpr (FIRST) {
+        } else if constexpr (BACK && FIRST) {
             // pixels past the image add nothing to layer 0's sums
 #pragma unroll
             for (int rr = 0; rr < kBwdStep; ++rr)
                 reinterpret_cast<uint4 *>(lg + (rr * 64 + 16 * wv) * 32)[lane] = make_uint4(0u, 0u, 0u, 0u);
         }
-        // --- weight gradient: x rows g .. g + 3 against dy rows g + 1, g + 2
-        bf16x8 gb[kBwdStep][2];
+        if constexpr (BACK) {
+            // --- weight gradient: x rows g .. g + 3 against dy rows g + 1, g + 2
+            bf16x8 gb[kBwdStep][2];
 #pragma unroll
-        for (int k = 0; k < kBwdStep; ++k)
+            for (int k = 0; k < kBwdStep; ++k)
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                if (h < hfirst || h >= hlast) continue;
-                if constexpr (CO == 32) {
-                    const uint16_t *p = reinterpret_cast<const uint16_t *>(lyb) + (ro[k + 1] * kBwdRow + 1 + 32 * h) * 32 + 16 * b + tro;
-                    gb[k][h] = join8(lds_tr(p), lds_tr(p + 4 * 32));
-                } else {
-                    // 8 pixels of channel i < 2 from the dword rows
-                    const uint32_t *p = reinterpret_cast<const uint32_t *>(lyb) + ro[k + 1] * SPX + 4 + 32 * h + 8 * kg;
-                    const uint4 u = reinterpret_cast<const uint4 *>(p)[0], v = reinterpret_cast<const uint4 *>(p)[1];
-                    const uint32_t w[8] = {u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w};
-                    uint32_t o[4];
+                for (int h = 0; h < 2; ++h) {
+                    if (h < hfirst || h >= hlast) continue;
+                    if constexpr (CO == 32) {
+                        const uint16_t *p = reinterpret_cast<const uint16_t *>(lyb) + (ro[k + 1] * kBwdRow + 1 + 32 * h) * 32 + 16 * b + tro;
+                        gb[k][h] = join8(lds_tr(p), lds_tr(p + 4 * 32));
+                    } else {
+                        // 8 pixels of channel i < 2 from the dword rows
+                        const uint32_t *p = reinterpret_cast<const uint32_t *>(lyb) + ro[k + 1] * SPX + 4 + 32 * h + 8 * kg;
+                        const uint4 u = reinterpret_cast<const uint4 *>(p)[0], v = reinterpret_cast<const uint4 *>(p)[1];
+                        const uint32_t w[8] = {u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w};
+                        uint32_t o[4];
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        o[e] = i == 0 ? (w[2 * e] & 0xffffu) | (w[2 * e + 1] << 16)
-                                      : i == 1 ? (w[2 * e] >> 16) | (w[2 * e + 1] & 0xffff0000u) : 0u;
-                    gb[k][h] = __builtin_bit_cast(bf16x8, make_uint4(o[0], o[1], o[2], o[3]));
+                        for (int e = 0; e < 4; ++e)
+                            o[e] = i == 0 ? (w[2 * e] & 0xffffu) | (w[2 * e + 1] << 16)
+                                          : i == 1 ? (w[2 * e] >> 16) | (w[2 * e + 1] & 0xffff0000u) : 0u;
+                        gb[k][h] = __builtin_bit_cast(bf16x8, make_uint4(o[0], o[1], o[2], o[3]));
+                    }
+                    if (a == 0) {
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) dbs += (float)gb[k][h][j];
+                    }
                 }
-                if (a == 0) {
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) dbs += (float)gb[k][h][j];
+            for (int k = 0; k < kRing; ++k)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    if (h < hfirst || h >= hlast) continue;
+                    const uint16_t *p = reinterpret_cast<const uint16_t *>(lx) + (ro[k] * kBwdRow + 32 * h) * 32 + 16 * a + tro;
+                    // staged pixels 0 .. 11 from the lane's first; the operands
+                    // shifted by 0, 1, 2 are dwords 0 .. 3, their odd pairs, 1 .. 4
+                    const u32x2 q0 = __builtin_bit_cast(u32x2, lds_tr(p)), q1 = __builtin_bit_cast(u32x2, lds_tr(p + 4 * 32)),
+                                q2 = __builtin_bit_cast(u32x2, lds_tr(p + 8 * 32));
+                    const uint32_t w[5] = {q0.x, q0.y, q1.x, q1.y, q2.x};
+                    const bf16x8 xs[3] = {
+                        __builtin_bit_cast(bf16x8, make_uint4(w[0], w[1], w[2], w[3])),
+                        __builtin_bit_cast(bf16x8, make_uint4(__builtin_amdgcn_alignbyte(w[1], w[0], 2),
+                                                              __builtin_amdgcn_alignbyte(w[2], w[1], 2),
+                                                              __builtin_amdgcn_alignbyte(w[3], w[2], 2),
+                                                              __builtin_amdgcn_alignbyte(w[4], w[3], 2))),
+                        __builtin_bit_cast(bf16x8, make_uint4(w[1], w[2], w[3], w[4]))};
+#pragma unroll
+                    for (int tyy = 0; tyy < 3; ++tyy) {
+                        const int q = k - tyy;   // dy row g + 1 + q
+                        if (q < 0 || q >= kBwdStep) continue;
+#pragma unroll
+                        for (int t = 0; t < 3; ++t) acc[3 * tyy + t] = mfma(xs[t], gb[q][h], acc[3 * tyy + t]);
+                    }
                 }
-            }
-#pragma unroll
-        for (int k = 0; k < kRing; ++k)
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                if (h < hfirst || h >= hlast) continue;
-                const uint16_t *p = reinterpret_cast<const uint16_t *>(lx) + (ro[k] * kBwdRow + 32 * h) * 32 + 16 * a + tro;
-                // staged pixels 0 .. 11 from the lane's first; the operands
-                // shifted by 0, 1, 2 are dwords 0 .. 3, their odd pairs, 1 .. 4
-                const u32x2 q0 = __builtin_bit_cast(u32x2, lds_tr(p)), q1 = __builtin_bit_cast(u32x2, lds_tr(p + 4 * 32)),
-                            q2 = __builtin_bit_cast(u32x2, lds_tr(p + 8 * 32));
-                const uint32_t w[5] = {q0.x, q0.y, q1.x, q1.y, q2.x};
-                const bf16x8 xs[3] = {
-                    __builtin_bit_cast(bf16x8, make_uint4(w[0], w[1], w[2], w[3])),
-                    __builtin_bit_cast(bf16x8, make_uint4(__builtin_amdgcn_alignbyte(w[1], w[0], 2),
-                                                          __builtin_amdgcn_alignbyte(w[2], w[1], 2),
-                                                          __builtin_amdgcn_alignbyte(w[3], w[2], 2),
-                                                          __builtin_amdgcn_alignbyte(w[4], w[3], 2))),
-                    __builtin_bit_cast(bf16x8, make_uint4(w[1], w[2], w[3], w[4]))};
-#pragma unroll
-                for (int tyy = 0; tyy < 3; ++tyy) {
-                    const int q = k - tyy;   // dy row g + 1 + q
-                    if (q < 0 || q >= kBwdStep) continue;
-#pragma unroll
-                    for (int t = 0; t < 3; ++t) acc[3 * tyy + t] = mfma(xs[t], gb[q][h], acc[3 * tyy + t]);
-                }
-            }
+        }
         if constexpr (FIRST) {
             // --- layer 0: (tap, ci) pairs 16 a .. + 15 against dx channels 16 b .. + 15
             __syncthreads();
@@ -929,7 +768,6 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
     }
     // lane holds D[ci = a 16 + 4 kg + r][co = b 16 + i]; the slot keeps the
     // real channels only
-    float *slot = part + unit * SLOT;
     if constexpr (CO == 2) {
         // the two halves of the chunk, added in a fixed order
         float *red = reinterpret_cast<float *>(lds);
@@ -945,16 +783,19 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
         dbs += red[2 * 9 * 64 * 4 + wv * 64 + lane];
     }
     const int co = b * 16 + i;
-    if (co < CO) {
+    if constexpr (BACK) {
+        float *slot = part + unit * SLOT;
+        if (co < CO) {
 #pragma unroll
-        for (int t = 0; t < 9; ++t)
+            for (int t = 0; t < 9; ++t)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) slot[(t * 32 + a * 16 + 4 * kg + r) * CO + co] = acc[t][r];
-    }
-    if (a == 0) {
-        dbs += __shfl_xor(dbs, 16);
-        dbs += __shfl_xor(dbs, 32);
-        if (kg == 0 && co < CO) slot[9 * 32 * CO + co] = dbs;
+                for (int r = 0; r < 4; ++r) slot[(t * 32 + a * 16 + 4 * kg + r) * CO + co] = acc[t][r];
+        }
+        if (a == 0) {
+            dbs += __shfl_xor(dbs, 16);
+            dbs += __shfl_xor(dbs, 32);
+            if (kg == 0 && co < CO) slot[9 * 32 * CO + co] = dbs;
+        }
     }
     if constexpr (FIRST) {
         float *s0 = part0 + unit * SLOT0;
@@ -1148,29 +989,18 @@ hipError_t cnn_prepare(const float *params, void *prep, hipStream_t st)
     return hipGetLastError();
 }
 
-static void conv_launch(int l, bool transposed, const void *in, ConvDims d, const void *prep, bool relu, uint16_t *out_bf,
-                        float *out_f32, hipStream_t st)
+static void conv_launch(int l, const void *in, ConvDims d, const void *prep, bool relu, uint16_t *out_bf, float *out_f32,
+                        hipStream_t st)
 {
     const dim3 grid((unsigned)(d.n * (d.h / kConvRows) * ((d.w + 63) / 64))), block(256);
-    if (!transposed) {
-        const uint16_t *wm = fwd_mat(prep, l);
-        const float *b = bias_of(prep, l);
-        if (l == 0)
-            hipLaunchKernelGGL((k_conv<3, 32, true>), grid, block, 0, st, in, d, wm, b, relu, out_bf, out_f32);
-        else if (l == 3)
-            hipLaunchKernelGGL((k_conv<32, 2, false>), grid, block, 0, st, in, d, wm, b, relu, out_bf, out_f32);
-        else
-            hipLaunchKernelGGL((k_conv<32, 32, false>), grid, block, 0, st, in, d, wm, b, relu, out_bf, out_f32);
-    } else {
-        // input gradient of layer l: a convolution from Co(l) to Ci(l) = 32 channels
-        const uint16_t *wm = bwd_mat(prep, l);
-        if (l == 3)
-            hipLaunchKernelGGL((k_conv<2, 32, false>), grid, block, 0, st, in, d, wm, (const float *)nullptr, false,
-                               out_bf, out_f32);
-        else
-            hipLaunchKernelGGL((k_conv<32, 32, false>), grid, block, 0, st, in, d, wm, (const float *)nullptr, false,
-                               out_bf, out_f32);
-    }
+    const uint16_t *wm = fwd_mat(prep, l);
+    const float *b = bias_of(prep, l);
+    if (l == 0)
+        hipLaunchKernelGGL((k_conv<3, 32>), grid, block, 0, st, in, d, wm, b, relu, out_bf, out_f32);
+    else if (l == 3)
+        hipLaunchKernelGGL((k_conv<32, 2>), grid, block, 0, st, in, d, wm, b, relu, out_bf, out_f32);
+    else
+        hipLaunchKernelGGL((k_conv<32, 32>), grid, block, 0, st, in, d, wm, b, relu, out_bf, out_f32);
 }
 
 // Rows per workgroup of layer l's weight-gradient pass: the smallest power
@@ -1217,12 +1047,7 @@ static uint64_t train_part_bytes(ConvDims d)
     return b + (uint64_t)wgrad_groups(d) * QSQ_CNN_PARAMS * 4;
 }
 
-// per-layer backward: channel-major copies of the input and of dy, then the slots
-uint64_t cnn_wgrad_scratch_bytes(int64_t n, int h, int w)
-{
-    const uint64_t cm = al256((uint64_t)n * h * w * 32 * 2);
-    return 2 * cm + wgrad_part_bytes(ConvDims{n, h, w});
-}
+uint64_t cnn_wgrad_scratch_bytes(int64_t n, int h, int w) { return wgrad_part_bytes(ConvDims{n, h, w}); }
 
 // the slots of layer l at `part` as a segment of a reduction job
 static void add_seg(int l, int64_t slots, float *part, float *dw, float *db, RedJob &J)
@@ -1238,21 +1063,6 @@ static void add_seg(int l, int64_t slots, float *part, float *dw, float *db, Red
     J.total += g.nout;
 }
 
-static void wgrad_slots_launch(int l, const uint16_t *xcm, const uint16_t *gcm, ConvDims d, float *part, float *dw,
-                               float *db, RedJob &J, hipStream_t st)
-{
-    const int64_t slots = wgrad_slots(d, l);
-    const int R = wgrad_rows(d, l);
-    const dim3 grid(slots), block(64 * ntile(kCi[l]) * ntile(kCo[l]));
-    if (l == 0)
-        hipLaunchKernelGGL((k_wgrad<3, 32>), grid, block, 0, st, xcm, gcm, d, R, part);
-    else if (l == 3)
-        hipLaunchKernelGGL((k_wgrad<32, 2>), grid, block, 0, st, xcm, gcm, d, R, part);
-    else
-        hipLaunchKernelGGL((k_wgrad<32, 32>), grid, block, 0, st, xcm, gcm, d, R, part);
-    add_seg(l, slots, part, dw, db, J);
-}
-
 static void wgrad_reduce(const RedJob &J, float *tmp, ConvDims d, hipStream_t st)
 {
     const int64_t groups = wgrad_groups(d);
@@ -1261,28 +1071,10 @@ static void wgrad_reduce(const RedJob &J, float *tmp, ConvDims d, hipStream_t st
                        groups);
 }
 
-static void wgrad_launch(int l, const uint16_t *xcm, const uint16_t *gcm, ConvDims d, float *part, float *dw,
-                         float *db, hipStream_t st)
-{
-    RedJob J{};
-    wgrad_slots_launch(l, xcm, gcm, d, part, dw, db, J, st);
-    uint64_t m = 0;
-    for (int k = 0; k < 4; ++k) m = slot_bytes(d, k) > m ? slot_bytes(d, k) : m;
-    wgrad_reduce(J, part + m / 4, d, st);
-}
-
-template <int C, bool SRC_F32>
-static void to_cm(const void *in, ConvDims d, uint16_t *out, hipStream_t st)
-{
-    const int64_t total = d.n * d.h * (int64_t)d.w * (C <= 4 ? 1 : C);
-    const int blocks = (int)(blocks_for(total, 256) < 8192 ? blocks_for(total, 256) : 8192);
-    hipLaunchKernelGGL((k_to_cm<C, SRC_F32>), dim3(blocks), dim3(256), 0, st, in, d.n * d.h, d.w, out);
-}
-
 hipError_t cnn_layer_forward(int l, const void *prep, const void *in, int64_t n, int h, int w, float *out_f32,
                              uint16_t *out_bf, hipStream_t st)
 {
-    conv_launch(l, false, in, ConvDims{n, h, w}, prep, l < 3, out_bf, out_f32, st);
+    conv_launch(l, in, ConvDims{n, h, w}, prep, l < 3, out_bf, out_f32, st);
     return hipGetLastError();
 }
 
@@ -1290,20 +1082,28 @@ hipError_t cnn_layer_backward(int l, const void *prep, const void *in, const uin
                               float *dw, float *db, float *dx_f32, void *scratch, hipStream_t st)
 {
     const ConvDims d{n, h, w};
-    const uint64_t cm = al256((uint64_t)n * h * w * 32 * 2);
-    uint16_t *xcm = static_cast<uint16_t *>(scratch);
-    uint16_t *gcm = reinterpret_cast<uint16_t *>(static_cast<char *>(scratch) + cm);
-    float *part = reinterpret_cast<float *>(static_cast<char *>(scratch) + 2 * cm);
+    const int R = wgrad_rows(d, l == 3 ? 3 : 1);
+    const int64_t units = wgrad_slots(d, l == 3 ? 3 : 1);
+    float *part = static_cast<float *>(scratch);
+    const dim3 grid((unsigned)units), block(256);
+    const uint16_t *act = static_cast<const uint16_t *>(in), *noact = nullptr;
+    const float *none = nullptr;
+    uint16_t *nodx = nullptr;
+    float *nof = nullptr;
     if (l == 0)
-        to_cm<3, true>(in, d, xcm, st);
+        hipLaunchKernelGGL((k_bwd<32, kBwdInput>), grid, block, 0, st, dy, noact, static_cast<const float *>(in), d, R,
+                           noact, nodx, nof, nof, part);
+    else if (l == 3)
+        hipLaunchKernelGGL((k_bwd<2, kBwdPlain>), grid, block, 0, st, dy, act, none, d, R, bwd_mat(prep, l), nodx, dx_f32,
+                           part, nof);
     else
-        to_cm<32, false>(in, d, xcm, st);
-    if (l == 3)
-        to_cm<2, false>(dy, d, gcm, st);
-    else
-        to_cm<32, false>(dy, d, gcm, st);
-    wgrad_launch(l, xcm, gcm, d, part, dw, db, st);
-    if (l > 0 && dx_f32) conv_launch(l, true, dy, d, prep, false, nullptr, dx_f32, st);
+        hipLaunchKernelGGL((k_bwd<32, kBwdPlain>), grid, block, 0, st, dy, act, none, d, R, bwd_mat(prep, l), nodx,
+                           dx_f32, part, nof);
+    RedJob J{};
+    add_seg(l, units, part, dw, db, J);
+    uint64_t m = 0;
+    for (int k = 0; k < 4; ++k) m = slot_bytes(d, k) > m ? slot_bytes(d, k) : m;
+    wgrad_reduce(J, part + m / 4, d, st);
     return hipGetLastError();
 }
 
@@ -1347,10 +1147,10 @@ uint64_t cnn_workspace_bytes(int64_t n, int h, int w) { return ws_layout(nullptr
 // forward through the four layers
 static void forward_layers(const void *prep, const float *x, ConvDims d, float *out, const CnnWs &s, hipStream_t st)
 {
-    conv_launch(0, false, x, d, prep, true, s.act[0], nullptr, st);
-    conv_launch(1, false, s.act[0], d, prep, true, s.act[1], nullptr, st);
-    conv_launch(2, false, s.act[1], d, prep, true, s.act[2], nullptr, st);
-    conv_launch(3, false, s.act[2], d, prep, false, nullptr, out, st);
+    conv_launch(0, x, d, prep, true, s.act[0], nullptr, st);
+    conv_launch(1, s.act[0], d, prep, true, s.act[1], nullptr, st);
+    conv_launch(2, s.act[1], d, prep, true, s.act[2], nullptr, st);
+    conv_launch(3, s.act[2], d, prep, false, nullptr, out, st);
 }
 
 hipError_t cnn_forward(const void *prep, const float *x, int64_t n, int h, int w, float *out, void *ws, hipStream_t st)
@@ -1382,14 +1182,15 @@ hipError_t cnn_train_step(float *params, float *adam_m, float *adam_v, int64_t t
         next += slot_bytes(d, l) / 4;
     }
     const float *none = nullptr;
+    float *nof = nullptr;
     const int R3 = wgrad_rows(d, 3), R1 = wgrad_rows(d, 1);   // (layers 1 and 2 alike)
     const int64_t u3 = wgrad_slots(d, 3), u1 = wgrad_slots(d, 1);
-    hipLaunchKernelGGL((k_bwd<2, false>), dim3((unsigned)u3), dim3(256), 0, st, s.gout, s.act[2], none, d, R3,
-                       bwd_mat(prep, 3), s.gh[0], part[3], (float *)nullptr);
-    hipLaunchKernelGGL((k_bwd<32, false>), dim3((unsigned)u1), dim3(256), 0, st, s.gh[0], s.act[1], none, d, R1,
-                       bwd_mat(prep, 2), s.gh[1], part[2], (float *)nullptr);
-    hipLaunchKernelGGL((k_bwd<32, true>), dim3((unsigned)u1), dim3(256), 0, st, s.gh[1], s.act[0], x, d, R1,
-                       bwd_mat(prep, 1), (uint16_t *)nullptr, part[1], part[0]);
+    hipLaunchKernelGGL((k_bwd<2, kBwdMasked>), dim3((unsigned)u3), dim3(256), 0, st, s.gout, s.act[2], none, d, R3,
+                       bwd_mat(prep, 3), s.gh[0], nof, part[3], nof);
+    hipLaunchKernelGGL((k_bwd<32, kBwdMasked>), dim3((unsigned)u1), dim3(256), 0, st, s.gh[0], s.act[1], none, d, R1,
+                       bwd_mat(prep, 2), s.gh[1], nof, part[2], nof);
+    hipLaunchKernelGGL((k_bwd<32, kBwdFirst>), dim3((unsigned)u1), dim3(256), 0, st, s.gh[1], s.act[0], x, d, R1,
+                       bwd_mat(prep, 1), (uint16_t *)nullptr, nof, part[1], part[0]);
     for (int l = 3; l >= 0; --l)
         add_seg(l, l == 3 ? u3 : u1, part[l], g + master_w(l), g + master_w(l) + 9 * kCi[l] * kCo[l], J);
     wgrad_reduce(J, next, d, st);

@@ -42,3 +42,39 @@ def test_step_gradient_with_the_gpus_roundings(shape):
         print(f"layer {l} {shape}: grad rel L2 w {ew:.2e} b {eb:.2e}")
         assert ew <= 1e-3 and eb <= 1e-3
         o += dw.size + db.size
+
+
+@pytest.mark.parametrize("shape", [(1, 32, 32), (3, 32, 96), (2, 128, 64)])
+def test_step_gradient_is_the_layers_in_a_row(shape):
+    """The training step's fused passes against the same kernel one layer at a
+    time (qsq_cnn_layer_backward: each held to the reference by itself), the
+    gradient handed on masked and rounded by torch.  Both sum in one order, so
+    only the loss gradient's exponential can differ, by a rounding: 1e-5, the
+    bound of one layer's accumulation, is held."""
+    import torch
+
+    from paper_1609_00724_amd import learn
+    prop, _, _, g, dev = _setup(31)
+    x, mask, logq = (torch.from_numpy(a).to(dev) for a in _batch(g, *shape))
+    lam, P = 0.1, mask.numel()
+    acts = [x]
+    for l in range(3):
+        acts.append(learn.to_bf16_bits(learn.layer_forward(prop, l, acts[-1])))
+    out = learn.layer_forward(prop, 3, acts[-1])
+    sig = 1 / (1 + torch.exp(-out[..., 0]))
+    dq = torch.where(torch.isfinite(logq), out[..., 1] - logq, torch.zeros_like(logq))
+    dy = torch.stack([(sig - mask).double() / P, 2.0 * float(np.float32(lam)) * dq.double() / P], -1).float()
+    want = []
+    for l in (3, 2, 1, 0):
+        dw, db, dx = learn.layer_backward(prop, l, acts[l], learn.to_bf16_bits(dy.contiguous()))
+        want = [dw, db, *want]
+        if l > 0:
+            dy = torch.where(learn.from_bf16_bits(acts[l]) > 0, dx, torch.zeros_like(dx))
+    _, grad = prop.train_step(x, mask, logq, lr=1e-3, lam=lam, want_grad=True)
+    torch.cuda.synchronize()
+    o = 0
+    for k, w in enumerate(want):
+        e = _rel_l2(grad[o:o + w.numel()].double().cpu().numpy(), w.double().cpu().numpy())
+        print(f"layer {k // 2} {'b' if k % 2 else 'w'} {shape}: rel L2 {e:.2e}")
+        assert e <= 1e-5
+        o += w.numel()
