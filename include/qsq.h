@@ -185,11 +185,14 @@ typedef struct qsq_trace_opts {
  *          256 lanes per compute unit, 1..15 (0: automatic, by the types, the
  *          field's size and the number of half-lines; at most 8)
  *   wg     workgroup size code: 0 = 256, 1 = 64, 2 = 128 lanes
- *   gather 0 = automatic: work lists short enough that the longest line sets
- *          the time (the list's length is compared on the device) are stepped
- *          with four lanes per half-line, in a launch shape of their own
- *          (trilinear Cartesian fields, records below 2 GiB); other lists 3
- *          where it applies, otherwise 1,
+ *   gather 0 = automatic: four lanes per half-line where that is faster, in a
+ *          launch shape of their own (the word's other fields are then not
+ *          read) -- Cartesian fields whose node records take less than 2 GiB -
+ *          64 MiB, with nx ny and nz below 2^23, and lists of half-lines
+ *          (counted on the device) up to a limit that the types, the stepper,
+ *          the field's size and the longest step set, 2^16 .. 2^19; quadratic
+ *          and cubic fields at any length.  Other lists 3 where it applies,
+ *          otherwise 1,
  *          1 = direct corner loads, 2 = per-lane LDS cache of
  *          the last cell's corners (FP32 or BF16 records and FP32 stepping,
  *          one field per call, field below 2 GiB; otherwise direct),
@@ -561,9 +564,12 @@ int qsq_vmap(const qsq_field *f, const qsq_volume_desc *d, const qsq_trace_opts 
 /* ---- measurement -------------------------------------------------------- */
 
 /* kernels the profiler times */
-#define QSQ_KERNEL_STEP 0       /* adaptive stepping kernel */
-#define QSQ_KERNEL_LAND 1       /* FP64 boundary landing */
-#define QSQ_KERNEL_ASSEMBLE 2   /* FP64 Q assembly */
+#define QSQ_KERNEL_STEP 0       /* stepping: the four-lane kernel and the one-lane
+                                   kernel of a call count as one */
+#define QSQ_KERNEL_LAND 1       /* FP64 boundary landing; with the Q assembly where
+                                   one kernel does both (calls up to 2^18 seeds,
+                                   batches up to 2^20, trilinear Euler up to 2^17) */
+#define QSQ_KERNEL_ASSEMBLE 2   /* FP64 Q assembly of the larger calls */
 
 /*
  * Kernel timing for benchmarks.  While enabled (process-wide), every launch of

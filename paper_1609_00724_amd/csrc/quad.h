@@ -490,7 +490,7 @@ __device__ __forceinline__ void quad_count(unsigned long long *work, const QuadC
         for (int k = 0; k < 4; ++k) atomicAdd(&work[k], v[k]);
 }
 
-// Stepping kernel of calls with few half-lines (quad_limit)
+// Stepping kernel of the lists that quad_list gives four lanes a line
 template <typename T, typename S, int MODE, bool BATCH, bool EULER>
 __global__ void __launch_bounds__(kQuadWg) k_trace_quad(TraceJob job)
 {

@@ -1,19 +1,25 @@
 // Field-line + deviation tracer for gfx950 (QSL Squasher, Sect. 3.1-3.5).
 //
-// Three kernels per trace call:
-//   k_trace    persistent wave64 lanes; each lane owns one half-line (seed x
-//              direction), takes adaptive Cash-Karp 5(4) steps of
-//              y = (x, dx1, dx2) under eq. (1) and eq. (5) in the stepping
-//              precision T, and retires when a trial step leaves the box or a
-//              stop condition holds.  Retired lanes are refilled from a device
-//              work counter with one atomic per wave (ballot + prefix count).
-//   k_land     FP64: re-solves the step that left the box for the step length
+// A trace call, after the seed pass and the work list (in spatial order):
+//   stepping   each half-line (seed x direction) takes adaptive Cash-Karp 5(4)
+//              steps of y = (x, dx1, dx2) under eq. (1) and eq. (5) in the
+//              stepping precision T until a trial step leaves the box or a
+//              stop condition holds.  k_trace: persistent wave64 lanes, one
+//              half-line each, refilled from a device work counter (ballot +
+//              prefix count).  k_trace_quad (quad.h): four lanes a half-line,
+//              for lists whose longest line sets the time.  Where the list's
+//              length decides, both are launched and one returns at once.
+//              k_trace_geo (quad_geo.h): general geometry.
+//   ends       FP64: the step that left the box re-solved for the step length
 //              whose 5th-order end lies on the first face crossed (regula
 //              falsi on the signed face distance, Anderson-Bjorck variant),
-//              then snaps to it.
-//   k_assemble FP64: per seed, projects the deviations perpendicular to the
-//              renormalised field at both ends and forms Q by eq. (10)-(11),
-//              the determinant form, the exit-face-plane Q and the length.
+//              then snapped to it; per seed, the deviations perpendicular to
+//              the renormalised field at both ends and Q by eq. (10)-(11), the
+//              determinant form, the exit-face-plane Q and the length.
+//              k_finish (finish.h) does both for calls of few seeds
+//              (finish_seeds); k_land, k_land_final (k_land_euler) and
+//              k_assemble for larger ones.  k_land_geo: general geometry.
+// launch_rules.h holds the rules that choose.
 //
 // Field records are 4-vectors per node (x fastest): PAPER mode holds
 // (Bhat, |B|) with Bhat = B/|B| formed on the nodes (footnote to Sect. 3.5);
