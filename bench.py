@@ -567,7 +567,9 @@ def traffic_file(name):
     return os.path.join(ROOT, "profiles", f"k_trace_traffic_{name}.json")
 
 
-KERNEL_SOURCES = ("paper_1609_00724_amd/csrc/trace.hip", "paper_1609_00724_amd/csrc/qsq_internal.h")
+# the stepping kernels' file and the headers it includes
+KERNEL_SOURCES = tuple(f"paper_1609_00724_amd/csrc/{f}" for f in (
+    "trace.hip", "qsq_internal.h", "launch_rules.h", "quad.h", "finish.h", "quad_geo.h"))
 
 
 def kernel_hash():

@@ -133,3 +133,14 @@ def test_kept_by_level_follows_the_bisection(dim, r):
         assert row["lines"] == len(want)
         assert row["attempts"] == len(want) * (10 * row["level"] + 1)
         assert row["max_attempts"] == 10 * row["level"] + 1
+
+
+def test_traffic_gate_covers_every_source_of_the_stepping_kernels():
+    """A header split off the kernels' file is hashed with it: figures taken
+    before a change in one are stale too."""
+    import re
+    d = os.path.join(ROOT, "paper_1609_00724_amd", "csrc")
+    src = open(os.path.join(d, "trace.hip")).read()
+    own = {f for f in re.findall(r'#include "([^"]+)"', src) if os.path.exists(os.path.join(d, f))}
+    assert {"quad.h", "finish.h"} <= own
+    assert own <= {os.path.basename(f) for f in bench.KERNEL_SOURCES}
