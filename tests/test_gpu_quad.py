@@ -167,3 +167,26 @@ def test_higher_orders(charges, order, storage, step, mode, stepper):
               step_dtype=step, stepper=stepper)
     assert ((r[0]["status"] & 0xFF) <= 5).sum() > 50
     assert _equal(*r)
+
+
+@pytest.mark.parametrize("n", [1, 17, 129, 20001])
+@pytest.mark.parametrize("geometry", ["cartesian", "spherical"])
+def test_work_counters_of_every_workgroup_arrive(charges, n, geometry):
+    # a workgroup adds its waves' counts in one piece: lists of part of a
+    # wave, of some waves of a workgroup, and of many workgroups
+    import torch
+
+    import paper_1609_00724_amd as q
+    b, origin, spacing = charges
+    if geometry == "spherical":
+        origin, spacing = (-0.3, -0.3, 1.0), tuple(w / (m - 1) for w, m in zip((0.6, 0.6, 0.5), N))
+    f = q.field_init(*(torch.from_numpy(c).cuda() for c in b), origin, spacing, storage="f32", geometry=geometry)
+    hi = [o + s * (m - 1) for o, s, m in zip(origin, spacing, N)]
+    rng = np.random.default_rng(n)
+    seeds = torch.from_numpy(rng.uniform(origin, hi, (n, 3))).cuda()
+    h = min(spacing)
+    out = q.trace(f, seeds, rtol=1e-4, atol=1e-4, h_init=0.1 * h, h_max=2 * h, want_steps=True, want_work=True)
+    steps = out["steps"]
+    attempts, evals, halves, landed = out["work"].tolist()
+    assert attempts == int(steps.sum()) and halves == int((steps > 0).sum())
+    assert 5 * attempts < evals <= 6 * attempts and (n == 1 or landed > 0) and landed <= halves
