@@ -12,6 +12,7 @@ struct StepCall {
     int record;             // bytes of a node record: 8, 16 or 32
     uint64_t field;         // bytes of the field's node records
     bool spread;            // lines spread through the box: most seeds send one both ways
+    bool volume;            // lines from the cells of a volume map, in curve order
     int64_t halves;         // half-lines at most
     double cap;             // longest step, in cells
 };
@@ -39,10 +40,30 @@ enum StepLoads { kLoadsDirect, kLoadsCells, kLoadsLds, kLoadsRegs, kLoadsBricks,
 // 64, 1-cell cap, 5.02 against 5.48).  One million seeds on the bottom face of
 // 224 x 224 x 112, 4-cell cap: 1.17 with three, 1.21 with two.  BF16 bricks are half the
 // size and gain from three throughout (1.18 against 1.26 ms).
+//   A volume's lines fill the box too, but neighbours of the list are neighbours
+// in space, so the line lies at larger fields, and lists of up to 2^19
+// half-lines gain from the longer queue of each lane.  FP64
+// stepping, 128^3 cells and a level, 4-cell cap: 384 x 384 x 256 FP32 records 100.3 ms
+// with two waves, 60.6 with one, 224 x 224 x 112 23.2 and 20.5, 128 x 128 x 64 10.8
+// and 11.9; BF16 records 224 x 224 x 112 17.2 and 17.8, 384 x 384 x 256 79.2 and 47.4.
+// Register caches, three waves and two: 384 x 384 x 256 66.2 and 56.7 (1-cell cap
+// 90.3 and 86.4), 224 x 224 x 112 18.1 and 16.3 (1-cell cap 31.9 and 34.5), 128 x 128
+// x 64 8.55 and 8.92; bricks 38.2 and 34.5 (1-cell cap 74.1 and 78.9), 14.0 and 14.3,
+// 8.5 and 8.9.  64^3 cells and a level, 8-cell cap: FP64 stepping 128 x 128 x 64 2.89
+// and 2.84, nodes 2.67 and 2.54, bricks 224 x 224 x 112 4.13 and 4.00.
+constexpr int64_t kShortList = (int64_t)1 << 19;
 inline int auto_waves(const StepCall &c, StepLoads loads)
 {
     if (c.euler || c.batch) return 0;
-    if (c.step64) return c.halves <= (int64_t)1 << 19 || (c.spread && c.field > (uint64_t)8 << 20) ? 1 : 0;
+    if (c.volume) {
+        const uint64_t MB = (uint64_t)1 << 20;
+        const bool few = c.halves <= kShortList;
+        if (c.step64) return few || c.field > 64 * MB ? 1 : 0;
+        if (loads == kLoadsRegs) return few || c.field > (c.cap <= 2.0 ? 256 : 32) * MB ? 2 : 0;
+        if (loads == kLoadsBricks && c.record == 16) return few || (c.cap > 2.0 && c.field > 256 * MB) ? 2 : 0;
+        return 0;
+    }
+    if (c.step64) return c.halves <= kShortList || (c.spread && c.field > (uint64_t)8 << 20) ? 1 : 0;
     const uint64_t MB = (uint64_t)1 << 20;
     const bool caches = loads == kLoadsRegs || (loads == kLoadsBricks && c.record == 16);
     if (caches) return c.spread && c.field > 4 * MB && !(c.cap <= 2.0 && c.field <= 32 * MB) ? 2 : 0;

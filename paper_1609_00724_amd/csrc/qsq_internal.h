@@ -124,9 +124,10 @@ struct TraceJob {
     // work lists of up to this many half-lines are stepped with four lanes per
     // line (0: none)
     int64_t quad_max;
+    bool volume;        // the seeds are a volume map's
     // workgroups of the one-lane stepping kernel that a list of more than
-    // few_from half-lines keeps to (filled in at its launch)
-    int64_t few_from;
+    // few_from or at most few_upto half-lines keeps to (filled in at its launch)
+    int64_t few_from, few_upto;
     int few;
     int simds;          // SIMDs of the device
     bool quad_ok;       // the field's records are addressable by the four-lane kernels

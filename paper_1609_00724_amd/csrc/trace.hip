@@ -1223,6 +1223,12 @@ constexpr int trace_waves(int most)
     return most ? (any ? 8 : 2) : three ? 3 : 1;
 }
 
+// a list that the first job.few workgroups step (TraceJob)
+__device__ __forceinline__ bool keeps_to_few(const TraceJob &job, int64_t total)
+{
+    return total > job.few_from || total <= job.few_upto;
+}
+
 // values formed here, not where they are used last
 template <typename T>
 __device__ __forceinline__ void hold(T v[3])
@@ -1259,7 +1265,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(trace_
     const int lane = (int)(threadIdx.x & 63);
     const int64_t total = *job.rec.n_work;
     if (total <= job.quad_max) return;   // the four-lane kernel's call, or nothing to do
-    if (total > job.few_from && (int)blockIdx.x >= job.few) return;
+    if (keeps_to_few(job, total) && (int)blockIdx.x >= job.few) return;
 
     // lane state
     double X[3] = {0, 0, 0}, s = 0.0;
@@ -2208,7 +2214,7 @@ static __global__ void k_part_counters(TraceJob job, int blocks, int wg, int npa
         if (p == 0) job.counter[kPartCounter] = (unsigned long long)qblocks * (kQuadWg / 64) * 16;
         return;
     }
-    if (total > job.few_from) blocks = job.few;
+    if (keeps_to_few(job, total)) blocks = job.few;
     const int64_t nb = p < blocks ? (blocks - p + nparts - 1) / nparts : 0;
     job.counter[kPartCounter + p] = (unsigned long long)(total * p / nparts + nb * wg);
 }
@@ -2325,6 +2331,7 @@ static StepCall step_call(const TraceJob &job, bool step64, bool batch, int64_t 
     c.step64 = step64;
     c.euler = job.o.stepper == QSQ_STEPPER_EULER;
     c.batch = batch;
+    c.volume = job.volume;
     c.record = job.storage == QSQ_F64 ? 32 : job.storage == QSQ_F32 ? 16 : 8;
     c.field = (uint64_t)g.n[0] * (uint64_t)g.n[1] * (uint64_t)g.n[2] * (uint64_t)c.record;
     c.halves = 2 * n_max;
@@ -2416,24 +2423,27 @@ static hipError_t launch_typed(const TraceJob &job, hipStream_t st)
         (void)gather;
         kern = trace_kernel<T, S, MODE, kGatherDirect, BATCH>(euler);
     }
-    // workgroups that stay resident; of a trace's list that turns out to be
-    // spread (only the device knows its length), the first `few`
+    // workgroups that stay resident; of a list that turns out to be spread (of
+    // a trace) or short (of a volume), which only the device knows, the first `few`
     const int64_t resident = (int64_t)cus * resident_blocks(kern, wg, lds);
-    auto cap_blocks = [&](bool spread) {
+    auto cap_blocks = [&](bool spread, int64_t halves) {
         int units = lanes;   // (256 lanes a compute unit: one wave per SIMD)
         if (units == 0 && interp_order<MODE>() == 1) {
             StepCall c = step_call(job, sizeof(T) == 8, BATCH, n_max);
             c.spread = spread;
+            c.halves = halves;
             units = auto_waves(c, loads);
         }
         const int64_t b = (int64_t)cus * (units ? units : 8) * (256 / wg);
         return b < resident ? b : resident;
     };
     const int64_t want = (2 * n_max + wg - 1) / wg;
-    const int blocks = (int)(want < cap_blocks(false) ? want : cap_blocks(false));
+    const int blocks = (int)(want < cap_blocks(false, 2 * n_max) ? want : cap_blocks(false, 2 * n_max));
     TraceJob js = job;
-    js.few = job.spatial_bits > 0 && cap_blocks(true) < blocks ? (int)cap_blocks(true) : blocks;
-    js.few_from = spread_halves(n_max);
+    const int64_t few = job.spatial_bits > 0 ? cap_blocks(true, 2 * n_max) : job.volume ? cap_blocks(false, kShortList) : blocks;
+    js.few = few < blocks ? (int)few : blocks;
+    js.few_from = job.spatial_bits > 0 ? spread_halves(n_max) : 2 * n_max;
+    js.few_upto = job.volume ? kShortList : 0;
     const int nparts = (job.o.launch >> 9) & 1 ? kParts : 1;
     // few half-lines: four lanes each.  The count is known on the device
     // only, so where it may fall on either side both kernels are launched and

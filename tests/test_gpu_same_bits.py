@@ -125,3 +125,29 @@ def test_spread_lists_keep_to_fewer_workgroups(step, parts):
         torch.cuda.synchronize()
         assert _equal(*r)
         assert int(r[0]["work"][2]) > (1.5 if not bottom else 0.5) * seeds
+
+
+@pytest.mark.parametrize("storage,step", [("f32", "f64"), ("f32", "f32"), ("f64", "f64")])
+def test_volume_whose_levels_keep_to_fewer_workgroups(charges, storage, step):  # noqa: F811
+    """A volume whose base list is long and whose levels' lists are short, in
+    one set of workgroups or some of it: the same samples as with a named
+    number of lanes, the work counted in full."""
+    import torch
+
+    import paper_1609_00724_amd as q
+    from paper_1609_00724_amd import _abi as A
+    from paper_1609_00724_amd.api import make_opts
+    f = _field(charges, storage, "paper")
+    h = min(charges[2])
+    spec = q.VolumeSpec(-1.0, 1.0, -1.0, 1.0, 0.0, 1.0, 7, 1, 7, 0.3, 1)
+    got = []
+    for lanes in (0, 1, 2):
+        plan = q.QMapPlan(spec, 2**22, "cuda", want_steps=True)
+        plan.run(f, make_opts(1e-2, 1e-2, 0.1 * h, 8 * h, step_dtype=step, launch=A.launch_word(lanes, 256, 0)))
+        r = plan.result()
+        assert int(plan.work[0]) == int(r["steps"].sum())
+        got.append({k: r[k].double() for k in ("keys", "fll", "q_perp", "status", "steps")})
+    n = got[0]["keys"].shape[0]
+    assert 2**21 < n < 2**21 + 2**18      # the levels' lists are short
+    for other in got[1:]:
+        assert _equal(got[0], other)

@@ -31,6 +31,7 @@ int main(int argc, char **argv)
         if (!strcmp(k, "record")) c.record = (int)x;
         if (!strcmp(k, "field")) c.field = (uint64_t)x;
         if (!strcmp(k, "spread")) c.spread = x != 0;
+        if (!strcmp(k, "volume")) c.volume = x != 0;
         if (!strcmp(k, "halves")) c.halves = (int64_t)x;
         if (!strcmp(k, "cap")) c.cap = x;
         if (!strcmp(k, "loads")) loads = (int)x;
@@ -106,3 +107,32 @@ def test_one_kernel_ends_only_the_calls_it_is_faster_for(ask):
     assert ask("finish", euler=1) == ask("finish", euler=1, batch=1) == 1 << 17
     assert ask("finish", euler=1, order=2) == ask("finish") == 1 << 18
     assert ask("finish", batch=1) == 1 << 20
+
+
+def test_volumes_keep_fewer_waves_where_their_fields_overflow_the_caches(ask):
+    # 128^3 cells and a level: FP64 stepping, 384 x 384 x 256 FP32 records: 60.6 ms with one wave, 100.3 with two
+    def waves(n, seeds=2**21, **kw):
+        return ask("waves", n, seeds, spread=0, volume=1, **kw)
+    for rec in (16, 32):
+        assert waves((384, 384, 256), step64=1, record=rec) == 1
+        assert waves((224, 224, 112), step64=1, record=rec) == 1
+        assert waves((128, 128, 64), step64=1, record=rec) == 0
+    assert waves((384, 384, 256), step64=1, record=8) == 1
+    assert waves((224, 224, 112), step64=1, record=8) == 0
+    # register caches: 56.7 ms with two waves, 66.2 with three; a 1-cell cap 86.4 and 90.3
+    assert waves((384, 384, 256), cap=4.0, loads=REGS) == 2
+    assert waves((384, 384, 256), cap=1.0, loads=REGS) == 2
+    assert waves((224, 224, 112), cap=4.0, loads=REGS) == 2
+    assert waves((224, 224, 112), cap=1.0, loads=REGS) == 0
+    assert waves((128, 128, 64), cap=4.0, loads=REGS) == 0
+    # bricks: 34.5 against 38.2 ms, a 1-cell cap 78.9 against 74.1
+    assert waves((384, 384, 256), cap=4.0, loads=BRICKS) == 2
+    assert waves((384, 384, 256), cap=1.0, loads=BRICKS) == 0
+    assert waves((224, 224, 112), cap=4.0, loads=BRICKS) == 0
+    # the longer queue of each lane evens out the ends of short lists
+    assert waves((128, 128, 64), 2**18, step64=1) == 1
+    assert waves((128, 128, 64), 2**18, cap=8.0, loads=REGS) == 2
+    assert waves((224, 224, 112), 2**18, cap=8.0, loads=BRICKS) == 2
+    # a slice's samples are no volume's
+    assert ask("waves", (384, 384, 256), 2**20, spread=0, step64=1) == 0
+    assert ask("waves", (384, 384, 256), 2**20, spread=0, cap=4.0, loads=REGS) == 0
