@@ -13,6 +13,7 @@ struct StepCall {
     uint64_t field;         // bytes of the field's node records
     bool spread;            // lines spread through the box: most seeds send one both ways
     bool volume;            // lines from the cells of a volume map, in curve order
+    bool lattice;           // the base lattice of a map: all its cells, in curve order
     int64_t halves;         // half-lines at most
     double cap;             // longest step, in cells
 };
@@ -79,9 +80,15 @@ inline int auto_waves(const StepCall &c, StepLoads loads)
 // 000 seeds 0.67 against 0.73 ms, 1.2 M 0.83 against 0.90.  A trilinear Euler step is
 // landed without a root find, and the separate kernels overtake sooner: landing and
 // Q of 60 000 random seeds 31 against 39 us, 131 072 58 and 52, 200 000 85 and 74; in a
-// batch 109 000 43 and 47, 217 000 75 and 69.
+// batch 109 000 43 and 47, 217 000 75 and 69.  The base lattice of a map comes side
+// by side: 512^2 cells of FP32 and BF16 records 0.226 and 0.236 ms against 0.204 and
+// 0.199 (64^3 of a volume 0.716 and 0.689 against 0.679 and 0.618), 256^2 0.09 and 0.09
+// against 0.16 and 0.15; a slice of FP64 records that lines leave both ways 0.376 against
+// 0.319.  64^3 cells of FP64 records k_finish takes faster (1.06 against 1.07, of 224 x
+// 224 x 112 nodes 1.22 against 1.33).
 inline int64_t finish_seeds(const StepCall &c, int order)
 {
+    if (c.lattice && order == 1 && (c.record < 32 || !c.volume)) return (int64_t)1 << 17;
     if (c.euler && order == 1) return (int64_t)1 << 17;
     return (int64_t)1 << (c.batch ? 20 : 18);
 }

@@ -1094,7 +1094,9 @@ static hipError_t launch_map(const qsq_field *f, const Geom &g, const StepOpts &
         job.q_perp = A.q;
         job.status = A.status;
         job.steps = A.att;
+        job.lattice = true;
         e = launch_trace(job, step_dtype, st);
+        job.lattice = false;
         if (e != hipSuccess) return e;
     }
     // every stepping launch after the base lattice (proposals, refinement

@@ -125,6 +125,7 @@ struct TraceJob {
     // line (0: none)
     int64_t quad_max;
     bool volume;        // the seeds are a volume map's
+    bool lattice;       // the seeds are a map's base lattice
     // workgroups of the one-lane stepping kernel that a list of more than
     // few_from or at most few_upto half-lines keeps to (filled in at its launch)
     int64_t few_from, few_upto;

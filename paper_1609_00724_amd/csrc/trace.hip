@@ -2332,6 +2332,7 @@ static StepCall step_call(const TraceJob &job, bool step64, bool batch, int64_t 
     c.euler = job.o.stepper == QSQ_STEPPER_EULER;
     c.batch = batch;
     c.volume = job.volume;
+    c.lattice = job.lattice;
     c.record = job.storage == QSQ_F64 ? 32 : job.storage == QSQ_F32 ? 16 : 8;
     c.field = (uint64_t)g.n[0] * (uint64_t)g.n[1] * (uint64_t)g.n[2] * (uint64_t)c.record;
     c.halves = 2 * n_max;
