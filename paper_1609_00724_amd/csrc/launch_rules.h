@@ -13,6 +13,7 @@ struct StepCall {
     uint64_t field;         // bytes of the field's node records
     bool spread;            // lines spread through the box: most seeds send one both ways
     bool volume;            // lines from the cells of a volume map, in curve order
+    bool slice;             // lines of a slice map, in curve order
     bool lattice;           // the base lattice of a map: all its cells, in curve order
     int64_t halves;         // half-lines at most
     double cap;             // longest step, in cells
@@ -32,7 +33,8 @@ enum StepLoads { kLoadsDirect, kLoadsCells, kLoadsLds, kLoadsRegs, kLoadsBricks,
 // ms with two and 3.16 with one, and from 500 000 seeds on the bottom face of
 // 224 x 224 x 112 3.10 and 3.34.  Up to 2^19 half-lines the longer queue of each
 // lane evens out the ends as well (280 000 over 64 x 64 x 32 cells 1.67 against
-// 1.27 ms).
+// 1.27 ms), save for the side by side lines of a slice over BF16 records (512^2 pixels
+// and a level, 256 x 256 x 128 cells at a 2-cell cap, 3.00 with two, 3.18 with one).
 //   FP32 stepping, register caches (three fit): the third wave's cells push the
 // others' out of the L1 and the L2: one million seeds, 4-cell cap, 224 x 224 x 112
 // FP32 records 6.98 ms with three waves, 5.74 with two; 128 x 128 x 64 2.54 against
@@ -64,7 +66,7 @@ inline int auto_waves(const StepCall &c, StepLoads loads)
         if (loads == kLoadsBricks && c.record == 16) return few || (c.cap > 2.0 && c.field > 256 * MB) ? 2 : 0;
         return 0;
     }
-    if (c.step64) return c.halves <= kShortList || (c.spread && c.field > (uint64_t)8 << 20) ? 1 : 0;
+    if (c.step64) return (c.halves <= kShortList && !(c.slice && c.record == 8)) || (c.spread && c.field > (uint64_t)8 << 20) ? 1 : 0;
     const uint64_t MB = (uint64_t)1 << 20;
     const bool caches = loads == kLoadsRegs || (loads == kLoadsBricks && c.record == 16);
     if (caches) return c.spread && c.field > 4 * MB && !(c.cap <= 2.0 && c.field <= 32 * MB) ? 2 : 0;
@@ -111,6 +113,12 @@ inline int64_t spread_halves(int64_t n) { return n + n / 2; }
 // many waves resident and a batch reloads its grid with every line: up to 2^17
 // (FP64, 128^2 x 64 cells at 1 cell: 128 000 half-lines 1.53 against 1.74 ms, 256 000
 // 2.45 against 2.34).
+//   The later lists of a slice hold its longest lines, side by side, and a lane's
+// neighbours share its cells: FP64 stepping over BF16 records, 63 000 half-lines of
+// 224 x 224 x 112 cells at a 1-cell cap, takes 3.5 ms with four lanes a line, two lines
+// one after another in each quad, and 3.04 with one lane.  Lists of half as many gain
+// from four (a 512^2 map's), and so do all over FP32 and FP64 records (1024^2 pixels and
+// a level 8.1 and 10.3 ms against 8.4 and 11.2 with one lane throughout).
 //   An Euler step has one evaluation, and one lane's does little beside it.  While
 // the caches hold a field of FP32 or BF16 records, lists of up to 2^17 gain (128^2
 // x 64 cells, FP32 records: 64 000 half-lines 0.77 against 1.25 ms, 128 000 1.21
@@ -128,6 +136,7 @@ inline int64_t quad_list(const StepCall &c, double edge, int order)
 {
     if (order > 1) return (int64_t)1 << 30;
     if (!(edge >= 32.0)) return (int64_t)1 << 16;
+    if (c.slice && !c.euler && c.step64 && c.record == 8) return (int64_t)3 << 14;
     if (c.euler && !c.batch && c.record < 32 && c.field <= (uint64_t)64 << 20) return (int64_t)1 << (c.step64 ? 16 : 17);
     return (int64_t)1 << (c.step64 || c.batch ? 17 : 19);
 }

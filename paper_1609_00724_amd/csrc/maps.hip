@@ -1076,6 +1076,7 @@ static hipError_t launch_map(const qsq_field *f, const Geom &g, const StepOpts &
     carve_records(base + Lo.trace, Lo.tcap, &job.rec, &job.counter);
     job.out_stride = Lo.tcap;
     job.steps_sum = 1;
+    job.slice = DIM == 2;
     job.volume = DIM == 3;
     job.work = reinterpret_cast<unsigned long long *>(out->work);
 

@@ -124,7 +124,7 @@ struct TraceJob {
     // work lists of up to this many half-lines are stepped with four lanes per
     // line (0: none)
     int64_t quad_max;
-    bool volume;        // the seeds are a volume map's
+    bool slice, volume; // the seeds are a slice or volume map's
     bool lattice;       // the seeds are a map's base lattice
     // workgroups of the one-lane stepping kernel that a list of more than
     // few_from or at most few_upto half-lines keeps to (filled in at its launch)

@@ -2331,6 +2331,7 @@ static StepCall step_call(const TraceJob &job, bool step64, bool batch, int64_t 
     c.step64 = step64;
     c.euler = job.o.stepper == QSQ_STEPPER_EULER;
     c.batch = batch;
+    c.slice = job.slice;
     c.volume = job.volume;
     c.lattice = job.lattice;
     c.record = job.storage == QSQ_F64 ? 32 : job.storage == QSQ_F32 ? 16 : 8;

@@ -32,6 +32,7 @@ int main(int argc, char **argv)
         if (!strcmp(k, "field")) c.field = (uint64_t)x;
         if (!strcmp(k, "spread")) c.spread = x != 0;
         if (!strcmp(k, "volume")) c.volume = x != 0;
+        if (!strcmp(k, "slice")) c.slice = x != 0;
         if (!strcmp(k, "lattice")) c.lattice = x != 0;
         if (!strcmp(k, "halves")) c.halves = (int64_t)x;
         if (!strcmp(k, "cap")) c.cap = x;
@@ -148,3 +149,15 @@ def test_large_lattices_end_in_separate_kernels(ask):
     assert ask("finish", lattice=1, volume=1, record=32) >= 8**6    # FP64 records: k_finish ahead
     assert ask("finish", lattice=1, record=16, order=3) == 2**18
     assert ask("finish", record=16) == 2**18                # a trace, a map's rounds
+
+
+def test_fp64_lists_of_slices_over_bf16_records(ask):
+    # 63 000 half-lines: 3.04 ms on one lane a line, 3.5 on four
+    assert 30000 < ask("quads", step64=1, slice=1, record=8) < 63000
+    assert ask("quads", step64=1, slice=1, record=16) == 2**17
+    assert ask("quads", step64=1, slice=1, record=32) == 2**17
+    assert ask("quads", step64=1, record=8) == 2**17      # a trace's list
+    assert ask("quads", slice=1, record=8) == 2**19
+    # 512^2 pixels: 3.00 ms with two waves, 3.18 with one
+    assert ask("waves", (256, 256, 128), 2**18, step64=1, slice=1, spread=0, record=8) == 0
+    assert ask("waves", (256, 256, 128), 2**18, step64=1, slice=1, spread=0, record=16) == 1
