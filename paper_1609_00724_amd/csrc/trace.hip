@@ -1213,14 +1213,18 @@ static __global__ void k_land_compact(TraceJob job)
 // 200 000 half-lines 1.78 against 1.52, BF16 1.43 against 1.32.
 // BF16 node records have the widening of each value on top, and 168 registers
 // spill (500 000 lines of 224 x 224 x 112 cells, 4-cell cap: 3.27 ms with three
-// waves, 2.64 with two).
-template <typename T, typename S, int GATHER, bool EULER>
+// waves, 2.64 with two).  FP64 stepping of a batch over FP32 or FP64 records holds
+// more than 256 registers, one wave, and is told so: scheduled for two it missed
+// them by 10 and took 85.8 ms for 15.9 M lines of 64 fields, 79.7 so; forced to two
+// it spills 16, 76.4 there but 2.9 against 2.3 for 186 000 lines of two fields.
+template <typename T, typename S, int GATHER, bool BATCH, bool EULER>
 constexpr int trace_waves(int most)
 {
     const bool three =
         EULER || (GATHER == kGatherRegs && !std::is_same<S, Bf16>::value) || GATHER == kGatherBricks;
     const bool any = sizeof(T) == 8 || three || GATHER == kGatherCells;
-    return most ? (any ? 8 : 2) : three ? 3 : 1;
+    const bool one = sizeof(T) == 8 && BATCH && !EULER && !std::is_same<S, Bf16>::value;
+    return most ? (one ? 1 : any ? 8 : 2) : three ? 3 : 1;
 }
 
 // a list that the first job.few workgroups step (TraceJob)
@@ -1245,7 +1249,7 @@ __device__ __forceinline__ double uniform(double v) { return v; }
 
 // (the Euler variants fit 3 waves per SIMD: one evaluation's state per step)
 template <typename T, typename S, int MODE, int GATHER, bool BATCH, bool EULER = false>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(trace_waves<T, S, GATHER, EULER>(0), trace_waves<T, S, GATHER, EULER>(1)))) k_trace(TraceJob job)
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(trace_waves<T, S, GATHER, BATCH, EULER>(0), trace_waves<T, S, GATHER, BATCH, EULER>(1)))) k_trace(TraceJob job)
 {
     static_assert(GATHER == kGatherDirect || (!BATCH && sizeof(T) == 4),
                   "cell caches: one field per launch, FP32 corner values");
