@@ -54,10 +54,14 @@ enum StepLoads { kLoadsDirect, kLoadsCells, kLoadsLds, kLoadsRegs, kLoadsBricks,
 // x 64 8.55 and 8.92; bricks 38.2 and 34.5 (1-cell cap 74.1 and 78.9), 14.0 and 14.3,
 // 8.5 and 8.9.  64^3 cells and a level, 8-cell cap: FP64 stepping 128 x 128 x 64 2.89
 // and 2.84, nodes 2.67 and 2.54, bricks 224 x 224 x 112 4.13 and 4.00.
+//   A batch keeps what fits, but for its short lists of FP64 stepping over BF16 records:
+// 186 000 lines of two fields of 64 to 128 nodes 2.98 ms with two waves, 2.45 with
+// one (354 000 of six 3.59 and 3.95).
 constexpr int64_t kShortList = (int64_t)1 << 19;
 inline int auto_waves(const StepCall &c, StepLoads loads)
 {
-    if (c.euler || c.batch) return 0;
+    if (c.euler) return 0;
+    if (c.batch) return c.step64 && c.record == 8 && c.halves <= kShortList ? 1 : 0;
     if (c.volume) {
         const uint64_t MB = (uint64_t)1 << 20;
         const bool few = c.halves <= kShortList;

@@ -161,3 +161,11 @@ def test_fp64_lists_of_slices_over_bf16_records(ask):
     # 512^2 pixels: 3.00 ms with two waves, 3.18 with one
     assert ask("waves", (256, 256, 128), 2**18, step64=1, slice=1, spread=0, record=8) == 0
     assert ask("waves", (256, 256, 128), 2**18, step64=1, slice=1, spread=0, record=16) == 1
+
+
+def test_short_fp64_batches_over_bf16_records_keep_one_wave(ask):
+    # 186 000 lines: 2.45 ms with one wave, 2.98 with two; 354 000 3.95 and 3.59
+    assert ask("waves", seeds=186000, step64=1, batch=1, record=8) == 1
+    assert ask("waves", seeds=354000, step64=1, batch=1, record=8) == 0
+    assert ask("waves", seeds=186000, step64=1, batch=1, record=16) == 0
+    assert ask("waves", seeds=186000, batch=1, record=8) == 0
