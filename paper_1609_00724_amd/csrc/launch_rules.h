@@ -117,12 +117,6 @@ inline int64_t spread_halves(int64_t n) { return n + n / 2; }
 // many waves resident and a batch reloads its grid with every line: up to 2^17
 // (FP64, 128^2 x 64 cells at 1 cell: 128 000 half-lines 1.53 against 1.74 ms, 256 000
 // 2.45 against 2.34).
-//   The later lists of a slice hold its longest lines, side by side, and a lane's
-// neighbours share its cells: FP64 stepping over BF16 records, 63 000 half-lines of
-// 224 x 224 x 112 cells at a 1-cell cap, takes 3.5 ms with four lanes a line, two lines
-// one after another in each quad, and 3.04 with one lane.  Lists of half as many gain
-// from four (a 512^2 map's), and so do all over FP32 and FP64 records (1024^2 pixels and
-// a level 8.1 and 10.3 ms against 8.4 and 11.2 with one lane throughout).
 //   An Euler step has one evaluation, and one lane's does little beside it.  While
 // the caches hold a field of FP32 or BF16 records, lists of up to 2^17 gain (128^2
 // x 64 cells, FP32 records: 64 000 half-lines 0.77 against 1.25 ms, 128 000 1.21
@@ -140,7 +134,6 @@ inline int64_t quad_list(const StepCall &c, double edge, int order)
 {
     if (order > 1) return (int64_t)1 << 30;
     if (!(edge >= 32.0)) return (int64_t)1 << 16;
-    if (c.slice && !c.euler && c.step64 && c.record == 8) return (int64_t)3 << 14;
     if (c.euler && !c.batch && c.record < 32 && c.field <= (uint64_t)64 << 20) return (int64_t)1 << (c.step64 ? 16 : 17);
     return (int64_t)1 << (c.step64 || c.batch ? 17 : 19);
 }

@@ -151,13 +151,9 @@ def test_large_lattices_end_in_separate_kernels(ask):
     assert ask("finish", record=16) == 2**18                # a trace, a map's rounds
 
 
-def test_fp64_lists_of_slices_over_bf16_records(ask):
-    # 63 000 half-lines: 3.04 ms on one lane a line, 3.5 on four
-    assert 30000 < ask("quads", step64=1, slice=1, record=8) < 63000
-    assert ask("quads", step64=1, slice=1, record=16) == 2**17
-    assert ask("quads", step64=1, slice=1, record=32) == 2**17
-    assert ask("quads", step64=1, record=8) == 2**17      # a trace's list
-    assert ask("quads", slice=1, record=8) == 2**19
+def test_fp64_stepping_of_slices_over_bf16_records(ask):
+    # 256^2 pixels, 65 536 half-lines: four lanes a line 1.3 times one lane's speed
+    assert ask("quads", step64=1, slice=1, record=8) == 2**17
     # 512^2 pixels: 3.00 ms with two waves, 3.18 with one
     assert ask("waves", (256, 256, 128), 2**18, step64=1, slice=1, spread=0, record=8) == 0
     assert ask("waves", (256, 256, 128), 2**18, step64=1, slice=1, spread=0, record=16) == 1
