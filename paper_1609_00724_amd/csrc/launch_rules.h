@@ -33,8 +33,9 @@ enum StepLoads { kLoadsDirect, kLoadsCells, kLoadsLds, kLoadsRegs, kLoadsBricks,
 // ms with two and 3.16 with one, and from 500 000 seeds on the bottom face of
 // 224 x 224 x 112 3.10 and 3.34.  Up to 2^19 half-lines the longer queue of each
 // lane evens out the ends as well (280 000 over 64 x 64 x 32 cells 1.67 against
-// 1.27 ms), save for the side by side lines of a slice over BF16 records (512^2 pixels
-// and a level, 256 x 256 x 128 cells at a 2-cell cap, 3.00 with two, 3.18 with one).
+// 1.27 ms), save for the side by side lines of a slice over FP32 or BF16 records (512^2
+// pixels and a level, 256 x 256 x 128 cells at a 2-cell cap, BF16 3.00 with two, 3.18
+// with one).
 //   FP32 stepping, register caches (three fit): the third wave's cells push the
 // others' out of the L1 and the L2: one million seeds, 4-cell cap, 224 x 224 x 112
 // FP32 records 6.98 ms with three waves, 5.74 with two; 128 x 128 x 64 2.54 against
@@ -70,7 +71,7 @@ inline int auto_waves(const StepCall &c, StepLoads loads)
         if (loads == kLoadsBricks && c.record == 16) return few || (c.cap > 2.0 && c.field > 256 * MB) ? 2 : 0;
         return 0;
     }
-    if (c.step64) return (c.halves <= kShortList && !(c.slice && c.record == 8)) || (c.spread && c.field > (uint64_t)8 << 20) ? 1 : 0;
+    if (c.step64) return (c.halves <= kShortList && !(c.slice && c.record < 32)) || (c.spread && c.field > (uint64_t)8 << 20) ? 1 : 0;
     const uint64_t MB = (uint64_t)1 << 20;
     const bool caches = loads == kLoadsRegs || (loads == kLoadsBricks && c.record == 16);
     if (caches) return c.spread && c.field > 4 * MB && !(c.cap <= 2.0 && c.field <= 32 * MB) ? 2 : 0;
